@@ -334,6 +334,7 @@ int launch_rotate(Ctx& c, int prec, const RotArgs& a);
 int launch_residual(Ctx& c, int prec, int x_blk, int hx_blk, int ncol, const int* active);
 int launch_check(Ctx& c, int* active, double tol);
 void init_kernel_attributes();
+void init_rr_attributes();
 int launch_gram_rows(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T, int kT,
                      long long out_off, int rows_e, int sym);
 // symmetric S^T T (to out_off_st) and S^T S (to out_off_ss) from one staging of [S | T]

@@ -4,40 +4,14 @@
 //    Algorithm 1 step 5; and Y^T Y, Y^T H Y of Algorithm 2 steps 3-4):
 //    tall-skinny TN products, split over the grid dimension N, FP64 partial
 //    tiles, then a fixed-order reduction (deterministic).
-//  * Rayleigh-Ritz on the small projected problem, FP64, one workgroup per
-//    element: diagonal scaling, Cholesky S^T S = U^T U, U^{-1}, the standard
-//    problem U^{-T} A U^{-1}, Householder tridiagonalisation, Sturm
-//    multisection and inverse iteration, then the coefficients C = D U^{-1} V
-//    of the lowest eigenpairs.
 //  * Rotations X <- S C (Eq. (2), Algorithm 1 steps 6-7; Algorithm 2 step 5).
 //  * Residual norms ||H x_i - theta_i x_i|| and the preconditioner energy.
-#include "dg_internal.h"
-#include "tridiag.h"
-#include "wave_ops.h"
+#include "dense_ops.h"
 
 #include <algorithm>
 #include <cstdio>
 
 namespace dg {
-
-// column-count codes: > 0 explicit, 0 -> E.K, -1 -> E.J
-__device__ __forceinline__ int kcode(int k, const ElemDev& E) { return k > 0 ? k : (k == 0 ? E.K : E.J); }
-// small-matrix offsets: >= 0 explicit, -1-w -> SmallLayout slot w for this element
-__device__ __forceinline__ long long soff(long long o, const ElemDev& E) {
-  if (o >= 0) return o;
-  const int KP = E.kmax3 + 2;
-  switch (-1 - (int)o) {
-    case 0: return SmallLayout::G(KP);
-    case 1: return SmallLayout::A(KP);
-    case 2: return SmallLayout::U(KP);
-    case 3: return SmallLayout::V(KP);
-    default: return SmallLayout::C(KP);
-  }
-}
-// rows of the blocks a kernel works on: 0 -> N (Q_k grid), 1 -> |E_k|
-__device__ __forceinline__ int nrows_of(const ElemDev& E, int rows_e) {
-  return rows_e ? E.en[0] * E.en[1] * E.en[2] : E.N;
-}
 
 // ---------------------------------------------------------------------------
 // virtual column access: column c of the concatenation of nb blocks of K cols
@@ -46,31 +20,6 @@ template <typename T>
 __device__ __forceinline__ const T* vcol(const ElemDev& E, const ColSet& s, int c, int K) {
   const int b = c / K;
   return reinterpret_cast<const T*>(E.blk[s.blk[b]]) + (size_t)(c - b * K) * E.ld;
-}
-
-// Loads through a global-address-space pointer: the block pointers come from tables
-// in memory, so the compiler cannot infer the address space and would otherwise use
-// flat loads, which also count against the LDS counter and get conservative waits.
-typedef double gd2 __attribute__((ext_vector_type(2)));
-template <typename V>
-__device__ __forceinline__ V gload(const void* p) {
-  return *(const __attribute__((address_space(1))) V*)(p);
-}
-__device__ __forceinline__ double2 gload2(const void* p) {
-  const gd2 v = *(const __attribute__((address_space(1))) gd2*)(p);
-  return double2{v.x, v.y};
-}
-typedef float gf2 __attribute__((ext_vector_type(2)));
-typedef float gf4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float2 gload2f(const void* p) {
-  const gf2 v = *(const __attribute__((address_space(1))) gf2*)(p);
-  return float2{v.x, v.y};
-}
-__device__ __forceinline__ void gstore2f(void* p, float x, float y) {
-  *(__attribute__((address_space(1))) gf2*)(p) = gf2{x, y};
-}
-__device__ __forceinline__ void gstore2(void* p, double x, double y) {
-  *(__attribute__((address_space(1))) gd2*)(p) = gd2{x, y};
 }
 
 // ---------------------------------------------------------------------------
@@ -109,15 +58,6 @@ struct GramArgs {
 constexpr int GP_THREADS = 512;
 constexpr int GP_R = 16;        // grid rows staged per step
 constexpr int GP_MAXCOL = 384;  // staged columns per workgroup (tiles are chosen to fit)
-
-typedef double d4v __attribute__((ext_vector_type(4)));
-typedef float f4v __attribute__((ext_vector_type(4)));
-
-// v_mfma_f64_16x16x4f64 lane layout (checked on the device): lane l supplies
-// A[l%16][l/16] and B[l/16][l%16]; result register q of lane l is D[l/16 + 4q][l%16].
-__device__ __forceinline__ d4v mfma16x16x4(double a, double b, d4v c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
 
 // 16x16 output block number b -> (p, q): row-major over p <= q when sym, else over all
 __host__ __device__ __forceinline__ void gram_block(int b, int bi, int bj, int sym, int& p, int& q) {
@@ -699,707 +639,6 @@ __global__ void __launch_bounds__(256) k_gram_reduce(GramReduceArgs A) {
   double s = 0.0;
   for (int q = 0; q < A.nsplit; ++q) s += p[(size_t)q * A.part_ld * A.part_ld];
   E.small[soff(A.out_off, E) + (size_t)i * ld + j] = s;
-}
-
-// ---------------------------------------------------------------------------
-// block reductions
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
-// sum over the block, result broadcast to every thread (fixed order)
-__device__ double block_sum(double v, double* sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  v = wave_sum(v);
-  __syncthreads();
-  if (lane == 0) sh[w] = v;
-  __syncthreads();
-  double s = 0.0;
-  for (int i = 0; i < nw; ++i) s += sh[i];
-  __syncthreads();
-  return s;
-}
-
-__device__ double block_max(double v, double* sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-  __syncthreads();
-  if (lane == 0) sh[w] = v;
-  __syncthreads();
-  double s = sh[0];
-  for (int i = 1; i < nw; ++i) s = fmax(s, sh[i]);
-  __syncthreads();
-  return s;
-}
-
-// Eigenvalues 0..nwant-1 (ascending) of the symmetric tridiagonal T (diagonal sd,
-// off-diagonal se) by multisection on Sturm counts: a group of 8 lanes owns one
-// eigenvalue and counts at the 8 interior points of its bracket, which shrinks
-// 9-fold per round; the round's bracket is read off the group's ballot. The
-// bracket keeps count(lo) <= j < count(hi) and stops below abstol or a few ulps of
-// its end points. Each lane of a group computes the same bracket, so the group
-// stays converged together. Ends with a barrier.
-__device__ void multisect_eigs(const double* sd, const double* se, int m, int nwant, double lo0, double hi0,
-                               double pivmin, double abstol, double* lam) {
-  const int lane = threadIdx.x & 63;
-  const int t = lane & 7, gsh = lane & 56;
-  const int per_pass = blockDim.x >> 3;
-  for (int j0 = 0; j0 < nwant; j0 += per_pass) {
-    const int j = j0 + (threadIdx.x >> 3);
-    if (j < nwant) {
-      double lo = lo0, hi = hi0;
-      for (int r = 0; r < 80; ++r) {
-        const double w = hi - lo;
-        if (!(w > fmax(abstol, 4.0 * 2.2204460492503131e-16 * fmax(fabs(lo), fabs(hi))))) break;
-        const double step = w * (1.0 / 9.0);
-        const int cnt = sturm_count(sd, se, m, lo + step * (double)(t + 1), pivmin);
-        const unsigned bits = (unsigned)(__ballot(cnt > j) >> gsh) & 0xFFu;
-        if (bits == 0) {
-          lo = lo + step * 8.0;
-        } else {
-          const int f = __ffs(bits) - 1;   // first point whose count exceeds j
-          const double nlo = f > 0 ? lo + step * (double)f : lo;
-          hi = lo + step * (double)(f + 1);
-          lo = nlo;
-        }
-      }
-      if (t == 0) lam[j] = 0.5 * (lo + hi);
-    }
-  }
-  __syncthreads();
-}
-
-// ---------------------------------------------------------------------------
-// Rayleigh-Ritz / symmetric eigen, one workgroup per element (FP64)
-// ---------------------------------------------------------------------------
-struct RRArgs {
-  const ElemDev* elems;
-  const int* active;
-  int nb;              // K3 = nb * E.K (RR_GEN); RR_SVD: K3 = kfix
-  int kfix;            // RR_SVD: matrix order
-  int nkeep;           // columns of C to produce (<= 0: E.K)
-  int mode;
-  int* status;         // per element: 0 ok, 2 breakdown of the X block
-  long long* phase_clk;  // optional: 16 timestamps per element (diagnostics)
-  double* work;          // per element work region (the working matrix above kRRLdsOrder)
-  long long work_stride;
-  double pivot_tol;      // X-column overlap pivots below this (after unit-diagonal scaling) = breakdown
-  double drop_tol;       // W/P columns whose scaled pivot is below this are left out of the basis
-  double* minpiv;        // optional: smallest scaled pivot, its column, dropped count (diagnostics)
-  double ortol;          // eigenvalues closer than ortol * ||T|| are treated as one cluster
-  int lds_dyn;           // dynamic LDS bytes of the launch (LDS variant)
-  int* hp_flag;          // optional, per element: 1 when the smallest scaled pivot is below hp_tol
-                         // (the rotated H P' would carry cancellation error), 0 otherwise and
-                         // for inactive elements
-  double hp_tol;
-};
-
-constexpr int kRRThreads = 512;     // LDS variant (orders up to kRRLdsOrder)
-constexpr int kRRThreadsL2 = 1024;  // L2-resident variant: more loads in flight for its latency-bound sweeps
-constexpr int kTriMax = 272;   // largest projected problem handled (3 x 88 + pad)
-
-// ---------------------------------------------------------------------------
-// Rayleigh-Ritz for the generalised problem (S = [X W P]), one workgroup per
-// element:
-//   scaled overlap -> Cholesky with column dropping -> in-place U^{-1} = Z
-//   -> T = A~ Z, A^ = Z^T T (FP64 MFMA) -> Householder tridiagonal
-//   -> Sturm multisection -> inverse iteration (batches of vectors)
-//   -> in-order Gram-Schmidt and back-transformation -> C = D Z V.
-// The working region W (the matrix, then the inverse-iteration factors, then
-// the eigenvectors and reflectors) is dynamic LDS for orders up to
-// kRRLdsOrder (kLds = true) and the element's slice of the Gram partial-sum
-// area in global memory above that (kLds = false; L2-resident). G keeps Z, Vm
-// the scaled A and then the packed reflectors, Um the eigenvectors of T
-// between phases.
-// ---------------------------------------------------------------------------
-constexpr int kLdsPerCU = 163840;                 // 160 KB of LDS per compute unit
-constexpr int kRRStaticLds = 21504;               // bound on k_rr_lds's static LDS
-constexpr int kRRLdsBytes = kLdsPerCU - kRRStaticLds;
-constexpr int kRRLdsOrder = 132;                  // np * np doubles fit in kRRLdsBytes
-
-__device__ __forceinline__ int refl_off(int kk, int m) { return kk * (m - 1) - kk * (kk - 1) / 2; }
-
-template <bool kLds>
-__global__ void __launch_bounds__(kLds ? kRRThreads : kRRThreadsL2) k_rr_lds(RRArgs A) {
-  const int e = blockIdx.x;
-  const ElemDev& E = A.elems[e];
-  if (A.active && !A.active[e]) {
-    if (A.hp_flag && threadIdx.x == 0) A.hp_flag[e] = 0;
-    return;
-  }
-  const int K = E.K;
-  const bool gen = A.mode == RR_GEN, svd = A.mode == RR_SVD;
-  const int n = gen ? A.nb * K : kcode(A.kfix, E);
-  const int kx = gen ? K : n;             // leading columns that are never left out
-  const int np = n + (n & 1);
-  const int nkeep = kcode(A.nkeep, E);
-  const int KP = E.kmax3 + 2;
-  double* G = E.small + SmallLayout::G(KP);     // in: S^T S (ld n); out: Z (ld np)
-  double* Am = E.small + SmallLayout::A(KP);    // in: S^T H S (ld n); then T; then A^
-  double* Um = E.small + SmallLayout::U(KP);    // staging: Z^T T, then eigenvectors of the tridiagonal
-  double* Vm = E.small + SmallLayout::V(KP);    // scaled A, then packed reflectors
-  double* Cm = E.small + SmallLayout::C(KP);
-  double* vec = E.small + SmallLayout::vec(KP);
-  double* d = vec + VS_D * KP;
-  double* theta = vec + VS_THETA * KP;
-  double* lam_s = vec + VS_FLAGS * KP;
-  extern __shared__ double rr_lds[];
-  double* const L = kLds ? rr_lds : A.work + (size_t)e * A.work_stride;
-  __shared__ double sh[16];
-  __shared__ int brk;
-  __shared__ double sd[kTriMax], se[kTriMax], stau[kTriMax];
-  __shared__ double vs[kTriMax], ps[kTriMax], ws[kTriMax];
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int lane = tid & 63, wv = tid >> 6, nw = nt >> 6;
-  auto stamp = [&](int k) {
-    if (A.phase_clk && tid == 0) A.phase_clk[e * 16 + k] = wall_clock64();
-  };
-  stamp(0);
-  if (tid == 0) brk = 0;
-  __syncthreads();
-  int ndrop = 0;
-  if (svd) {
-    // eigen-decomposition of the Gram matrix itself
-    for (int idx = tid; idx < np * np; idx += nt) {
-      const int i = idx / np, j = idx % np;
-      L[idx] = (i < n && j < n) ? G[(size_t)i * n + j] : 0.0;
-    }
-    __syncthreads();
-  } else {
-  // ---- scaled overlap in LDS, scaled A in Vm
-  for (int i = tid; i < np; i += nt) {
-    const double gii = i < n ? G[(size_t)i * n + i] : 1.0;
-    if (!(gii > 0.0) && i < kx) brk = 1;
-    d[i] = (i < n && gii > 0.0) ? 1.0 / sqrt(gii) : (i < n ? 0.0 : 1.0);
-  }
-  __syncthreads();
-  for (int idx = tid; idx < np * np; idx += nt) {
-    const int i = idx / np, j = idx % np;
-    const bool in = i < n && j < n;
-    const double s2 = d[i] * d[j];
-    L[idx] = in ? G[(size_t)i * n + j] * s2 : (i == j ? 1.0 : 0.0);
-    if (gen) Vm[idx] = in ? 0.5 * (Am[(size_t)i * n + j] + Am[(size_t)j * n + i]) * s2 : 0.0;
-  }
-  __syncthreads();
-  // ---- Cholesky L = U^T U (upper, in place); nearly dependent W/P columns leave the basis.
-  // Rows keep their unscaled values during the elimination (one barrier per
-  // column); the rows are divided by sqrt(pivot) at the end.
-  double pmin = 1.0;
-  int jmin = -1;
-  for (int j = 0; j < n; ++j) {
-    const double piv = L[j * np + j];
-    if (piv < pmin) {
-      pmin = piv;
-      jmin = j;
-    }
-    if (j >= kx && !(piv > A.drop_tol)) {
-      __syncthreads();
-      for (int i = tid; i < n; i += nt) {
-        if (i == j) continue;
-        L[i * np + j] = 0.0;
-        L[j * np + i] = 0.0;
-        Vm[(size_t)i * np + j] = 0.0;
-        Vm[(size_t)j * np + i] = 0.0;
-      }
-      if (tid == 0) {
-        L[j * np + j] = 1.0;
-        Vm[(size_t)j * np + j] = 0.0;
-        d[j] = 0.0;
-        ws[j] = 1.0;
-      }
-      ++ndrop;
-      __syncthreads();
-      continue;
-    }
-    if (!(piv > A.pivot_tol) && tid == 0) brk = 1;
-    const double pinv = 1.0 / fmax(piv, 1e-300);
-    if (tid == 0) ws[j] = sqrt(fmax(piv, 1e-300));
-    for (int i = j + 1 + wv; i < n; i += nw) {
-      const double f = L[j * np + i] * pinv;
-      double* row = L + i * np;
-      const double* rj = L + j * np;
-      for (int k = i + lane; k < n; k += 64) row[k] -= f * rj[k];
-    }
-    __syncthreads();
-  }
-  // divide row j by sqrt(pivot_j): U
-  for (int j = wv; j < n; j += nw) {
-    const double u = ws[j];
-    double* row = L + j * np;
-    for (int k = j + 1 + lane; k < n; k += 64) row[k] = (d[j] == 0.0 && k != j) ? 0.0 : row[k] / u;
-    if (lane == 0) row[j] = u;
-  }
-  __syncthreads();
-  if (A.hp_flag && tid == 0) A.hp_flag[e] = (brk || !(pmin >= A.hp_tol)) ? 1 : 0;
-  if (A.minpiv && tid == 0) {
-    A.minpiv[3 * e] = pmin;
-    A.minpiv[3 * e + 1] = jmin;
-    A.minpiv[3 * e + 2] = ndrop;
-  }
-  if (brk) {
-    // X itself is not positive definite: keep X (C = [I; 0; 0]) and report it
-    for (int idx = tid; idx < n * nkeep; idx += nt) {
-      const int i = idx / nkeep, j = idx % nkeep;
-      Cm[idx] = (i == j) ? 1.0 : 0.0;
-    }
-    if (tid == 0) A.status[e] = 2;
-    return;
-  }
-  if (tid == 0) A.status[e] = 0;
-  stamp(1);
-  if constexpr (kLds) {
-    // ---- Z = U^{-1}: rows are independent, Z[i][j] = -(1/U[j][j]) sum_{k=i}^{j-1} Z[i][k] U[k][j]
-    // left to right. A quad of lanes owns a row (the k sum split four ways, DPP quad
-    // reduction); Z[i][j] is kept transposed in the free strictly lower triangle
-    // (L[j][i]), the reciprocal diagonal in ws, so U stays intact until every row is
-    // done; then Z moves to the upper triangle.
-    for (int i = tid; i < n; i += nt) ws[i] = 1.0 / L[i * np + i];
-    __syncthreads();
-    {
-      const int ql = tid & 3;
-      for (int i = tid >> 2; i < n; i += nt >> 2) {
-        const double zii = ws[i];
-        for (int j = i + 1; j < n; ++j) {
-          double t = 0.0;
-          for (int k = i + ql; k < j; k += 4) t += (k == i ? zii : L[k * np + i]) * L[k * np + j];
-          t += dpp_mov<0xB1>(t);   // quad_perm [1,0,3,2]
-          t += dpp_mov<0x4E>(t);   // quad_perm [2,3,0,1]
-          if (ql == 0) L[j * np + i] = -ws[j] * t;
-        }
-      }
-    }
-    __syncthreads();
-    for (int idx = tid; idx < n * n; idx += nt) {
-      const int i = idx / n, j = idx % n;
-      if (i < j) L[i * np + j] = L[j * np + i];
-      else if (i == j) L[i * np + i] = ws[i];
-    }
-    __syncthreads();
-  } else {
-    // ---- Z = U^{-1} in place, column by column (column j uses the inverted leading block):
-    // Z[i][j] = -(1/U[j][j]) sum_{k=i}^{j-1} Z[i][k] U[k][j]
-    for (int j = 0; j < n; ++j) {
-      for (int k = tid; k < j; k += nt) vs[k] = L[k * np + j];
-      __syncthreads();
-      const double ajj = 1.0 / L[j * np + j];
-      for (int i = wv; i < j; i += nw) {
-        const double* zi = L + i * np;
-        double t = 0.0;
-        for (int k = i + lane; k < j; k += 64) t += zi[k] * vs[k];
-        t = wave_sum_dpp(t);
-        if (lane == 0) ps[i] = -ajj * t;
-      }
-      __syncthreads();
-      for (int i = tid; i < j; i += nt) L[i * np + j] = ps[i];
-      if (tid == 0) L[j * np + j] = ajj;
-    }
-    __syncthreads();
-  }
-  if (!gen) {
-    // Cholesky QR: C = D Z orthonormalises the columns (n x nkeep)
-    for (int idx = tid; idx < n * nkeep; idx += nt) {
-      const int i = idx / nkeep, j = idx % nkeep;
-      Cm[idx] = (i <= j && j < n) ? d[i] * L[i * np + j] : 0.0;
-    }
-    stamp(9);
-    return;
-  }
-  // keep Z for the coefficients
-  for (int idx = tid; idx < np * np; idx += nt) {
-    const int i = idx / np, j = idx % np;
-    G[idx] = (i <= j && j < n) ? L[idx] : 0.0;
-  }
-  stamp(2);
-  // ---- T = A~ Z (Am), then A^ = Z^T T (Um), as 16x16 FP64 MFMA tiles (one wave per tile)
-  {
-    const int nt16 = (n + 15) >> 4;
-    const int kst = (n + 3) >> 2;
-    for (int t = wv; t < nt16 * nt16; t += nw) {
-      const int ti = t / nt16, tj = t % nt16;
-      const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
-      const int kmax = min(kst, (tj * 16 + 16 + 3) >> 2);   // Z[k][j] = 0 for k > j
-      d4v acc = {0.0, 0.0, 0.0, 0.0};
-      for (int ks = 0; ks < kmax; ++ks) {
-        const int k = ks * 4 + (lane >> 4);
-        const double av = (ia < n && k < n) ? Vm[(size_t)ia * np + k] : 0.0;
-        const double bv = (jb < n && k <= jb) ? L[k * np + jb] : 0.0;
-        acc = mfma16x16x4(av, bv, acc);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = ti * 16 + (lane >> 4) + 4 * q;
-        if (i < n && jb < n) Am[(size_t)i * np + jb] = acc[q];
-      }
-    }
-    __syncthreads();
-    for (int t = wv; t < nt16 * nt16; t += nw) {
-      const int ti = t / nt16, tj = t % nt16;
-      const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
-      const int kmax = min(kst, (ti * 16 + 16 + 3) >> 2);   // Z[k][i] = 0 for k > i
-      d4v acc = {0.0, 0.0, 0.0, 0.0};
-      for (int ks = 0; ks < kmax; ++ks) {
-        const int k = ks * 4 + (lane >> 4);
-        const double av = (ia < n && k <= ia) ? L[k * np + ia] : 0.0;
-        const double bv = (jb < n && k < n) ? Am[(size_t)k * np + jb] : 0.0;
-        acc = mfma16x16x4(av, bv, acc);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = ti * 16 + (lane >> 4) + 4 * q;
-        if (i < n && jb < n) Um[(size_t)i * np + jb] = acc[q];
-      }
-    }
-  }
-  __syncthreads();
-  for (int idx = tid; idx < n * n; idx += nt) {
-    const int i = idx / n, j = idx % n;
-    L[(size_t)i * np + j] = 0.5 * (Um[(size_t)i * np + j] + Um[(size_t)j * np + i]);
-  }
-  __syncthreads();
-  if (ndrop > 0) {
-    // left-out columns get an eigenvalue above the whole spectrum (Gershgorin bound)
-    double rmax = 0.0;
-    for (int i = tid; i < n; i += nt) {
-      double sacc = 0.0;
-      for (int k = 0; k < n; ++k) sacc += fabs(L[(size_t)i * np + k]);
-      rmax = fmax(rmax, sacc);
-    }
-    rmax = block_max(rmax, sh);
-    for (int j = tid; j < n; j += nt)
-      if (d[j] == 0.0) L[(size_t)j * np + j] = 2.0 * rmax + 1.0;
-    __syncthreads();
-  }
-  }   // !svd
-  stamp(3);
-  // ---- Householder tridiagonalisation in LDS; reflector kk kept in column kk below the diagonal
-  const int m = n;
-  __shared__ int skip;
-  // the product p = tau A v splits the rows between sets of 256 threads
-  constexpr int kSets = (kLds ? kRRThreads : kRRThreadsL2) / 256;
-  __shared__ double pq[kSets][kTriMax];
-  for (int kk = 0; kk < m - 2; ++kk) {
-    const int mr = m - kk - 1;
-    if (wv == 0) {
-      // reflector from column kk (one wave)
-      double part = 0.0;
-      for (int i = lane; i < mr; i += 64) {
-        const double x = L[(kk + 1 + i) * np + kk];
-        part += x * x;
-      }
-      const double ss = wave_sum_dpp(part);
-      const double x0 = L[(kk + 1) * np + kk];
-      const double alpha = x0 >= 0.0 ? -sqrt(ss) : sqrt(ss);
-      const double vv = ss - x0 * x0 + (x0 - alpha) * (x0 - alpha);
-      const bool zero = !(ss > 0.0);
-      for (int i = lane; i < mr; i += 64) vs[i] = (i == 0) ? x0 - alpha : L[(kk + 1 + i) * np + kk];
-      if (lane == 0) {
-        sd[kk] = L[kk * np + kk];
-        stau[kk] = zero ? 0.0 : 2.0 / vv;
-        se[kk] = zero ? 0.0 : alpha;
-        skip = zero ? 1 : 0;
-      }
-    }
-    __syncthreads();
-    if (skip) continue;
-    const double tau = stau[kk];
-    // p = tau A v; A is symmetric, so row i is read as column i (consecutive threads,
-    // consecutive addresses): two threads per row, each over half of the rows
-    {
-      const int q = tid >> 8, qn = (mr + kSets - 1) / kSets;
-      const int j0 = q * qn, j1 = min(mr, j0 + qn);
-      for (int i = tid & 255; i < mr; i += 256) {
-        const double* col = L + (kk + 1) * np + kk + 1 + i;
-        double acc = 0.0;
-        for (int j = j0; j < j1; ++j) acc += col[j * np] * vs[j];
-        pq[q][i] = acc;
-      }
-    }
-    __syncthreads();
-    if (wv == 0) {
-      double kp = 0.0;
-      for (int i = lane; i < mr; i += 64) {
-        double p = 0.0;
-#pragma unroll
-        for (int q = 0; q < kSets; ++q) p += pq[q][i];
-        p *= tau;
-        ps[i] = p;
-        kp += vs[i] * p;
-      }
-      const double Kc = 0.5 * tau * wave_sum_dpp(kp);
-      for (int i = lane; i < mr; i += 64) ws[i] = ps[i] - Kc * vs[i];
-    }
-    __syncthreads();
-    {
-      // this lane's entries of v and w stay in registers across the rows
-      constexpr int NQ = ((kLds ? kRRLdsOrder : kTriMax) + 63) / 64;
-      double vj[NQ], wj[NQ];
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int j = lane + 64 * q;
-        vj[q] = j < mr ? vs[j] : 0.0;
-        wj[q] = j < mr ? ws[j] : 0.0;
-      }
-      for (int i = wv; i < mr; i += nw) {
-        double* row = L + (kk + 1 + i) * np + kk + 1;
-        const double vi = vs[i], wi = ws[i];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          const int j = lane + 64 * q;
-          if (j < mr) row[j] -= vi * wj[q] + wi * vj[q];
-        }
-        if (lane == 0) L[(kk + 1 + i) * np + kk] = vi;
-      }
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    if (m >= 2) {
-      sd[m - 2] = L[(size_t)(m - 2) * np + m - 2];
-      se[m - 2] = L[(size_t)(m - 1) * np + m - 2];
-      stau[m - 2] = 0.0;
-    }
-    sd[m - 1] = L[(size_t)(m - 1) * np + m - 1];
-    se[m - 1] = 0.0;
-  }
-  // reflectors to Vm, packed by column (rows kk+1 .. m-1 of column kk)
-  for (int kk = wv; kk < m - 2; kk += nw) {
-    double* dst = Vm + refl_off(kk, m);
-    for (int i = lane; i < m - 1 - kk; i += 64) dst[i] = L[(size_t)(kk + 1 + i) * np + kk];
-  }
-  __syncthreads();
-  stamp(4);
-  // ---- eigenvalues by bisection on Sturm counts (thread j -> j-th smallest)
-  __shared__ double sb_lo, sb_hi, sb_norm;
-  if (tid == 0) {
-    double lo = 1e300, hi = -1e300, nrm = 0.0;
-    for (int i = 0; i < m; ++i) {
-      const double r = (i > 0 ? fabs(se[i - 1]) : 0.0) + (i < m - 1 ? fabs(se[i]) : 0.0);
-      lo = fmin(lo, sd[i] - r);
-      hi = fmax(hi, sd[i] + r);
-      nrm = fmax(nrm, fabs(sd[i]) + r);
-    }
-    sb_norm = fmax(nrm, 1e-300);
-    sb_lo = lo - 1e-12 * sb_norm - 1e-300;
-    sb_hi = hi + 1e-12 * sb_norm + 1e-300;
-  }
-  __syncthreads();
-  const double onenorm = sb_norm;
-  const double pivmin = 1e-300 + 1e-30 * onenorm * onenorm;
-  const int nwant = svd ? m : min(nkeep, m);
-  multisect_eigs(sd, se, m, nwant, sb_lo, sb_hi, pivmin, 2.0 * 2.2204460492503131e-16 * onenorm, lam_s);
-  stamp(5);
-  // ---- eigenvectors of T by inverse iteration, factors in LDS, R vectors per batch;
-  // eigenvalues closer than ortol ||T|| form a cluster whose vectors are computed in
-  // order, each re-orthogonalised against the earlier ones (read back from Um)
-  __shared__ int cst[kTriMax];
-  __shared__ double shf[kTriMax];
-  __shared__ int maxrank;
-  if (tid == 0) {
-    const double ortol = A.ortol * onenorm, pertol = 10.0 * 2.2e-16 * onenorm;
-    int mr = 0;
-    for (int j = 0; j < nwant; ++j) {
-      cst[j] = (j > 0 && lam_s[j] - lam_s[j - 1] <= ortol) ? cst[j - 1] : j;
-      shf[j] = lam_s[j];
-      if (j > 0 && cst[j] != j && shf[j] < shf[j - 1] + pertol) shf[j] = shf[j - 1] + pertol;
-      mr = max(mr, j - cst[j]);
-    }
-    maxrank = mr;
-  }
-  __syncthreads();
-  double* Zv = Um;   // eigenvector j of T at Zv[j * np + i]
-  // R vectors per batch, each with five FP64 arrays and a byte array of length np
-  const long long wbytes = kLds ? (long long)A.lds_dyn : A.work_stride * (long long)sizeof(double);
-  const int R = (int)min((long long)nt, wbytes / (np * (5 * (int)sizeof(double) + 1)));
-  // vector of this thread: spread over the waves (latency hiding); its storage
-  // column: consecutive lanes adjacent when the whole block has a slot
-  const int slot = (lane < (R + nw - 1) / nw) ? lane * nw + wv : R;
-  const int col = R == nt ? wv * 64 + lane : slot;
-  for (int cb = 0; cb < nwant; cb += R) {
-    for (int rnd = 0; rnd <= maxrank; ++rnd) {
-      const int j = cb + slot;
-      if (slot < R && j < nwant && j - cst[j] == rnd) {
-        StridedD ta{L + 0 * (size_t)np * R + col, R};
-        StridedD tb{L + 1 * (size_t)np * R + col, R};
-        StridedD tu{L + 2 * (size_t)np * R + col, R};
-        StridedD tl{L + 3 * (size_t)np * R + col, R};
-        StridedD z{L + 4 * (size_t)np * R + col, R};
-        StridedB pv{reinterpret_cast<unsigned char*>(L + 5 * (size_t)np * R) + col, R};
-        tri_lu(sd, se, m, shf[j], 2.2e-16 * onenorm, ta, tb, tu, tl, pv);
-        for (int i = 0; i < m; ++i) z[i] = hash_unit(j, i);
-        // an isolated eigenvalue needs no re-orthogonalisation: two solves (growth
-        // at most ~1/(eps ||T||) each, far from overflow), one normalisation
-        const bool single = cst[j] == j && (j + 1 >= nwant || cst[j + 1] == j + 1);
-        const int n_it = single ? 2 : 4;
-        for (int it = 0; it < n_it; ++it) {
-          tri_solve(m, ta, tb, tu, tl, pv, z);
-          if (single && it + 1 < n_it) continue;
-          for (int q = cst[j]; q < j; ++q) {
-            const double* zq = Zv + (size_t)q * np;
-            double dot = 0.0;
-            for (int i = 0; i < m; ++i) dot += zq[i] * z[i];
-            for (int i = 0; i < m; ++i) z[i] -= dot * zq[i];
-          }
-          double nn = 0.0;
-          for (int i = 0; i < m; ++i) nn += z[i] * z[i];
-          nn = 1.0 / sqrt(nn);
-          for (int i = 0; i < m; ++i) z[i] *= nn;
-        }
-        for (int i = 0; i < np; ++i) Zv[(size_t)j * np + i] = (i < m) ? z[i] : 0.0;
-      }
-      __syncthreads();
-    }
-  }
-  stamp(6);
-  // ---- eigenvectors and reflectors into LDS: in-order Gram-Schmidt, back-transformation
-  double* zl = L;                                  // nwant x np
-  double* rl = L + (size_t)nwant * np;             // packed reflectors
-  const int nrefl = m >= 2 ? refl_off(m - 2, m) : 0;
-  for (int idx = tid; idx < nwant * np; idx += nt) zl[idx] = Zv[idx];
-  for (int idx = tid; idx < nrefl; idx += nt) rl[idx] = Vm[idx];
-  __syncthreads();
-  for (int j = 1; j < nwant; ++j) {
-    double* zj = zl + j * np;
-    for (int q = wv; q < j; q += nw) {
-      const double* zq = zl + q * np;
-      double dot = 0.0;
-      for (int i = lane; i < m; i += 64) dot += zq[i] * zj[i];
-      dot = wave_sum_dpp(dot);
-      if (lane == 0) ps[q] = dot;
-    }
-    __syncthreads();
-    // z_j -= sum_q (z_q . z_j) z_q: a quad of lanes per row, the q sum split four ways;
-    // per-wave sums of squares for the norm
-    {
-      const int ql = tid & 3;
-      double part = 0.0;
-      for (int i = tid >> 2; i < m; i += nt >> 2) {
-        double t = 0.0;
-        for (int q = ql; q < j; q += 4) t += ps[q] * zl[q * np + i];
-        t += dpp_mov<0xB1>(t);   // quad_perm [1,0,3,2]
-        t += dpp_mov<0x4E>(t);   // quad_perm [2,3,0,1]
-        if (ql == 0) {
-          const double v = zj[i] - t;
-          zj[i] = v;
-          part += v * v;
-        }
-      }
-      part = wave_sum_dpp(part);
-      if (lane == 0) sh[wv] = part;
-    }
-    __syncthreads();
-    {
-      double nn2 = 0.0;
-      for (int q = 0; q < nw; ++q) nn2 += sh[q];
-      const double nn = 1.0 / sqrt(nn2);
-      for (int i = tid; i < m; i += nt) zj[i] *= nn;
-    }
-    __syncthreads();
-  }
-  stamp(7);
-  if constexpr (kLds) {
-    // back-transform: z <- H_0 ... H_{m-3} z with eight lanes per vector (the dot
-    // product reduced within the lane group) and every vector at once: the reflectors
-    // are read-only, so the vectors need no barriers between reflectors
-    {
-      const int l8 = tid & 7;
-      for (int j = tid >> 3; j < nwant; j += nt >> 3) {
-        double* z = zl + (size_t)j * np;
-        for (int kk = m - 3; kk >= 0; --kk) {
-          const double tau = stau[kk];
-          if (tau == 0.0) continue;
-          const double* v = rl + refl_off(kk, m);   // rows kk+1 .. m-1
-          const int len = m - 1 - kk;
-          double dot = 0.0;
-          for (int i = l8; i < len; i += 8) dot += v[i] * z[kk + 1 + i];
-          dot = group8_sum(dot) * tau;
-          for (int i = l8; i < len; i += 8) z[kk + 1 + i] -= dot * v[i];
-        }
-      }
-    }
-  } else {
-    // back-transform: z <- H_0 ... H_{m-3} z (lanes over rows); a wave carries four of
-    // its vectors through the reflectors together, so that their dot products and
-    // reductions overlap
-    {
-      constexpr int BV = 4;
-      for (int j0 = wv; j0 < nwant; j0 += BV * nw) {
-        double* z[BV];
-        bool on[BV];
-#pragma unroll
-        for (int b = 0; b < BV; ++b) {
-          const int j = j0 + b * nw;
-          on[b] = j < nwant;
-          z[b] = zl + (size_t)(on[b] ? j : j0) * np;
-        }
-        for (int kk = m - 3; kk >= 0; --kk) {
-          const double tau = stau[kk];
-          if (tau == 0.0) continue;
-          const double* v = rl + refl_off(kk, m);   // rows kk+1 .. m-1
-          double dot[BV];
-#pragma unroll
-          for (int b = 0; b < BV; ++b) dot[b] = 0.0;
-          for (int i = lane; i < m - 1 - kk; i += 64) {
-            const double vi = v[i];
-#pragma unroll
-            for (int b = 0; b < BV; ++b) dot[b] += vi * z[b][kk + 1 + i];
-          }
-#pragma unroll
-          for (int b = 0; b < BV; ++b) dot[b] = wave_sum_dpp(dot[b]) * tau;
-          for (int i = lane; i < m - 1 - kk; i += 64) {
-            const double vi = v[i];
-#pragma unroll
-            for (int b = 0; b < BV; ++b)
-              if (on[b]) z[b][kk + 1 + i] -= dot[b] * vi;
-          }
-        }
-      }
-    }
-  }
-  __syncthreads();
-  stamp(8);
-  if (svd) {
-    // C = V[:, sel] / sigma with sigma = sqrt(eigenvalue), descending
-    for (int idx = tid; idx < n * nkeep; idx += nt) {
-      const int i = idx / nkeep, j = idx % nkeep;
-      const int col = m - 1 - j;
-      const double sg = (col >= 0) ? sqrt(fmax(lam_s[col], 0.0)) : 0.0;
-      Cm[idx] = (col >= 0 && sg > 0.0) ? zl[col * np + i] / sg : 0.0;
-    }
-    for (int j = tid; j < nkeep; j += nt) theta[j] = (m - 1 - j >= 0) ? sqrt(fmax(lam_s[m - 1 - j], 0.0)) : 0.0;
-    __syncthreads();
-    stamp(9);
-    return;
-  }
-  // ---- C = D Z V[:, :nkeep] (n x nkeep, ld nkeep) as 16x16 FP64 MFMA tiles (one wave
-  // per tile; Z[i][k] = 0 for k < i, so a tile's k range starts at its first row);
-  // left-out rows are zero (d = 0)
-  {
-    const int nti = (n + 15) >> 4, ntj = (nkeep + 15) >> 4;
-    const int kst = (n + 3) >> 2;
-    for (int tile = wv; tile < nti * ntj; tile += nw) {
-      const int ti = tile / ntj, tj = tile % ntj;
-      const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
-      d4v acc = {0.0, 0.0, 0.0, 0.0};
-      for (int ks = ti * 4; ks < kst; ++ks) {
-        const int k = ks * 4 + (lane >> 4);
-        const double av = (ia < n && k < n && k >= ia) ? G[(size_t)ia * np + k] : 0.0;
-        const double bv = (jb < nwant && k < n) ? zl[(size_t)jb * np + k] : 0.0;
-        acc = mfma16x16x4(av, bv, acc);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = ti * 16 + (lane >> 4) + 4 * q;
-        if (i < n && jb < nkeep) Cm[(size_t)i * nkeep + jb] = jb < nwant ? d[i] * acc[q] : 0.0;
-      }
-    }
-  }
-  for (int j = tid; j < nkeep; j += nt) theta[j] = j < nwant ? lam_s[j] : 0.0;
-  __syncthreads();
-  stamp(9);
 }
 
 // ---------------------------------------------------------------------------
@@ -2344,7 +1583,6 @@ void init_kernel_attributes() {
     gram_attrs<6>();
     gram_attrs<8>();
     gram_attrs<12>();
-    set_lds_limit((const void*)k_rr_lds<true>, kRRLdsBytes);
     return true;
   }();
   (void)done;
@@ -2555,50 +1793,6 @@ int launch_gram_rows(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T,
 int launch_gram_pair(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T, int kT, long long out_off_st,
                      long long out_off_ss, const int* active) {
   return gram_impl(c, prec, S, kS, T, kT, out_off_st, active, 0, 1, true, out_off_ss);
-}
-
-int launch_rr(Ctx& c, int nb, int kfix, int nkeep, int mode, const int* active) {
-  // algorithmic flop estimate: Cholesky + inverse (n^3/3 each), two n^3 products,
-  // tridiagonalisation (4n^3/3), back-transformation and coefficients (4 n^2 k)
-  double flops = 0.0;
-  int npmax = 0;
-  size_t need = 0;   // bytes of the working region: matrix, then eigenvectors + reflectors
-  for (int e = 0; e < c.n_elem; ++e) {
-    const int n = mode == RR_GEN ? nb * c.K[e] : (kfix > 0 ? kfix : (kfix == 0 ? c.K[e] : c.J[e]));
-    const int npe = n + (n & 1);
-    const int nk = nkeep > 0 ? nkeep : (nkeep == 0 ? c.K[e] : c.J[e]);
-    const int nw = mode == RR_SVD ? n : std::min(nk, n);
-    npmax = std::max(npmax, npe);
-    need = std::max({need, (size_t)(nw * npe + n * (n - 1) / 2) * sizeof(double),
-                     (size_t)npe * npe * sizeof(double), (size_t)npe * 41});
-    if (active && !c.active_host.empty() && !c.active_host[e]) continue;
-    flops += (mode == RR_GEN ? 2.0 / 3.0 + 2.0 : 0.0) * (double)n * n * n + 4.0 / 3.0 * (double)n * n * n +
-             4.0 * (double)n * n * nk;
-  }
-  if (npmax > kTriMax) {
-    set_error("projected problem of order " + std::to_string(npmax) + " above the limit " +
-              std::to_string(kTriMax));
-    return DG_ERR_SHAPE;
-  }
-  // the working region lives in LDS when the orders allow it, else in the element's
-  // slice of the Gram partial-sum area (free between the Gram reduction and the rotation)
-  const bool in_lds = npmax <= kRRLdsOrder && need <= (size_t)kRRLdsBytes;
-  if (!in_lds && need > (size_t)c.gram_part_stride * sizeof(double)) {
-    set_error("Rayleigh-Ritz work region of " + std::to_string(need) + " bytes above the partial-sum slice");
-    return DG_ERR_SHAPE;
-  }
-  RRArgs a{c.elems_dev, active, nb, kfix, nkeep, mode, c.dev_status,
-           c.log_level >= 2 ? c.dev_phase : nullptr, c.gram_part, c.gram_part_stride,
-           c.rr_pivot_tol, c.rr_drop_tol, c.log_level >= 3 ? c.dev_minpiv : nullptr, c.rr_ortol,
-           in_lds ? (int)need : 0, mode == RR_GEN ? c.dev_hpflag : nullptr, c.hp_tol};
-  TimedScope ts(c, TC_RR, flops);
-  if (in_lds) {
-    hipLaunchKernelGGL(k_rr_lds<true>, dim3(c.n_elem), dim3(kRRThreads), need, c.stream, a);
-  } else {
-    hipLaunchKernelGGL(k_rr_lds<false>, dim3(c.n_elem), dim3(kRRThreadsL2), 0, c.stream, a);
-  }
-  DG_HIP(hipGetLastError());
-  return DG_OK;
 }
 
 int launch_rotate(Ctx& c, int prec, const RotArgs& a_in) {

@@ -1,0 +1,996 @@
+// Rayleigh-Ritz on the small projected problem (FP64): the generalised eigenproblem of
+// (S^T H S, S^T S) for S = [X W P] (Eq. (4); Algorithm 1 step 5, Algorithm 2 step 4), and
+// the eigen-decomposition and Cholesky-QR passes of the ALB orthonormalisation.
+//
+//   scaled overlap -> Cholesky with column dropping -> U^{-1} = Z -> A^ = Z^T A~ Z
+//   -> Householder tridiagonal T                       (k_rr_head, one workgroup per element)
+//   -> eigenvalues of T by multisection                (k_rr_eig, a workgroup per eigenvalue)
+//   -> eigenvectors of T by inverse iteration          (k_rr_inv, a lane per vector)
+//   -> in-order Gram-Schmidt                           (k_rr_mgs, one workgroup per element)
+//   -> back-transformation                             (k_rr_back, a wave or eight lanes per vector)
+//   -> coefficients C = D Z V                          (k_rr_coef, a wave per 16x16 tile)
+//
+// The steps are separate launches so that each takes the split that suits it: a launch
+// has one to a few dozen elements, and one workgroup per element for all of it leaves
+// most of the 256 compute units idle behind serial sweeps.
+#include "dense_ops.h"
+#include "tridiag.h"
+
+#include <algorithm>
+#include <cstdio>
+
+namespace dg {
+
+struct RRArgs {
+  const ElemDev* elems;
+  const int* active;
+  int nb;              // K3 = nb * E.K (RR_GEN); RR_SVD: K3 = kfix
+  int kfix;            // RR_SVD: matrix order
+  int nkeep;           // columns of C to produce (<= 0: E.K)
+  int mode;
+  int* status;         // per element: 0 ok, 2 breakdown of the X block
+  long long* phase_clk;  // optional: 16 timestamps per element (diagnostics)
+  double* work;          // per element work region (the working matrix above kRRLdsOrder)
+  long long work_stride;
+  double pivot_tol;      // X-column overlap pivots below this (after unit-diagonal scaling) = breakdown
+  double drop_tol;       // W/P columns whose scaled pivot is below this are left out of the basis
+  double* minpiv;        // optional: smallest scaled pivot, its column, dropped count (diagnostics)
+  double ortol;          // eigenvalues closer than ortol * ||T|| are treated as one cluster
+  int lds_dyn;           // dynamic LDS bytes of the launch (LDS variant)
+  int* hp_flag;          // optional, per element: 1 when the smallest scaled pivot is below hp_tol
+                         // (the rotated H P' would carry cancellation error), 0 otherwise and
+                         // for inactive elements
+  double hp_tol;
+};
+
+
+constexpr int kRRThreads = 512;     // LDS variant (orders up to kRRLdsOrder)
+constexpr int kRRThreadsL2 = 1024;  // L2-resident variant: more loads in flight for its latency-bound sweeps
+constexpr int kTriMax = 272;   // largest projected problem handled (3 x 88 + pad)
+constexpr int kOrthMax = 88;   // most eigenvectors (J + guards)
+
+constexpr int kLdsPerCU = 163840;                 // 160 KB of LDS per compute unit
+constexpr int kRRStaticLds = 21504;               // bound on k_rr_head's static LDS
+constexpr int kRRLdsBytes = kLdsPerCU - kRRStaticLds;
+constexpr int kRRLdsOrder = 132;                  // np * np doubles fit in kRRLdsBytes
+
+// where the steps leave their matrices (leading dimension np); the inputs are S^T S in
+// slot G and S^T H S in slot A (leading dimension n), the result C is in slot C
+enum RRSlot { kSlotZ, kSlotRefl, kSlotVec };
+__device__ __forceinline__ long long rr_slot(RRSlot w, int KP) {
+  switch (w) {
+    case kSlotZ: return SmallLayout::G(KP);
+    case kSlotRefl: return SmallLayout::A(KP);
+    default: return SmallLayout::U(KP);
+  }
+}
+
+struct RRShape {
+  int n, np;      // order, and rounded up to even (leading dimension)
+  int kx;         // leading columns that are never left out
+  int nkeep;      // columns of C
+  int nwant;      // eigenpairs computed
+  int KP;
+  bool gen, svd;
+};
+
+__device__ __forceinline__ RRShape rr_shape(const RRArgs& A, const ElemDev& E) {
+  RRShape s;
+  s.gen = A.mode == RR_GEN;
+  s.svd = A.mode == RR_SVD;
+  s.n = s.gen ? A.nb * E.K : kcode(A.kfix, E);
+  s.np = s.n + (s.n & 1);
+  s.kx = s.gen ? E.K : s.n;
+  s.nkeep = kcode(A.nkeep, E);
+  s.nwant = s.svd ? s.n : min(s.nkeep, s.n);
+  s.KP = E.kmax3 + 2;
+  return s;
+}
+
+// element e takes part: active, and its overlap factorisation did not break down
+__device__ __forceinline__ bool rr_on(const RRArgs& A, int e) {
+  if (A.active && !A.active[e]) return false;
+  return A.mode == RR_SVD || A.status[e] != 2;
+}
+
+__device__ __forceinline__ void rr_stamp(const RRArgs& A, int e, int k, int block) {
+  if (A.phase_clk && block == 0 && threadIdx.x == 0) A.phase_clk[e * 16 + k] = wall_clock64();
+}
+
+// ---------------------------------------------------------------------------
+// overlap factorisation, standard form and Householder tridiagonalisation, one workgroup
+// per element.  The working matrix is dynamic LDS for orders up to kRRLdsOrder (kLds =
+// true) and the element's slice of the Gram partial-sum area above that (L2-resident).
+// G keeps Z, Vm the scaled A.
+// ---------------------------------------------------------------------------
+template <bool kLds>
+__global__ void __launch_bounds__(kLds ? kRRThreads : kRRThreadsL2) k_rr_head(RRArgs A) {
+  const int e = blockIdx.x;
+  const ElemDev& E = A.elems[e];
+  if (A.active && !A.active[e]) {
+    if (A.hp_flag && threadIdx.x == 0) A.hp_flag[e] = 0;
+    return;
+  }
+  const int K = E.K;
+  const bool gen = A.mode == RR_GEN, svd = A.mode == RR_SVD;
+  const int n = gen ? A.nb * K : kcode(A.kfix, E);
+  const int kx = gen ? K : n;             // leading columns that are never left out
+  const int np = n + (n & 1);
+  const int nkeep = kcode(A.nkeep, E);
+  const int KP = E.kmax3 + 2;
+  double* G = E.small + SmallLayout::G(KP);     // in: S^T S (ld n); out: Z (ld np)
+  double* Am = E.small + SmallLayout::A(KP);    // in: S^T H S (ld n); then T; then A^
+  double* Um = E.small + SmallLayout::U(KP);    // staging: Z^T T, then eigenvectors of the tridiagonal
+  double* Vm = E.small + SmallLayout::V(KP);    // scaled A, then packed reflectors
+  double* Cm = E.small + SmallLayout::C(KP);
+  double* vec = E.small + SmallLayout::vec(KP);
+  double* d = vec + VS_D * KP;
+  extern __shared__ double rr_lds[];
+  double* const L = kLds ? rr_lds : A.work + (size_t)e * A.work_stride;
+  __shared__ double sh[16];
+  __shared__ int brk;
+  __shared__ double sd[kTriMax], se[kTriMax], stau[kTriMax];
+  __shared__ double vs[kTriMax], ps[kTriMax], ws[kTriMax];
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int lane = tid & 63, wv = tid >> 6, nw = nt >> 6;
+  auto stamp = [&](int k) {
+    if (A.phase_clk && tid == 0) A.phase_clk[e * 16 + k] = wall_clock64();
+  };
+  stamp(0);
+  if (tid == 0) brk = 0;
+  __syncthreads();
+  int ndrop = 0;
+  if (svd) {
+    // eigen-decomposition of the Gram matrix itself
+    for (int idx = tid; idx < np * np; idx += nt) {
+      const int i = idx / np, j = idx % np;
+      L[idx] = (i < n && j < n) ? G[(size_t)i * n + j] : 0.0;
+    }
+    __syncthreads();
+  } else {
+  // ---- scaled overlap in LDS, scaled A in Vm
+  for (int i = tid; i < np; i += nt) {
+    const double gii = i < n ? G[(size_t)i * n + i] : 1.0;
+    if (!(gii > 0.0) && i < kx) brk = 1;
+    d[i] = (i < n && gii > 0.0) ? 1.0 / sqrt(gii) : (i < n ? 0.0 : 1.0);
+  }
+  __syncthreads();
+  for (int idx = tid; idx < np * np; idx += nt) {
+    const int i = idx / np, j = idx % np;
+    const bool in = i < n && j < n;
+    const double s2 = d[i] * d[j];
+    L[idx] = in ? G[(size_t)i * n + j] * s2 : (i == j ? 1.0 : 0.0);
+    if (gen) Vm[idx] = in ? 0.5 * (Am[(size_t)i * n + j] + Am[(size_t)j * n + i]) * s2 : 0.0;
+  }
+  __syncthreads();
+  // ---- Cholesky L = U^T U (upper, in place); nearly dependent W/P columns leave the basis.
+  // Rows keep their unscaled values during the elimination (one barrier per
+  // column); the rows are divided by sqrt(pivot) at the end.
+  double pmin = 1.0;
+  int jmin = -1;
+  for (int j = 0; j < n; ++j) {
+    const double piv = L[j * np + j];
+    if (piv < pmin) {
+      pmin = piv;
+      jmin = j;
+    }
+    if (j >= kx && !(piv > A.drop_tol)) {
+      __syncthreads();
+      for (int i = tid; i < n; i += nt) {
+        if (i == j) continue;
+        L[i * np + j] = 0.0;
+        L[j * np + i] = 0.0;
+        Vm[(size_t)i * np + j] = 0.0;
+        Vm[(size_t)j * np + i] = 0.0;
+      }
+      if (tid == 0) {
+        L[j * np + j] = 1.0;
+        Vm[(size_t)j * np + j] = 0.0;
+        d[j] = 0.0;
+        ws[j] = 1.0;
+      }
+      ++ndrop;
+      __syncthreads();
+      continue;
+    }
+    if (!(piv > A.pivot_tol) && tid == 0) brk = 1;
+    const double pinv = 1.0 / fmax(piv, 1e-300);
+    if (tid == 0) ws[j] = sqrt(fmax(piv, 1e-300));
+    for (int i = j + 1 + wv; i < n; i += nw) {
+      const double f = L[j * np + i] * pinv;
+      double* row = L + i * np;
+      const double* rj = L + j * np;
+      for (int k = i + lane; k < n; k += 64) row[k] -= f * rj[k];
+    }
+    __syncthreads();
+  }
+  // divide row j by sqrt(pivot_j): U
+  for (int j = wv; j < n; j += nw) {
+    const double u = ws[j];
+    double* row = L + j * np;
+    for (int k = j + 1 + lane; k < n; k += 64) row[k] = (d[j] == 0.0 && k != j) ? 0.0 : row[k] / u;
+    if (lane == 0) row[j] = u;
+  }
+  __syncthreads();
+  if (A.hp_flag && tid == 0) A.hp_flag[e] = (brk || !(pmin >= A.hp_tol)) ? 1 : 0;
+  if (A.minpiv && tid == 0) {
+    A.minpiv[3 * e] = pmin;
+    A.minpiv[3 * e + 1] = jmin;
+    A.minpiv[3 * e + 2] = ndrop;
+  }
+  if (brk) {
+    // X itself is not positive definite: keep X (C = [I; 0; 0]) and report it
+    for (int idx = tid; idx < n * nkeep; idx += nt) {
+      const int i = idx / nkeep, j = idx % nkeep;
+      Cm[idx] = (i == j) ? 1.0 : 0.0;
+    }
+    if (tid == 0) A.status[e] = 2;
+    return;
+  }
+  if (tid == 0) A.status[e] = 0;
+  stamp(1);
+  if constexpr (kLds) {
+    // ---- Z = U^{-1}: rows are independent, Z[i][j] = -(1/U[j][j]) sum_{k=i}^{j-1} Z[i][k] U[k][j]
+    // left to right. A quad of lanes owns a row (the k sum split four ways, DPP quad
+    // reduction); Z[i][j] is kept transposed in the free strictly lower triangle
+    // (L[j][i]), the reciprocal diagonal in ws, so U stays intact until every row is
+    // done; then Z moves to the upper triangle.
+    for (int i = tid; i < n; i += nt) ws[i] = 1.0 / L[i * np + i];
+    __syncthreads();
+    {
+      const int ql = tid & 3;
+      for (int i = tid >> 2; i < n; i += nt >> 2) {
+        const double zii = ws[i];
+        for (int j = i + 1; j < n; ++j) {
+          double t = 0.0;
+          for (int k = i + ql; k < j; k += 4) t += (k == i ? zii : L[k * np + i]) * L[k * np + j];
+          t += dpp_mov<0xB1>(t);   // quad_perm [1,0,3,2]
+          t += dpp_mov<0x4E>(t);   // quad_perm [2,3,0,1]
+          if (ql == 0) L[j * np + i] = -ws[j] * t;
+        }
+      }
+    }
+    __syncthreads();
+    for (int idx = tid; idx < n * n; idx += nt) {
+      const int i = idx / n, j = idx % n;
+      if (i < j) L[i * np + j] = L[j * np + i];
+      else if (i == j) L[i * np + i] = ws[i];
+    }
+    __syncthreads();
+  } else {
+    // ---- Z = U^{-1} in place, column by column (column j uses the inverted leading block):
+    // Z[i][j] = -(1/U[j][j]) sum_{k=i}^{j-1} Z[i][k] U[k][j]
+    for (int j = 0; j < n; ++j) {
+      for (int k = tid; k < j; k += nt) vs[k] = L[k * np + j];
+      __syncthreads();
+      const double ajj = 1.0 / L[j * np + j];
+      for (int i = wv; i < j; i += nw) {
+        const double* zi = L + i * np;
+        double t = 0.0;
+        for (int k = i + lane; k < j; k += 64) t += zi[k] * vs[k];
+        t = wave_sum_dpp(t);
+        if (lane == 0) ps[i] = -ajj * t;
+      }
+      __syncthreads();
+      for (int i = tid; i < j; i += nt) L[i * np + j] = ps[i];
+      if (tid == 0) L[j * np + j] = ajj;
+    }
+    __syncthreads();
+  }
+  if (!gen) {
+    // Cholesky QR: C = D Z orthonormalises the columns (n x nkeep)
+    for (int idx = tid; idx < n * nkeep; idx += nt) {
+      const int i = idx / nkeep, j = idx % nkeep;
+      Cm[idx] = (i <= j && j < n) ? d[i] * L[i * np + j] : 0.0;
+    }
+    stamp(4);
+    return;
+  }
+  // keep Z for the coefficients
+  for (int idx = tid; idx < np * np; idx += nt) {
+    const int i = idx / np, j = idx % np;
+    G[idx] = (i <= j && j < n) ? L[idx] : 0.0;
+  }
+  stamp(2);
+  // ---- T = A~ Z (Am), then A^ = Z^T T (Um), as 16x16 FP64 MFMA tiles (one wave per tile)
+  {
+    const int nt16 = (n + 15) >> 4;
+    const int kst = (n + 3) >> 2;
+    for (int t = wv; t < nt16 * nt16; t += nw) {
+      const int ti = t / nt16, tj = t % nt16;
+      const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
+      const int kmax = min(kst, (tj * 16 + 16 + 3) >> 2);   // Z[k][j] = 0 for k > j
+      d4v acc = {0.0, 0.0, 0.0, 0.0};
+      for (int ks = 0; ks < kmax; ++ks) {
+        const int k = ks * 4 + (lane >> 4);
+        const double av = (ia < n && k < n) ? Vm[(size_t)ia * np + k] : 0.0;
+        const double bv = (jb < n && k <= jb) ? L[k * np + jb] : 0.0;
+        acc = mfma16x16x4(av, bv, acc);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = ti * 16 + (lane >> 4) + 4 * q;
+        if (i < n && jb < n) Am[(size_t)i * np + jb] = acc[q];
+      }
+    }
+    __syncthreads();
+    for (int t = wv; t < nt16 * nt16; t += nw) {
+      const int ti = t / nt16, tj = t % nt16;
+      const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
+      const int kmax = min(kst, (ti * 16 + 16 + 3) >> 2);   // Z[k][i] = 0 for k > i
+      d4v acc = {0.0, 0.0, 0.0, 0.0};
+      for (int ks = 0; ks < kmax; ++ks) {
+        const int k = ks * 4 + (lane >> 4);
+        const double av = (ia < n && k <= ia) ? L[k * np + ia] : 0.0;
+        const double bv = (jb < n && k < n) ? Am[(size_t)k * np + jb] : 0.0;
+        acc = mfma16x16x4(av, bv, acc);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = ti * 16 + (lane >> 4) + 4 * q;
+        if (i < n && jb < n) Um[(size_t)i * np + jb] = acc[q];
+      }
+    }
+  }
+  __syncthreads();
+  for (int idx = tid; idx < n * n; idx += nt) {
+    const int i = idx / n, j = idx % n;
+    L[(size_t)i * np + j] = 0.5 * (Um[(size_t)i * np + j] + Um[(size_t)j * np + i]);
+  }
+  __syncthreads();
+  if (ndrop > 0) {
+    // left-out columns get an eigenvalue above the whole spectrum (Gershgorin bound)
+    double rmax = 0.0;
+    for (int i = tid; i < n; i += nt) {
+      double sacc = 0.0;
+      for (int k = 0; k < n; ++k) sacc += fabs(L[(size_t)i * np + k]);
+      rmax = fmax(rmax, sacc);
+    }
+    rmax = block_max(rmax, sh);
+    for (int j = tid; j < n; j += nt)
+      if (d[j] == 0.0) L[(size_t)j * np + j] = 2.0 * rmax + 1.0;
+    __syncthreads();
+  }
+  }   // !svd
+  stamp(3);
+  // ---- Householder tridiagonalisation in LDS; reflector kk kept in column kk below the diagonal
+  const int m = n;
+  __shared__ int skip;
+  // the product p = tau A v splits the rows between sets of 256 threads
+  constexpr int kSets = (kLds ? kRRThreads : kRRThreadsL2) / 256;
+  __shared__ double pq[kSets][kTriMax];
+  for (int kk = 0; kk < m - 2; ++kk) {
+    const int mr = m - kk - 1;
+    if (wv == 0) {
+      // reflector from column kk (one wave)
+      double part = 0.0;
+      for (int i = lane; i < mr; i += 64) {
+        const double x = L[(kk + 1 + i) * np + kk];
+        part += x * x;
+      }
+      const double ss = wave_sum_dpp(part);
+      const double x0 = L[(kk + 1) * np + kk];
+      const double alpha = x0 >= 0.0 ? -sqrt(ss) : sqrt(ss);
+      const double vv = ss - x0 * x0 + (x0 - alpha) * (x0 - alpha);
+      const bool zero = !(ss > 0.0);
+      for (int i = lane; i < mr; i += 64) vs[i] = (i == 0) ? x0 - alpha : L[(kk + 1 + i) * np + kk];
+      if (lane == 0) {
+        sd[kk] = L[kk * np + kk];
+        stau[kk] = zero ? 0.0 : 2.0 / vv;
+        se[kk] = zero ? 0.0 : alpha;
+        skip = zero ? 1 : 0;
+      }
+    }
+    __syncthreads();
+    if (skip) continue;
+    const double tau = stau[kk];
+    // p = tau A v; A is symmetric, so row i is read as column i (consecutive threads,
+    // consecutive addresses): two threads per row, each over half of the rows
+    {
+      const int q = tid >> 8, qn = (mr + kSets - 1) / kSets;
+      const int j0 = q * qn, j1 = min(mr, j0 + qn);
+      for (int i = tid & 255; i < mr; i += 256) {
+        const double* col = L + (kk + 1) * np + kk + 1 + i;
+        double acc = 0.0;
+        for (int j = j0; j < j1; ++j) acc += col[j * np] * vs[j];
+        pq[q][i] = acc;
+      }
+    }
+    __syncthreads();
+    if (wv == 0) {
+      double kp = 0.0;
+      for (int i = lane; i < mr; i += 64) {
+        double p = 0.0;
+#pragma unroll
+        for (int q = 0; q < kSets; ++q) p += pq[q][i];
+        p *= tau;
+        ps[i] = p;
+        kp += vs[i] * p;
+      }
+      const double Kc = 0.5 * tau * wave_sum_dpp(kp);
+      for (int i = lane; i < mr; i += 64) ws[i] = ps[i] - Kc * vs[i];
+    }
+    __syncthreads();
+    {
+      // this lane's entries of v and w stay in registers across the rows
+      constexpr int NQ = ((kLds ? kRRLdsOrder : kTriMax) + 63) / 64;
+      double vj[NQ], wj[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int j = lane + 64 * q;
+        vj[q] = j < mr ? vs[j] : 0.0;
+        wj[q] = j < mr ? ws[j] : 0.0;
+      }
+      for (int i = wv; i < mr; i += nw) {
+        double* row = L + (kk + 1 + i) * np + kk + 1;
+        const double vi = vs[i], wi = ws[i];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          const int j = lane + 64 * q;
+          // (which of the two products is rounded first is fixed, so that the result
+          // does not hang on the compiler's choice)
+          const double t = kLds ? fma(vi, wj[q], wi * vj[q]) : fma(wi, vj[q], vi * wj[q]);
+          if (j < mr) row[j] -= t;
+        }
+        if (lane == 0) L[(kk + 1 + i) * np + kk] = vi;
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    if (m >= 2) {
+      sd[m - 2] = L[(size_t)(m - 2) * np + m - 2];
+      se[m - 2] = L[(size_t)(m - 1) * np + m - 2];
+      stau[m - 2] = 0.0;
+    }
+    sd[m - 1] = L[(size_t)(m - 1) * np + m - 1];
+    se[m - 1] = 0.0;
+  }
+  // T, the reflectors (column kk with zeros in rows <= kk) and tau for the kernels below
+  double* Rf = E.small + rr_slot(kSlotRefl, KP);
+  __syncthreads();
+  for (int i = tid; i < m; i += nt) {
+    vec[VS_T0 * KP + i] = sd[i];
+    vec[VS_T1 * KP + i] = se[i];
+    vec[VS_T2 * KP + i] = i < m - 2 ? stau[i] : 0.0;
+  }
+  for (int kk = wv; kk < m - 2; kk += nw)
+    for (int i = lane; i < np; i += 64)
+      Rf[(size_t)kk * np + i] = (i > kk && i < m) ? L[(size_t)i * np + kk] : 0.0;
+}
+
+// ---------------------------------------------------------------------------
+// eigenvalues 0..nwant-1 (ascending) of the tridiagonal T by multisection on Sturm
+// counts.  One round takes the counts at the 8 interior points of the bracket, which
+// shrinks 9-fold; it keeps count(lo) <= j < count(hi) and stops below 2 eps ||T|| or a
+// few ulps of its end points (FP64: about 17 rounds).
+// Bound by the serial count (a reciprocal and five fused operations per row, about 100
+// cycles), so a workgroup of two waves owns one eigenvalue and takes two rounds per
+// count: lanes 0..7 the round's points, 72 more lanes the points of each of the nine
+// brackets it may leave.  Order 264, 88 eigenvalues: 140 us; 490 us in the element's one
+// workgroup, eight lanes per eigenvalue, before.
+// ---------------------------------------------------------------------------
+constexpr int kEigThreads = 128;
+
+__global__ void __launch_bounds__(kEigThreads) k_rr_eig(RRArgs A) {
+  const int e = blockIdx.y;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  const int j = blockIdx.x;
+  if (j >= s.nwant) return;
+  rr_stamp(A, e, 4, blockIdx.x);
+  const int m = s.n;
+  double* vec = E.small + SmallLayout::vec(s.KP);
+  const double* gd = vec + VS_T0 * s.KP;
+  const double* ge = vec + VS_T1 * s.KP;
+  double* lam = vec + VS_FLAGS * s.KP;
+  __shared__ double sd[kTriMax], se[kTriMax];
+  __shared__ double sh[16];
+  __shared__ unsigned long long bits[2][2];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  for (int i = tid; i < m; i += kEigThreads) {
+    sd[i] = gd[i];
+    se[i] = ge[i];
+  }
+  __syncthreads();
+  // Gershgorin bounds
+  double lo = 1e300, hi = -1e300, nrm = 0.0;
+  for (int i = tid; i < m; i += kEigThreads) {
+    const double r = (i > 0 ? fabs(se[i - 1]) : 0.0) + (i < m - 1 ? fabs(se[i]) : 0.0);
+    lo = fmin(lo, sd[i] - r);
+    hi = fmax(hi, sd[i] + r);
+    nrm = fmax(nrm, fabs(sd[i]) + r);
+  }
+  const double onenorm = fmax(block_max(nrm, sh), 1e-300);
+  lo = -block_max(-lo, sh);
+  hi = block_max(hi, sh);
+  lo = lo - 1e-12 * onenorm - 1e-300;
+  hi = hi + 1e-12 * onenorm + 1e-300;
+  const double pivmin = 1e-300 + 1e-30 * onenorm * onenorm;
+  const double abstol = 2.0 * 2.2204460492503131e-16 * onenorm;
+  // a round's update from the flags of its 8 points (count > j)
+  auto shrink = [](unsigned b, double step, double& l, double& h) {
+    if (b == 0) {
+      l = l + step * 8.0;
+    } else {
+      const int f = __ffs(b) - 1;   // first point whose count exceeds j
+      const double nlo = f > 0 ? l + step * (double)f : l;
+      h = l + step * (double)(f + 1);
+      l = nlo;
+    }
+  };
+  auto wide = [&](double l, double h) {
+    return h - l > fmax(abstol, 4.0 * 2.2204460492503131e-16 * fmax(fabs(l), fabs(h)));
+  };
+  // this lane's point: of the current bracket (tid < 8), or of the bracket that the
+  // round leaves when its first exceeding point is f (8: none)
+  const int f = (tid - 8) >> 3, t = tid & 7;
+  for (int r = 0; r < 80; r += 2) {
+    if (!wide(lo, hi)) break;
+    const double step = (hi - lo) * (1.0 / 9.0);
+    int cnt = 0;
+    if (tid < 80) {
+      double pl = lo, ph = hi, ps = step;
+      if (tid >= 8) {
+        shrink(f < 8 ? 1u << f : 0u, step, pl, ph);
+        ps = (ph - pl) * (1.0 / 9.0);
+      }
+      cnt = sturm_count(sd, se, m, pl + ps * (double)(t + 1), pivmin);
+    }
+    const unsigned long long bl = __ballot(tid < 80 && cnt > j);
+    const int buf = (r >> 1) & 1;   // two buffers: one barrier per count
+    if (lane == 0) bits[buf][wv] = bl;
+    __syncthreads();
+    const unsigned long long b0 = bits[buf][0], b1 = bits[buf][1];
+    const unsigned first = (unsigned)(b0 & 0xFF);
+    const int at = 8 + 8 * (first ? __ffs(first) - 1 : 8);   // the second round's flags
+    const unsigned second = (unsigned)((at < 64 ? b0 >> at : b1 >> (at - 64)) & 0xFF);
+    shrink(first, step, lo, hi);
+    if (!wide(lo, hi)) break;
+    shrink(second, (hi - lo) * (1.0 / 9.0), lo, hi);
+  }
+  if (tid == 0) {
+    lam[j] = 0.5 * (lo + hi);
+    if (j == 0) lam[s.KP - 1] = onenorm;   // for the eigenvectors
+  }
+}
+
+// ---------------------------------------------------------------------------
+// eigenvectors of T by inverse iteration.  Eigenvalues closer than ortol ||T|| form a
+// cluster, whose vectors are computed in order, each re-orthogonalised against the
+// earlier ones; a lane owns the clusters that start at its index.  Serial per vector
+// (LU with partial pivoting, two or four solves), so the vectors are spread over the
+// chip, four clusters per one-wave workgroup, with the factors in LDS.
+// Order 264, 88 vectors: 115 us; 1020 us in the element's one workgroup (factors in L2)
+// before.
+// ---------------------------------------------------------------------------
+constexpr int kInvPerWg = 4;
+
+__host__ __device__ constexpr size_t inv_lds(int np) { return (size_t)np * kInvPerWg * (5 * sizeof(double) + 1); }
+
+__global__ void __launch_bounds__(64) k_rr_inv(RRArgs A) {
+  const int e = blockIdx.y;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  const int j0 = blockIdx.x * kInvPerWg;
+  if (j0 >= s.nwant) return;
+  rr_stamp(A, e, 5, blockIdx.x);
+  const int m = s.n, np = s.np, nwant = s.nwant;
+  const double* vec = E.small + SmallLayout::vec(s.KP);
+  const double* gd = vec + VS_T0 * s.KP;
+  const double* ge = vec + VS_T1 * s.KP;
+  const double* lam = vec + VS_FLAGS * s.KP;
+  double* Zv = E.small + rr_slot(kSlotVec, s.KP);
+  extern __shared__ double dyn[];
+  __shared__ double sd[kTriMax], se[kTriMax], slam[kTriMax];
+  const int lane = threadIdx.x;
+  for (int i = lane; i < m; i += 64) {
+    sd[i] = gd[i];
+    se[i] = ge[i];
+  }
+  for (int i = lane; i < nwant; i += 64) slam[i] = lam[i];
+  __syncthreads();
+  const double onenorm = lam[s.KP - 1];
+  const double ortol = A.ortol * onenorm, pertol = 10.0 * 2.2e-16 * onenorm;
+  const int c = j0 + lane;
+  if (lane >= kInvPerWg || c >= nwant) return;
+  if (c > 0 && slam[c] - slam[c - 1] <= ortol) return;   // not the first of its cluster
+  constexpr int R = kInvPerWg;
+  StridedD ta{dyn + 0 * (size_t)np * R + lane, R};
+  StridedD tb{dyn + 1 * (size_t)np * R + lane, R};
+  StridedD tu{dyn + 2 * (size_t)np * R + lane, R};
+  StridedD tl{dyn + 3 * (size_t)np * R + lane, R};
+  StridedD z{dyn + 4 * (size_t)np * R + lane, R};
+  StridedB pv{reinterpret_cast<unsigned char*>(dyn + 5 * (size_t)np * R) + lane, R};
+  double shift = slam[c];
+  for (int j = c; j < nwant; ++j) {
+    if (j > c) {
+      if (!(slam[j] - slam[j - 1] <= ortol)) break;
+      double sj = slam[j];
+      if (sj < shift + pertol) sj = shift + pertol;
+      shift = sj;
+    }
+    tri_lu(sd, se, m, shift, 2.2e-16 * onenorm, ta, tb, tu, tl, pv);
+    for (int i = 0; i < m; ++i) z[i] = hash_unit(j, i);
+    // an isolated eigenvalue needs no re-orthogonalisation: two solves (growth
+    // at most ~1/(eps ||T||) each, far from overflow), one normalisation
+    const bool single = j == c && (j + 1 >= nwant || !(slam[j + 1] - slam[j] <= ortol));
+    const int n_it = single ? 2 : 4;
+    for (int it = 0; it < n_it; ++it) {
+      tri_solve(m, ta, tb, tu, tl, pv, z);
+      if (single && it + 1 < n_it) continue;
+      for (int q = c; q < j; ++q) {
+        const double* zq = Zv + (size_t)q * np;
+        double dot = 0.0;
+        strided_blocks(m, [&](int i, auto u) {
+          double a[CVN(u)], b[CVN(u)];
+          for_n(u, [&](int k) { a[k] = zq[i + k]; b[k] = z[i + k]; });
+          for_n(u, [&](int k) { dot += a[k] * b[k]; });
+        });
+        strided_blocks(m, [&](int i, auto u) {
+          double a[CVN(u)], b[CVN(u)];
+          for_n(u, [&](int k) { a[k] = zq[i + k]; b[k] = z[i + k]; });
+          for_n(u, [&](int k) { b[k] -= dot * a[k]; });
+          for_n(u, [&](int k) { z[i + k] = b[k]; });
+        });
+      }
+      double nn = 0.0;
+      strided_blocks(m, [&](int i, auto u) {
+        double b[CVN(u)];
+        for_n(u, [&](int k) { b[k] = z[i + k]; });
+        for_n(u, [&](int k) { nn += b[k] * b[k]; });
+      });
+      nn = 1.0 / sqrt(nn);
+      strided_blocks(m, [&](int i, auto u) {
+        double b[CVN(u)];
+        for_n(u, [&](int k) { b[k] = z[i + k]; });
+        for_n(u, [&](int k) { z[i + k] = b[k] * nn; });
+      });
+    }
+    strided_blocks(m, [&](int i, auto u) {
+      double b[CVN(u)];
+      for_n(u, [&](int k) { b[k] = z[i + k]; });
+      for_n(u, [&](int k) { Zv[(size_t)j * np + i + k] = b[k]; });
+    });
+    if (np > m) Zv[(size_t)j * np + m] = 0.0;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// in-order Gram-Schmidt on the eigenvectors, one workgroup per element: each vector
+// against all earlier ones (dot products a wave each, the update a quad of lanes per row
+// with the sum over vectors split four ways), then its norm.  A serial chain over the
+// vectors, so the vectors stay in LDS, as many as fit (the later ones are read from L2).
+// NT threads set the order of the norm's sum: 512 for orders that fit in LDS as a
+// matrix, 1024 above.  Order 264, 88 vectors: 310 us; 751 us with all vectors in L2 before.
+// ---------------------------------------------------------------------------
+constexpr int kMgsLds = kLdsPerCU - 8192;   // dynamic LDS limit
+
+template <int NT>
+__global__ void __launch_bounds__(NT) k_rr_mgs(RRArgs A) {
+  const int e = blockIdx.x;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  rr_stamp(A, e, 6, 0);
+  const int m = s.n, np = s.np, nwant = s.nwant;
+  double* Zv = E.small + rr_slot(kSlotVec, s.KP);
+  extern __shared__ double dyn[];
+  __shared__ double ps[kOrthMax];
+  __shared__ double sh[16];
+  constexpr int nw = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  double* zj = dyn;                 // the current vector
+  double* zl = dyn + np;            // vectors 0 .. cap - 1
+  const int cap = min(nwant, A.lds_dyn / (np * (int)sizeof(double)) - 1);
+  for (int idx = tid; idx < cap * np; idx += NT) zl[idx] = Zv[idx];
+  __syncthreads();
+  for (int j = 1; j < nwant; ++j) {
+    // (vector 0 stays as inverse iteration left it)
+    for (int i = tid; i < np; i += NT) zj[i] = j < cap ? zl[j * np + i] : Zv[(size_t)j * np + i];
+    __syncthreads();
+    for (int q = wv; q < j; q += nw) {
+      double dot = 0.0;
+      if (q < cap) {
+        const double* zq = zl + q * np;
+        for (int i = lane; i < m; i += 64) dot += zq[i] * zj[i];
+      } else {
+        const double* zq = Zv + (size_t)q * np;
+        for (int i = lane; i < m; i += 64) dot += zq[i] * zj[i];
+      }
+      dot = wave_sum_dpp(dot);
+      if (lane == 0) ps[q] = dot;
+    }
+    __syncthreads();
+    // z_j -= sum_q (z_q . z_j) z_q; per-wave sums of squares for the norm
+    const int ql = tid & 3;
+    double part = 0.0;
+    for (int i = tid >> 2; i < m; i += NT >> 2) {
+      double t = 0.0;
+      const int jl = min(j, cap);
+      int q = ql;
+      for (; q < jl; q += 4) t += ps[q] * zl[q * np + i];
+      for (; q < j; q += 4) t += ps[q] * Zv[(size_t)q * np + i];
+      t += dpp_mov<0xB1>(t);   // quad_perm [1,0,3,2]
+      t += dpp_mov<0x4E>(t);   // quad_perm [2,3,0,1]
+      if (ql == 0) {
+        const double v = zj[i] - t;
+        zj[i] = v;
+        part += v * v;
+      }
+    }
+    part = wave_sum_dpp(part);
+    if (lane == 0) sh[wv] = part;
+    __syncthreads();
+    double nn2 = 0.0;
+    for (int q = 0; q < nw; ++q) nn2 += sh[q];
+    const double nn = 1.0 / sqrt(nn2);
+    for (int i = tid; i < m; i += NT) {
+      const double v = zj[i] * nn;
+      if (j < cap) zl[j * np + i] = v;
+      Zv[(size_t)j * np + i] = v;
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// back-transformation z <- H_0 ... H_{m-3} z of the eigenvectors, in place.  A vector's
+// reflectors are a serial chain (dot product, reduction, update), so every vector has
+// lanes of its own and the vectors are spread over the chip: a wave per vector (kWave),
+// or eight lanes for the orders that fit in LDS as a matrix.  The vectors sit in LDS and
+// the reflectors stream through it, kBackChunk at a time, the next ones in flight.
+// Order 264, 88 vectors: 127 us; 1766 us in the element's one workgroup, both in L2, before.
+// ---------------------------------------------------------------------------
+constexpr int kBackThreads = 256;
+constexpr int kBackChunk = 16;
+constexpr int kBackStage = (kBackChunk * kTriMax + kBackThreads - 1) / kBackThreads;
+template <bool kWave>
+constexpr int kBackVecs = kWave ? kBackThreads / 64 : kBackThreads / 8;   // vectors per workgroup
+
+template <bool kWave>
+constexpr size_t back_lds(int np) { return (size_t)(kBackVecs<kWave> + kBackChunk) * np * sizeof(double); }
+
+template <bool kWave>
+__global__ void __launch_bounds__(kBackThreads) k_rr_back(RRArgs A) {
+  const int e = blockIdx.y;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  constexpr int NV = kBackVecs<kWave>;
+  const int j0 = blockIdx.x * NV;
+  if (j0 >= s.nwant) return;
+  rr_stamp(A, e, 7, blockIdx.x);
+  const int m = s.n, np = s.np, nwant = s.nwant;
+  const double* gtau = E.small + SmallLayout::vec(s.KP) + VS_T2 * s.KP;
+  const double* Rf = E.small + rr_slot(kSlotRefl, s.KP);
+  double* V = E.small + rr_slot(kSlotVec, s.KP);
+  extern __shared__ double dyn[];
+  __shared__ double stau[kTriMax];
+  double* rl = dyn;                            // reflectors of the chunk
+  double* zl = dyn + (size_t)kBackChunk * np;  // vectors
+  const int tid = threadIdx.x;
+  constexpr int LPV = kWave ? 64 : 8;          // lanes per vector
+  const int l = tid % LPV, slot = tid / LPV;
+  const int nv = min(NV, nwant - j0);
+  for (int i = tid; i < m; i += kBackThreads) stau[i] = gtau[i];
+  for (int idx = tid; idx < nv * np; idx += kBackThreads) zl[idx] = V[(size_t)j0 * np + idx];
+  const int nrefl = max(0, m - 2);
+  const int nchunk = (nrefl + kBackChunk - 1) / kBackChunk;
+  double pre[kBackStage];
+  auto fetch = [&](int c) {
+    const int cnt = min(kBackChunk, nrefl - c * kBackChunk) * np;
+    const double* src = Rf + (size_t)c * kBackChunk * np;
+#pragma unroll
+    for (int u = 0; u < kBackStage; ++u) {
+      const int idx = tid + kBackThreads * u;
+      if (idx < cnt) pre[u] = gload<double>(src + idx);
+    }
+  };
+  if (nchunk > 0) fetch(nchunk - 1);
+  for (int c = nchunk - 1; c >= 0; --c) {
+    const int k0 = c * kBackChunk, nk = min(kBackChunk, nrefl - k0), cnt = nk * np;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kBackStage; ++u) {
+      const int idx = tid + kBackThreads * u;
+      if (idx < cnt) rl[idx] = pre[u];
+    }
+    __syncthreads();
+    if (c > 0) fetch(c - 1);
+    if (slot < nv) {
+      for (int k = nk - 1; k >= 0; --k) {
+        const int kk = k0 + k;
+        const double tau = stau[kk];
+        if (tau == 0.0) continue;
+        const double* v = rl + k * np + kk + 1;   // rows kk + 1 .. m - 1
+        double* z = zl + slot * np + kk + 1;
+        const int len = m - 1 - kk;
+        if constexpr (kWave) {
+          constexpr int NQ = (kTriMax + 63) / 64;
+          double vq[NQ], zq[NQ], dot = 0.0;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            if (64 * q < len) {
+              const int i = l + 64 * q;
+              vq[q] = i < len ? v[i] : 0.0;
+              zq[q] = i < len ? z[i] : 0.0;
+            }
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            if (64 * q < len && l + 64 * q < len) dot += vq[q] * zq[q];
+          dot = wave_sum_dpp(dot) * tau;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            if (64 * q < len && l + 64 * q < len) z[l + 64 * q] = zq[q] - dot * vq[q];
+        } else {
+          constexpr int NQ = (kRRLdsOrder + 7) / 8;
+          double vq[NQ], zq[NQ], dot = 0.0;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            if (8 * q < len) {
+              const int i = l + 8 * q;
+              vq[q] = i < len ? v[i] : 0.0;
+              zq[q] = i < len ? z[i] : 0.0;
+            }
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            if (8 * q < len && l + 8 * q < len) dot += vq[q] * zq[q];
+          dot = group8_sum(dot) * tau;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            if (8 * q < len && l + 8 * q < len) z[l + 8 * q] = zq[q] - dot * vq[q];
+        }
+        // the next reflector's lanes read rows that other lanes of the group wrote
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
+  __syncthreads();
+  for (int idx = tid; idx < nv * np; idx += kBackThreads) V[(size_t)j0 * np + idx] = zl[idx];
+}
+
+// ---------------------------------------------------------------------------
+// coefficients: C = D Z V (RR_GEN, 16x16 FP64 MFMA tiles, one wave each; Z[i][k] = 0 for
+// k < i, so a tile's k range starts at its first row; left-out rows are zero, d = 0), or
+// the singular vectors over their singular values, descending (RR_SVD)
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) k_rr_coef(RRArgs A) {
+  const int e = blockIdx.y;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  const int n = s.n, np = s.np, nkeep = s.nkeep, nwant = s.nwant;
+  double* vec = E.small + SmallLayout::vec(s.KP);
+  const double* d = vec + VS_D * s.KP;
+  const double* lam = vec + VS_FLAGS * s.KP;
+  double* theta = vec + VS_THETA * s.KP;
+  const double* Z = E.small + rr_slot(kSlotZ, s.KP);
+  const double* V = E.small + rr_slot(kSlotVec, s.KP);
+  double* C = E.small + SmallLayout::C(s.KP);
+  if (s.svd) {
+    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n * nkeep; idx += gridDim.x * 256) {
+      const int i = idx / nkeep, j = idx % nkeep;
+      const int col = n - 1 - j;
+      const double sg = (col >= 0) ? sqrt(fmax(lam[col], 0.0)) : 0.0;
+      C[idx] = (col >= 0 && sg > 0.0) ? V[(size_t)col * np + i] / sg : 0.0;
+    }
+    if (blockIdx.x == 0)
+      for (int j = threadIdx.x; j < nkeep; j += 256)
+        theta[j] = (n - 1 - j >= 0) ? sqrt(fmax(lam[n - 1 - j], 0.0)) : 0.0;
+    return;
+  }
+  rr_stamp(A, e, 8, blockIdx.x);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int nti = (n + 15) >> 4, ntj = (nkeep + 15) >> 4;
+  const int kst = (n + 3) >> 2;
+  const int tile = blockIdx.x * 4 + wv;
+  if (tile < nti * ntj) {
+    const int ti = tile / ntj, tj = tile % ntj;
+    const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
+    d4v acc = {0.0, 0.0, 0.0, 0.0};
+    for (int ks = ti * 4; ks < kst; ++ks) {
+      const int k = ks * 4 + (lane >> 4);
+      const double av = (ia < n && k < n && k >= ia) ? Z[(size_t)ia * np + k] : 0.0;
+      const double bv = (jb < nwant && k < n) ? V[(size_t)jb * np + k] : 0.0;
+      acc = mfma16x16x4(av, bv, acc);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = ti * 16 + (lane >> 4) + 4 * q;
+      if (i < n && jb < nkeep) C[(size_t)i * nkeep + jb] = jb < nwant ? d[i] * acc[q] : 0.0;
+    }
+  }
+  if (blockIdx.x == 0)
+    for (int j = threadIdx.x; j < nkeep; j += 256) theta[j] = j < nwant ? lam[j] : 0.0;
+}
+
+// ---------------------------------------------------------------------------
+// launcher
+// ---------------------------------------------------------------------------
+void init_rr_attributes() {
+  static const bool done = [] {
+    auto lds = [](const void* fn, int bytes) {
+      (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    };
+    lds((const void*)k_rr_head<true>, kRRLdsBytes);
+    lds((const void*)k_rr_inv, (int)inv_lds(kTriMax));
+    lds((const void*)k_rr_mgs<512>, kMgsLds);
+    lds((const void*)k_rr_mgs<1024>, kMgsLds);
+    lds((const void*)k_rr_back<true>, (int)back_lds<true>(kTriMax));
+    lds((const void*)k_rr_back<false>, (int)back_lds<false>(kRRLdsOrder));
+    return true;
+  }();
+  (void)done;
+}
+
+int launch_rr(Ctx& c, int nb, int kfix, int nkeep, int mode, const int* active) {
+  // algorithmic flop estimate: Cholesky + inverse (n^3/3 each), two n^3 products,
+  // tridiagonalisation (4n^3/3), back-transformation and coefficients (4 n^2 k)
+  double flops = 0.0;
+  int npmax = 0;
+  size_t need = 0;   // bytes of the working matrix
+  int nmax = 0, nwmax = 0, nkmax = 0;
+  for (int e = 0; e < c.n_elem; ++e) {
+    const int n = mode == RR_GEN ? nb * c.K[e] : (kfix > 0 ? kfix : (kfix == 0 ? c.K[e] : c.J[e]));
+    const int npe = n + (n & 1);
+    const int nk = nkeep > 0 ? nkeep : (nkeep == 0 ? c.K[e] : c.J[e]);
+    nmax = std::max(nmax, n);
+    nkmax = std::max(nkmax, nk);
+    nwmax = std::max(nwmax, mode == RR_SVD ? n : std::min(nk, n));
+    npmax = std::max(npmax, npe);
+    need = std::max(need, (size_t)npe * npe * sizeof(double));
+    if (active && !c.active_host.empty() && !c.active_host[e]) continue;
+    flops += (mode == RR_GEN ? 2.0 / 3.0 + 2.0 : 0.0) * (double)n * n * n + 4.0 / 3.0 * (double)n * n * n +
+             4.0 * (double)n * n * nk;
+  }
+  if (npmax > kTriMax) {
+    set_error("projected problem of order " + std::to_string(npmax) + " above the limit " +
+              std::to_string(kTriMax));
+    return DG_ERR_SHAPE;
+  }
+  // the working region lives in LDS when the orders allow it, else in the element's
+  // slice of the Gram partial-sum area (free between the Gram reduction and the rotation)
+  const bool in_lds = npmax <= kRRLdsOrder && need <= (size_t)kRRLdsBytes;
+  if (!in_lds && need > (size_t)c.gram_part_stride * sizeof(double)) {
+    set_error("Rayleigh-Ritz work region of " + std::to_string(need) + " bytes above the partial-sum slice");
+    return DG_ERR_SHAPE;
+  }
+  RRArgs a{c.elems_dev, active, nb, kfix, nkeep, mode, c.dev_status,
+           c.log_level >= 2 ? c.dev_phase : nullptr, c.gram_part, c.gram_part_stride,
+           c.rr_pivot_tol, c.rr_drop_tol, c.log_level >= 3 ? c.dev_minpiv : nullptr, c.rr_ortol,
+           in_lds ? (int)need : 0, mode == RR_GEN ? c.dev_hpflag : nullptr, c.hp_tol};
+  TimedScope ts(c, TC_RR, flops);
+  if (in_lds) {
+    hipLaunchKernelGGL(k_rr_head<true>, dim3(c.n_elem), dim3(kRRThreads), need, c.stream, a);
+  } else {
+    hipLaunchKernelGGL(k_rr_head<false>, dim3(c.n_elem), dim3(kRRThreadsL2), 0, c.stream, a);
+  }
+  if (mode != RR_CHOLQR) {
+    auto over = [](int n, int per) { return (unsigned)((n + per - 1) / per); };
+    const unsigned ne = (unsigned)c.n_elem;
+    hipLaunchKernelGGL(k_rr_eig, dim3(nwmax, ne), dim3(kEigThreads), 0, c.stream, a);
+    hipLaunchKernelGGL(k_rr_inv, dim3(over(nwmax, kInvPerWg), ne), dim3(64), inv_lds(npmax), c.stream, a);
+    // as many vectors as fit, and the current one
+    const size_t mgs = std::min((size_t)kMgsLds, (size_t)(nwmax + 1) * npmax * sizeof(double));
+    a.lds_dyn = (int)mgs;
+    if (in_lds) {
+      hipLaunchKernelGGL(k_rr_mgs<512>, dim3(ne), dim3(512), mgs, c.stream, a);
+      hipLaunchKernelGGL(k_rr_back<false>, dim3(over(nwmax, kBackVecs<false>), ne), dim3(kBackThreads),
+                         back_lds<false>(npmax), c.stream, a);
+    } else {
+      hipLaunchKernelGGL(k_rr_mgs<1024>, dim3(ne), dim3(1024), mgs, c.stream, a);
+      hipLaunchKernelGGL(k_rr_back<true>, dim3(over(nwmax, kBackVecs<true>), ne), dim3(kBackThreads),
+                         back_lds<true>(npmax), c.stream, a);
+    }
+    hipLaunchKernelGGL(k_rr_coef, dim3(over(over(nmax, 16) * over(nkmax, 16), 4), ne), dim3(256), 0, c.stream, a);
+  }
+  DG_HIP(hipGetLastError());
+  return DG_OK;
+}
+
+
+}  // namespace dg

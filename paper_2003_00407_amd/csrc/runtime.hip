@@ -371,6 +371,7 @@ int create(Ctx** out, int n_elem, const dg_element_desc* d, const dg_options* op
     return DG_ERR_OOM;
   }
   init_kernel_attributes();
+  init_rr_attributes();
   // owned here until every staging step has succeeded (no leak on an early return)
   std::unique_ptr<Ctx> owner(new Ctx());
   Ctx* c = owner.get();

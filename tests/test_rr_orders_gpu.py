@@ -60,3 +60,24 @@ def test_orders_across_lds_limit_vs_dense(precision):
         assert err < 1e-8
         assert orth < 1e-10
         assert rn < 2e-9
+
+
+@pytest.mark.parametrize("J, guards", [(1, 4), (17, 4), (18, 4), (39, 4), (56, 8), (57, 8), (80, 8)])
+def test_projected_orders_at_tile_edges_vs_dense(J, guards):
+    """Projected orders 15, 63, 66, 129, 192, 195 and 264: on both sides of the 16-row
+    tiles, the 64-row register chunks and the 16-vector workgroups of the Rayleigh-Ritz
+    kernels.  Eigenvalues are second order in the residual (1e-9), so dense eigh is met to
+    rounding: 1e-10 leaves a factor of a thousand over eps ||H||."""
+    torch = need_torch_cuda()
+    from paper_2003_00407_amd import dgalb as D
+    rng = np.random.default_rng(J)
+    el = W._box_element((12, 12, 12), (8.0, 8.0, 8.0), rng.uniform(0.0, 8.0, size=(4, 3)), J)
+    print(f"[rr-orders] J {J} guards {guards}: order {3 * (J + guards)}", flush=True)
+    E = D.Elements([el], n_guard=guards)
+    eig, res, iters, st = E.solve(None, tol=1e-9, seed=3)
+    X = E.vectors().cpu().numpy().reshape(J, el.npts).T
+    assert st == 0
+    H = _separable_dense_T(el.n, el.length) + np.diag(el.v_eff)
+    ref = scipy.linalg.eigh(H, eigvals_only=True, subset_by_index=[0, J - 1])
+    assert np.max(np.abs(eig.cpu().numpy() - ref)) < 1e-10
+    assert np.max(np.abs(X.T @ X - np.eye(J))) < 1e-10
