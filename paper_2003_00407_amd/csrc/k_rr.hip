@@ -2,8 +2,10 @@
 // (S^T H S, S^T S) for S = [X W P] (Eq. (4); Algorithm 1 step 5, Algorithm 2 step 4), and
 // the eigen-decomposition and Cholesky-QR passes of the ALB orthonormalisation.
 //
-//   scaled overlap -> Cholesky with column dropping -> U^{-1} = Z -> A^ = Z^T A~ Z
-//   -> Householder tridiagonal T                       (k_rr_head, one workgroup per element)
+//   scaled overlap -> Cholesky with column dropping    (k_rr_chol, one workgroup per element)
+//   -> U^{-1} = Z                                      (k_rr_zinv_*, a wave or a quad of lanes per row)
+//   -> A^ = Z^T A~ Z                                   (k_rr_prod, a wave per 16x16 tile)
+//   -> Householder tridiagonal T                       (k_rr_tri, one workgroup per element)
 //   -> eigenvalues of T by multisection                (k_rr_eig, a workgroup per eigenvalue)
 //   -> eigenvectors of T by inverse iteration          (k_rr_inv, a lane per vector)
 //   -> in-order Gram-Schmidt                           (k_rr_mgs, one workgroup per element)
@@ -50,18 +52,20 @@ constexpr int kTriMax = 272;   // largest projected problem handled (3 x 88 + pa
 constexpr int kOrthMax = 88;   // most eigenvectors (J + guards)
 
 constexpr int kLdsPerCU = 163840;                 // 160 KB of LDS per compute unit
-constexpr int kRRStaticLds = 21504;               // bound on k_rr_head's static LDS
+constexpr int kRRStaticLds = 21504;               // bound on k_rr_tri's static LDS
 constexpr int kRRLdsBytes = kLdsPerCU - kRRStaticLds;
 constexpr int kRRLdsOrder = 132;                  // np * np doubles fit in kRRLdsBytes
 
 // where the steps leave their matrices (leading dimension np); the inputs are S^T S in
 // slot G and S^T H S in slot A (leading dimension n), the result C is in slot C
-enum RRSlot { kSlotZ, kSlotRefl, kSlotVec };
+enum RRSlot { kSlotUt, kSlotZ, kSlotT, kSlotAhat, kSlotRefl, kSlotVec };
 __device__ __forceinline__ long long rr_slot(RRSlot w, int KP) {
   switch (w) {
-    case kSlotZ: return SmallLayout::G(KP);
-    case kSlotRefl: return SmallLayout::A(KP);
-    default: return SmallLayout::U(KP);
+    case kSlotZ: return SmallLayout::G(KP);      // S^T S is done with once it is factored
+    case kSlotT: return SmallLayout::V(KP);
+    case kSlotAhat:                              // S^T H S is done with once T is formed
+    case kSlotRefl: return SmallLayout::A(KP);   // A^ is read before the reflectors are written
+    default: return SmallLayout::U(KP);          // U^T until Z is formed, then the eigenvectors
   }
 }
 
@@ -98,261 +102,474 @@ __device__ __forceinline__ void rr_stamp(const RRArgs& A, int e, int k, int bloc
 }
 
 // ---------------------------------------------------------------------------
-// overlap factorisation, standard form and Householder tridiagonalisation, one workgroup
-// per element.  The working matrix is dynamic LDS for orders up to kRRLdsOrder (kLds =
-// true) and the element's slice of the Gram partial-sum area above that (L2-resident).
-// G keeps Z, Vm the scaled A.
+// scaled overlap -> Cholesky with column dropping: U (upper, U^T U = D S^T S D), written
+// transposed (column j of U contiguous at Ut + j np), 1 / U_jj, the scaling D.
+//
+// One workgroup per element, right-looking in panels of 16 rows.  Every wave factors the
+// panel's diagonal block for itself (a lane per column, multipliers broadcast by lane
+// reads), carrying one trailing column per lane along, so a panel needs two barriers;
+// the trailing update is FP64 MFMA tiles.  v_mfma_f64_16x16x4f64 adds its four products
+// as a chain of fused multiply-adds in ascending k (checked on the device), so every
+// entry is updated by the same chain, one fused operation per row in ascending order, as
+// by rank-1 updates.  Nearly dependent W/P columns leave the basis.
+// Order 264: 252 us; 1870 us as 264 rank-1 updates of the L2-resident matrix, a barrier
+// each, before.
 // ---------------------------------------------------------------------------
-template <bool kLds>
-__global__ void __launch_bounds__(kLds ? kRRThreads : kRRThreadsL2) k_rr_head(RRArgs A) {
+constexpr int kCholThreads = 1024;
+constexpr int kCholPitch = 280;                                        // doubles per staged row
+constexpr int kCholLds = 3 * 16 * kCholPitch * (int)sizeof(double);    // panel rows (twice), multipliers
+
+__device__ __forceinline__ void no_basis_change(double* C, int n, int nkeep) {
+  for (int idx = threadIdx.x; idx < n * nkeep; idx += blockDim.x) {
+    const int i = idx / nkeep, j = idx % nkeep;
+    C[idx] = (i == j) ? 1.0 : 0.0;
+  }
+}
+
+__global__ void __launch_bounds__(kCholThreads) k_rr_chol(RRArgs A) {
   const int e = blockIdx.x;
   const ElemDev& E = A.elems[e];
   if (A.active && !A.active[e]) {
     if (A.hp_flag && threadIdx.x == 0) A.hp_flag[e] = 0;
     return;
   }
-  const int K = E.K;
-  const bool gen = A.mode == RR_GEN, svd = A.mode == RR_SVD;
-  const int n = gen ? A.nb * K : kcode(A.kfix, E);
-  const int kx = gen ? K : n;             // leading columns that are never left out
-  const int np = n + (n & 1);
-  const int nkeep = kcode(A.nkeep, E);
-  const int KP = E.kmax3 + 2;
-  double* G = E.small + SmallLayout::G(KP);     // in: S^T S (ld n); out: Z (ld np)
-  double* Am = E.small + SmallLayout::A(KP);    // in: S^T H S (ld n); then T; then A^
-  double* Um = E.small + SmallLayout::U(KP);    // staging: Z^T T, then eigenvectors of the tridiagonal
-  double* Vm = E.small + SmallLayout::V(KP);    // scaled A, then packed reflectors
-  double* Cm = E.small + SmallLayout::C(KP);
+  const RRShape s = rr_shape(A, E);
+  rr_stamp(A, e, 0, 0);
+  const int n = s.n, np = s.np;
+  const double* G = E.small + SmallLayout::G(s.KP);
+  double* Ut = E.small + rr_slot(kSlotUt, s.KP);
+  double* vec = E.small + SmallLayout::vec(s.KP);
+  double* d = vec + VS_D * s.KP;
+  double* rinv = vec + VS_T0 * s.KP;
+  double* W = A.work + (size_t)e * A.work_stride;   // working matrix, upper part
+  extern __shared__ double dyn[];
+  double* P = dyn;                       // the panel's rows as the trailing update left them
+  double* Pf = dyn + 16 * kCholPitch;    // factored
+  double* F = dyn + 32 * kCholPitch;     // -(row / pivot): multipliers of the trailing update
+  __shared__ double sd[kTriMax], sdiag[kTriMax], su[kTriMax];
+  __shared__ int brk;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  constexpr int nw = kCholThreads / 64;
+  if (tid == 0) brk = 0;
+  __syncthreads();
+  for (int i = tid; i < n; i += kCholThreads) {
+    const double gii = G[(size_t)i * n + i];
+    if (!(gii > 0.0) && i < s.kx) brk = 1;
+    sd[i] = gii > 0.0 ? 1.0 / sqrt(gii) : 0.0;
+  }
+  __syncthreads();
+  for (int idx = tid; idx < n * n; idx += kCholThreads) {
+    const int i = idx / n, j = idx % n;
+    if (j < i) continue;
+    const double s2 = sd[i] * sd[j];
+    W[(size_t)i * np + j] = G[idx] * s2;
+  }
+  const int l16 = lane & 15, kl = lane >> 4;
+  double pmin = 1.0;
+  int jmin = -1, ndrop = 0;
+  __syncthreads();
+  // the first panel's rows; later ones are left in P by the trailing update
+  for (int idx = tid; idx < 16 * n; idx += kCholThreads) {
+    const int r = idx / n, k = idx % n;
+    P[r * kCholPitch + k] = (r < n && k >= r) ? W[(size_t)r * np + k] : 0.0;
+  }
+  for (int j0 = 0; j0 < n; j0 += 16) {
+    const int nr = min(16, n - j0);
+    __syncthreads();
+    // this lane's columns: j0 + l16 of the diagonal block, and trailing column k
+    const int k = j0 + 16 + tid;
+    if (wv == 0 || j0 + 16 + 64 * wv < n) {
+      double c[16], t[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        c[r] = (r < nr && l16 < nr && l16 >= r) ? P[r * kCholPitch + j0 + l16] : 0.0;
+        t[r] = (r < nr && k < n) ? P[r * kCholPitch + k] : 0.0;
+      }
+      unsigned dropped = 0;   // rows of this panel that leave the basis
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        double f = 0.0;
+        if (j < nr) {
+          const double piv = lane_read(c[j], j);
+          if (piv < pmin) {
+            pmin = piv;
+            jmin = j0 + j;
+          }
+          if (j0 + j >= s.kx && !(piv > A.drop_tol)) {
+            dropped |= 1u << j;
+            ++ndrop;
+            t[j] = 0.0;
+          } else {
+            if (!(piv > A.pivot_tol) && tid == 0) brk = 1;
+            const double pinv = 1.0 / fmax(piv, 1e-300);
+            const double fj = c[j] * pinv;
+            f = -(t[j] * pinv);
+#pragma unroll
+            for (int i = j + 1; i < 16; ++i) {
+              const double fi = lane_read(fj, i);
+              c[i] = fma(-fi, c[j], c[i]);
+              t[i] = fma(-fi, t[j], t[i]);
+            }
+          }
+        }
+        if (k < n) F[j * kCholPitch + k] = f;
+      }
+      // rows j0 .. j0 + nr - 1, not yet divided by the square roots of their pivots
+      if (k < n) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          Pf[r * kCholPitch + k] = r < nr ? t[r] : 0.0;
+          if (r < nr) Ut[(size_t)k * np + j0 + r] = t[r];
+        }
+      }
+      if (wv == 0 && lane < nr) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (r <= l16 && r < nr) {
+            const bool on = !((dropped >> r) & 1);
+            if (r < l16) Ut[(size_t)(j0 + l16) * np + j0 + r] = on ? c[r] : 0.0;
+            else sdiag[j0 + r] = on ? fmax(c[r], 1e-300) : -1.0;   // -1: left out
+          }
+      }
+    }
+    __syncthreads();
+    // trailing update, upper tiles; the first tile row is the next panel
+    const int b0 = j0 + 16, nb = (n - b0 + 15) >> 4;
+    for (int tl = wv; b0 < n && tl < nb * (nb + 1) / 2; tl += nw) {
+      int ti = 0, tk = tl;
+      while (tk >= nb - ti) {
+        tk -= nb - ti;
+        ++ti;
+      }
+      tk += ti;
+      const int i0 = b0 + 16 * ti, kc = b0 + 16 * tk + l16;
+      const int ia = min(i0 + l16, n - 1), kb = min(kc, n - 1);   // beyond the matrix: results not stored
+      double a[4], b[4];
+      d4v acc;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        acc[q] = gload<double>(W + (size_t)min(i0 + kl + 4 * q, n - 1) * np + kb);
+        a[q] = F[(4 * q + kl) * kCholPitch + ia];
+        b[q] = Pf[(4 * q + kl) * kCholPitch + kb];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc = mfma16x16x4(a[q], b[q], acc);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = i0 + kl + 4 * q;
+        if (i >= n || kc >= n) continue;
+        if (ti == 0) P[(kl + 4 * q) * kCholPitch + kc] = acc[q];
+        else W[(size_t)i * np + kc] = acc[q];
+      }
+    }
+  }
+  __syncthreads();
+  // U: rows divided by the square roots of the pivots; a left-out row or column is zero
+  // beside its unit diagonal
+  for (int j = tid; j < n; j += kCholThreads) {
+    const double p = sdiag[j];
+    const double u = p < 0.0 ? 1.0 : sqrt(p);
+    su[j] = u;
+    rinv[j] = 1.0 / u;
+    if (p < 0.0) sd[j] = 0.0;
+  }
+  __syncthreads();
+  for (int k = wv; k < n; k += nw) {
+    const bool out = sd[k] == 0.0;
+    for (int j = lane; j <= k; j += 64) {
+      double* p = Ut + (size_t)k * np + j;
+      *p = j == k ? su[k] : (out ? 0.0 : *p / su[j]);
+    }
+  }
+  for (int i = tid; i < n; i += kCholThreads) d[i] = sd[i];
+  if (tid == 0) {
+    if (A.hp_flag) A.hp_flag[e] = (brk || !(pmin >= A.hp_tol)) ? 1 : 0;
+    if (A.minpiv) {
+      A.minpiv[3 * e] = pmin;
+      A.minpiv[3 * e + 1] = jmin;
+      A.minpiv[3 * e + 2] = ndrop;
+    }
+    A.status[e] = brk ? 2 : 0;
+  }
+  // X itself is not positive definite: keep X (C = [I; 0; 0]) and report it
+  if (brk) no_basis_change(E.small + SmallLayout::C(s.KP), n, s.nkeep);
+}
+
+// ---------------------------------------------------------------------------
+// Z = U^{-1}, row by row: Z[i][j] = -(1/U[j][j]) sum_{k=i}^{j-1} Z[i][k] U[k][j].  The rows
+// are independent chains over j, so each has lanes of its own, spread over the chip: a
+// wave (kWave: Z[i][k] on lane (k - i) % 64, the columns of U prefetched) or, for the
+// orders that fit in LDS as a matrix, a quad of lanes (the k sum split four ways).
+// RR_CHOLQR: the coefficients C = D Z.
+// Order 264: 93 us; 1070 us in the element's one workgroup, two barriers a column, before.
+// ---------------------------------------------------------------------------
+constexpr int kZinvRows = 4;   // rows per workgroup, kWave
+
+__global__ void __launch_bounds__(64 * kZinvRows) k_rr_zinv_wave(RRArgs A) {
+  const int e = blockIdx.y;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  rr_stamp(A, e, 1, blockIdx.x);
+  const int n = s.n, np = s.np;
+  const int lane = threadIdx.x & 63;
+  const int i = blockIdx.x * kZinvRows + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double* Ut = E.small + rr_slot(kSlotUt, s.KP);
+  double* Z = E.small + rr_slot(kSlotZ, s.KP);
+  const double* vec = E.small + SmallLayout::vec(s.KP);
+  const double* gr = vec + VS_T0 * s.KP;
+  __shared__ double rinv[kTriMax];
+  for (int x = threadIdx.x; x < n; x += blockDim.x) rinv[x] = gr[x];
+  __syncthreads();
+  if (i >= n) return;
+  constexpr int NQ = (kTriMax + 63) / 64, NC = 4;
+  double z[NQ], u[NC][NQ], un[NC][NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) z[q] = 0.0;
+  if (lane == 0) z[0] = rinv[i];
+  // columns jb .. jb + 3 of U, rows i + lane + 64 q above the diagonal
+  auto load = [&](int jb, double (&dst)[NC][NQ]) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        // on and past the diagonal (where Z is still zero): the diagonal
+        const int j = min(jb + c, n - 1), k = min(i + lane + 64 * q, j);
+        if (64 * q < jb + NC - i) dst[c][q] = gload<double>(Ut + (size_t)j * np + k);
+      }
+  };
+  if (i + 1 < n) load(i + 1, un);
+  for (int jb = i + 1; jb < n; jb += NC) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) u[c][q] = un[c][q];
+    if (jb + NC < n) load(jb + NC, un);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int j = jb + c;
+      if (j >= n) continue;
+      double t = 0.0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (64 * q < j - i) t = fma(z[q], u[c][q], t);
+      t = wave_sum_dpp(t);
+      const double zj = -rinv[j] * t;
+      const int off = j - i;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if ((off >> 6) == q && lane == (off & 63)) z[q] = zj;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int k = i + lane + 64 * q;
+    if (k < n) Z[(size_t)i * np + k] = z[q];
+  }
+  if (!s.gen) {
+    const double di = vec[VS_D * s.KP + i];
+    double* C = E.small + SmallLayout::C(s.KP) + (size_t)i * s.nkeep;
+    for (int k = lane; k < i && k < s.nkeep; k += 64) C[k] = 0.0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int k = i + lane + 64 * q;
+      if (k < s.nkeep) C[k] = k < n ? di * z[q] : 0.0;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(64) k_rr_zinv_quad(RRArgs A) {
+  const int e = blockIdx.y;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  const int n = s.n, np = s.np;
+  const int i0 = blockIdx.x * 16;
+  if (i0 >= n) return;
+  rr_stamp(A, e, 1, blockIdx.x);
+  const int tid = threadIdx.x, ql = tid & 3, r = tid >> 2, i = i0 + r;
+  const double* Ut = E.small + rr_slot(kSlotUt, s.KP);
+  double* Z = E.small + rr_slot(kSlotZ, s.KP);
+  const double* vec = E.small + SmallLayout::vec(s.KP);
+  const double* rinv = vec + VS_T0 * s.KP;
+  constexpr int kPitch = kRRLdsOrder + 1;
+  __shared__ double zl[16][kPitch], ul[16][kPitch], ri[kPitch];
+  for (int x = tid; x < n; x += 64) ri[x] = rinv[x];
+  for (int x = tid; x < 16 * kPitch; x += 64) zl[x / kPitch][x % kPitch] = 0.0;
+  __syncthreads();
+  if (ql == 0 && i < n) zl[r][i] = ri[i];
+  constexpr int NS = (16 * kRRLdsOrder + 63) / 64;
+  double pre[NS];
+  // columns j0 .. j0 + 15 of U from row i0 on
+  auto fetch = [&](int j0) {
+#pragma unroll
+    for (int x = 0; x < NS; ++x) {
+      const int c = (tid + 64 * x) & 15, k = i0 + ((tid + 64 * x) >> 4);
+      pre[x] = (j0 + c < n && k < j0 + c) ? gload<double>(Ut + (size_t)(j0 + c) * np + k) : 0.0;
+    }
+  };
+  fetch(i0);
+  for (int j0 = i0; j0 < n; j0 += 16) {
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < NS; ++x) {
+      const int c = (tid + 64 * x) & 15, k = i0 + ((tid + 64 * x) >> 4);
+      if (k < kRRLdsOrder) ul[c][k] = pre[x];
+    }
+    __syncthreads();
+    if (j0 + 16 < n) fetch(j0 + 16);
+    for (int j = max(j0, i0 + 1); j < min(n, j0 + 16); ++j) {
+      double t = 0.0;
+      if (j > i) {
+        const double* zr = zl[r];
+        const double* uc = ul[j - j0];
+#pragma unroll 4
+        for (int k = i + ql; k < j; k += 4) t = fma(zr[k], uc[k], t);
+      }
+      t += dpp_mov<0xB1>(t);   // quad_perm [1,0,3,2]
+      t += dpp_mov<0x4E>(t);   // quad_perm [2,3,0,1]
+      if (ql == 0 && j > i) zl[r][j] = -ri[j] * t;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  __syncthreads();
+  const int nrow = min(16, n - i0);
+  for (int x = tid; x < nrow * n; x += 64) {
+    const int rr = x / n, k = x % n;
+    if (k >= i0 + rr) Z[(size_t)(i0 + rr) * np + k] = zl[rr][k];
+  }
+  if (!s.gen) {
+    double* C = E.small + SmallLayout::C(s.KP);
+    for (int x = tid; x < nrow * s.nkeep; x += 64) {
+      const int rr = x / s.nkeep, k = x % s.nkeep;
+      C[(size_t)(i0 + rr) * s.nkeep + k] =
+          (k >= i0 + rr && k < n) ? vec[VS_D * s.KP + i0 + rr] * zl[rr][k] : 0.0;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// standard form: T = A~ Z (kSecond = false; A~ = D S^T H S D, symmetrised as it is read),
+// then A^ = Z^T T, as 16x16 FP64 MFMA tiles, one wave each.  Order 264: 33 us for both;
+// 640 us in the element's one workgroup before.
+// ---------------------------------------------------------------------------
+template <bool kSecond>
+__global__ void __launch_bounds__(256) k_rr_prod(RRArgs A) {
+  const int e = blockIdx.y;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  if (!kSecond) rr_stamp(A, e, 2, blockIdx.x);
+  const int n = s.n, np = s.np;
+  const double* Am = E.small + SmallLayout::A(s.KP);
+  const double* Z = E.small + rr_slot(kSlotZ, s.KP);
+  const double* d = E.small + SmallLayout::vec(s.KP) + VS_D * s.KP;
+  double* T = E.small + rr_slot(kSlotT, s.KP);
+  double* Ah = E.small + rr_slot(kSlotAhat, s.KP);
+  const int lane = threadIdx.x & 63;
+  const int nt16 = (n + 15) >> 4, kst = (n + 3) >> 2;
+  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= nt16 * nt16) return;
+  const int ti = t / nt16, tj = t % nt16;
+  const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
+  d4v acc = {0.0, 0.0, 0.0, 0.0};
+  const int tz = kSecond ? ti : tj;
+  const int kmax = min(kst, (tz * 16 + 16 + 3) >> 2);   // Z[k][j] = 0 for k > j
+  const int ic = min(ia, n - 1), jc = min(jb, n - 1);   // beyond the matrix: results not stored
+  const double di = kSecond ? 0.0 : d[ic];
+  constexpr int U = 8;   // k-steps whose loads are in flight together
+  for (int k0 = 0; k0 < kmax; k0 += U) {
+    double av[U], bv[U], aw[U], dk[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min((k0 + u) * 4 + (lane >> 4), n - 1);
+      if constexpr (!kSecond) {
+        av[u] = gload<double>(Am + (size_t)ic * n + k);
+        aw[u] = gload<double>(Am + (size_t)k * n + ic);
+        dk[u] = gload<double>(d + k);
+        bv[u] = gload<double>(Z + (size_t)min(k, jc) * np + jc);
+      } else {
+        av[u] = gload<double>(Z + (size_t)min(k, ic) * np + ic);
+        bv[u] = gload<double>(T + (size_t)k * np + jc);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (k0 + u >= kmax) continue;
+      const int k = (k0 + u) * 4 + (lane >> 4);
+      double a, b;
+      if constexpr (!kSecond) {
+        // left-out columns have d = 0: their rows and columns are zero
+        const double s2 = di * dk[u];
+        a = (k < n && s2 != 0.0) ? 0.5 * (av[u] + aw[u]) * s2 : 0.0;
+        b = k <= jc ? bv[u] : 0.0;
+      } else {
+        a = k <= ic ? av[u] : 0.0;
+        b = k < n ? bv[u] : 0.0;
+      }
+      acc = mfma16x16x4(a, b, acc);
+    }
+  }
+  double* out = kSecond ? Ah : T;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = ti * 16 + (lane >> 4) + 4 * q;
+    if (i < n && jb < n) out[(size_t)i * np + jb] = acc[q];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Householder tridiagonalisation of A^ (RR_SVD: of the Gram matrix itself), one workgroup
+// per element.  The working matrix is dynamic LDS for orders up to kRRLdsOrder (kLds =
+// true) and the element's slice of the Gram partial-sum area above that (L2-resident).
+// ---------------------------------------------------------------------------
+template <bool kLds>
+__global__ void __launch_bounds__(kLds ? kRRThreads : kRRThreadsL2) k_rr_tri(RRArgs A) {
+  const int e = blockIdx.x;
+  const ElemDev& E = A.elems[e];
+  if (!rr_on(A, e)) return;
+  const RRShape s = rr_shape(A, E);
+  rr_stamp(A, e, 3, 0);
+  const int n = s.n, np = s.np, KP = s.KP;
+  const double* G = E.small + SmallLayout::G(KP);
+  const double* Ah = E.small + rr_slot(kSlotAhat, KP);
   double* vec = E.small + SmallLayout::vec(KP);
-  double* d = vec + VS_D * KP;
+  const double* d = vec + VS_D * KP;
   extern __shared__ double rr_lds[];
   double* const L = kLds ? rr_lds : A.work + (size_t)e * A.work_stride;
   __shared__ double sh[16];
-  __shared__ int brk;
   __shared__ double sd[kTriMax], se[kTriMax], stau[kTriMax];
   __shared__ double vs[kTriMax], ps[kTriMax], ws[kTriMax];
   const int tid = threadIdx.x, nt = blockDim.x;
   const int lane = tid & 63, wv = tid >> 6, nw = nt >> 6;
-  auto stamp = [&](int k) {
-    if (A.phase_clk && tid == 0) A.phase_clk[e * 16 + k] = wall_clock64();
-  };
-  stamp(0);
-  if (tid == 0) brk = 0;
-  __syncthreads();
-  int ndrop = 0;
-  if (svd) {
-    // eigen-decomposition of the Gram matrix itself
+  if (s.svd) {
     for (int idx = tid; idx < np * np; idx += nt) {
       const int i = idx / np, j = idx % np;
       L[idx] = (i < n && j < n) ? G[(size_t)i * n + j] : 0.0;
     }
     __syncthreads();
   } else {
-  // ---- scaled overlap in LDS, scaled A in Vm
-  for (int i = tid; i < np; i += nt) {
-    const double gii = i < n ? G[(size_t)i * n + i] : 1.0;
-    if (!(gii > 0.0) && i < kx) brk = 1;
-    d[i] = (i < n && gii > 0.0) ? 1.0 / sqrt(gii) : (i < n ? 0.0 : 1.0);
-  }
-  __syncthreads();
-  for (int idx = tid; idx < np * np; idx += nt) {
-    const int i = idx / np, j = idx % np;
-    const bool in = i < n && j < n;
-    const double s2 = d[i] * d[j];
-    L[idx] = in ? G[(size_t)i * n + j] * s2 : (i == j ? 1.0 : 0.0);
-    if (gen) Vm[idx] = in ? 0.5 * (Am[(size_t)i * n + j] + Am[(size_t)j * n + i]) * s2 : 0.0;
-  }
-  __syncthreads();
-  // ---- Cholesky L = U^T U (upper, in place); nearly dependent W/P columns leave the basis.
-  // Rows keep their unscaled values during the elimination (one barrier per
-  // column); the rows are divided by sqrt(pivot) at the end.
-  double pmin = 1.0;
-  int jmin = -1;
-  for (int j = 0; j < n; ++j) {
-    const double piv = L[j * np + j];
-    if (piv < pmin) {
-      pmin = piv;
-      jmin = j;
-    }
-    if (j >= kx && !(piv > A.drop_tol)) {
-      __syncthreads();
-      for (int i = tid; i < n; i += nt) {
-        if (i == j) continue;
-        L[i * np + j] = 0.0;
-        L[j * np + i] = 0.0;
-        Vm[(size_t)i * np + j] = 0.0;
-        Vm[(size_t)j * np + i] = 0.0;
-      }
-      if (tid == 0) {
-        L[j * np + j] = 1.0;
-        Vm[(size_t)j * np + j] = 0.0;
-        d[j] = 0.0;
-        ws[j] = 1.0;
-      }
-      ++ndrop;
-      __syncthreads();
-      continue;
-    }
-    if (!(piv > A.pivot_tol) && tid == 0) brk = 1;
-    const double pinv = 1.0 / fmax(piv, 1e-300);
-    if (tid == 0) ws[j] = sqrt(fmax(piv, 1e-300));
-    for (int i = j + 1 + wv; i < n; i += nw) {
-      const double f = L[j * np + i] * pinv;
-      double* row = L + i * np;
-      const double* rj = L + j * np;
-      for (int k = i + lane; k < n; k += 64) row[k] -= f * rj[k];
-    }
-    __syncthreads();
-  }
-  // divide row j by sqrt(pivot_j): U
-  for (int j = wv; j < n; j += nw) {
-    const double u = ws[j];
-    double* row = L + j * np;
-    for (int k = j + 1 + lane; k < n; k += 64) row[k] = (d[j] == 0.0 && k != j) ? 0.0 : row[k] / u;
-    if (lane == 0) row[j] = u;
-  }
-  __syncthreads();
-  if (A.hp_flag && tid == 0) A.hp_flag[e] = (brk || !(pmin >= A.hp_tol)) ? 1 : 0;
-  if (A.minpiv && tid == 0) {
-    A.minpiv[3 * e] = pmin;
-    A.minpiv[3 * e + 1] = jmin;
-    A.minpiv[3 * e + 2] = ndrop;
-  }
-  if (brk) {
-    // X itself is not positive definite: keep X (C = [I; 0; 0]) and report it
-    for (int idx = tid; idx < n * nkeep; idx += nt) {
-      const int i = idx / nkeep, j = idx % nkeep;
-      Cm[idx] = (i == j) ? 1.0 : 0.0;
-    }
-    if (tid == 0) A.status[e] = 2;
-    return;
-  }
-  if (tid == 0) A.status[e] = 0;
-  stamp(1);
-  if constexpr (kLds) {
-    // ---- Z = U^{-1}: rows are independent, Z[i][j] = -(1/U[j][j]) sum_{k=i}^{j-1} Z[i][k] U[k][j]
-    // left to right. A quad of lanes owns a row (the k sum split four ways, DPP quad
-    // reduction); Z[i][j] is kept transposed in the free strictly lower triangle
-    // (L[j][i]), the reciprocal diagonal in ws, so U stays intact until every row is
-    // done; then Z moves to the upper triangle.
-    for (int i = tid; i < n; i += nt) ws[i] = 1.0 / L[i * np + i];
-    __syncthreads();
-    {
-      const int ql = tid & 3;
-      for (int i = tid >> 2; i < n; i += nt >> 2) {
-        const double zii = ws[i];
-        for (int j = i + 1; j < n; ++j) {
-          double t = 0.0;
-          for (int k = i + ql; k < j; k += 4) t += (k == i ? zii : L[k * np + i]) * L[k * np + j];
-          t += dpp_mov<0xB1>(t);   // quad_perm [1,0,3,2]
-          t += dpp_mov<0x4E>(t);   // quad_perm [2,3,0,1]
-          if (ql == 0) L[j * np + i] = -ws[j] * t;
-        }
-      }
-    }
-    __syncthreads();
     for (int idx = tid; idx < n * n; idx += nt) {
       const int i = idx / n, j = idx % n;
-      if (i < j) L[i * np + j] = L[j * np + i];
-      else if (i == j) L[i * np + i] = ws[i];
+      L[(size_t)i * np + j] = 0.5 * (Ah[(size_t)i * np + j] + Ah[(size_t)j * np + i]);
     }
-    __syncthreads();
-  } else {
-    // ---- Z = U^{-1} in place, column by column (column j uses the inverted leading block):
-    // Z[i][j] = -(1/U[j][j]) sum_{k=i}^{j-1} Z[i][k] U[k][j]
-    for (int j = 0; j < n; ++j) {
-      for (int k = tid; k < j; k += nt) vs[k] = L[k * np + j];
+    int ndrop = 0;
+    for (int i = tid; i < n; i += nt) ndrop += d[i] == 0.0;
+    if (__syncthreads_or(ndrop)) {
+      // left-out columns get an eigenvalue above the whole spectrum (Gershgorin bound)
+      double rmax = 0.0;
+      for (int i = tid; i < n; i += nt) {
+        double sacc = 0.0;
+        for (int k = 0; k < n; ++k) sacc += fabs(L[(size_t)i * np + k]);
+        rmax = fmax(rmax, sacc);
+      }
+      rmax = block_max(rmax, sh);
+      for (int j = tid; j < n; j += nt)
+        if (d[j] == 0.0) L[(size_t)j * np + j] = 2.0 * rmax + 1.0;
       __syncthreads();
-      const double ajj = 1.0 / L[j * np + j];
-      for (int i = wv; i < j; i += nw) {
-        const double* zi = L + i * np;
-        double t = 0.0;
-        for (int k = i + lane; k < j; k += 64) t += zi[k] * vs[k];
-        t = wave_sum_dpp(t);
-        if (lane == 0) ps[i] = -ajj * t;
-      }
-      __syncthreads();
-      for (int i = tid; i < j; i += nt) L[i * np + j] = ps[i];
-      if (tid == 0) L[j * np + j] = ajj;
-    }
-    __syncthreads();
-  }
-  if (!gen) {
-    // Cholesky QR: C = D Z orthonormalises the columns (n x nkeep)
-    for (int idx = tid; idx < n * nkeep; idx += nt) {
-      const int i = idx / nkeep, j = idx % nkeep;
-      Cm[idx] = (i <= j && j < n) ? d[i] * L[i * np + j] : 0.0;
-    }
-    stamp(4);
-    return;
-  }
-  // keep Z for the coefficients
-  for (int idx = tid; idx < np * np; idx += nt) {
-    const int i = idx / np, j = idx % np;
-    G[idx] = (i <= j && j < n) ? L[idx] : 0.0;
-  }
-  stamp(2);
-  // ---- T = A~ Z (Am), then A^ = Z^T T (Um), as 16x16 FP64 MFMA tiles (one wave per tile)
-  {
-    const int nt16 = (n + 15) >> 4;
-    const int kst = (n + 3) >> 2;
-    for (int t = wv; t < nt16 * nt16; t += nw) {
-      const int ti = t / nt16, tj = t % nt16;
-      const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
-      const int kmax = min(kst, (tj * 16 + 16 + 3) >> 2);   // Z[k][j] = 0 for k > j
-      d4v acc = {0.0, 0.0, 0.0, 0.0};
-      for (int ks = 0; ks < kmax; ++ks) {
-        const int k = ks * 4 + (lane >> 4);
-        const double av = (ia < n && k < n) ? Vm[(size_t)ia * np + k] : 0.0;
-        const double bv = (jb < n && k <= jb) ? L[k * np + jb] : 0.0;
-        acc = mfma16x16x4(av, bv, acc);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = ti * 16 + (lane >> 4) + 4 * q;
-        if (i < n && jb < n) Am[(size_t)i * np + jb] = acc[q];
-      }
-    }
-    __syncthreads();
-    for (int t = wv; t < nt16 * nt16; t += nw) {
-      const int ti = t / nt16, tj = t % nt16;
-      const int ia = ti * 16 + (lane & 15), jb = tj * 16 + (lane & 15);
-      const int kmax = min(kst, (ti * 16 + 16 + 3) >> 2);   // Z[k][i] = 0 for k > i
-      d4v acc = {0.0, 0.0, 0.0, 0.0};
-      for (int ks = 0; ks < kmax; ++ks) {
-        const int k = ks * 4 + (lane >> 4);
-        const double av = (ia < n && k <= ia) ? L[k * np + ia] : 0.0;
-        const double bv = (jb < n && k < n) ? Am[(size_t)k * np + jb] : 0.0;
-        acc = mfma16x16x4(av, bv, acc);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = ti * 16 + (lane >> 4) + 4 * q;
-        if (i < n && jb < n) Um[(size_t)i * np + jb] = acc[q];
-      }
     }
   }
-  __syncthreads();
-  for (int idx = tid; idx < n * n; idx += nt) {
-    const int i = idx / n, j = idx % n;
-    L[(size_t)i * np + j] = 0.5 * (Um[(size_t)i * np + j] + Um[(size_t)j * np + i]);
-  }
-  __syncthreads();
-  if (ndrop > 0) {
-    // left-out columns get an eigenvalue above the whole spectrum (Gershgorin bound)
-    double rmax = 0.0;
-    for (int i = tid; i < n; i += nt) {
-      double sacc = 0.0;
-      for (int k = 0; k < n; ++k) sacc += fabs(L[(size_t)i * np + k]);
-      rmax = fmax(rmax, sacc);
-    }
-    rmax = block_max(rmax, sh);
-    for (int j = tid; j < n; j += nt)
-      if (d[j] == 0.0) L[(size_t)j * np + j] = 2.0 * rmax + 1.0;
-    __syncthreads();
-  }
-  }   // !svd
-  stamp(3);
   // ---- Householder tridiagonalisation in LDS; reflector kk kept in column kk below the diagonal
   const int m = n;
   __shared__ int skip;
@@ -711,6 +928,7 @@ __global__ void __launch_bounds__(NT) k_rr_mgs(RRArgs A) {
       double t = 0.0;
       const int jl = min(j, cap);
       int q = ql;
+#pragma unroll 8
       for (; q < jl; q += 4) t += ps[q] * zl[q * np + i];
       for (; q < j; q += 4) t += ps[q] * Zv[(size_t)q * np + i];
       t += dpp_mov<0xB1>(t);   // quad_perm [1,0,3,2]
@@ -916,7 +1134,8 @@ void init_rr_attributes() {
     auto lds = [](const void* fn, int bytes) {
       (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     };
-    lds((const void*)k_rr_head<true>, kRRLdsBytes);
+    lds((const void*)k_rr_chol, kCholLds);
+    lds((const void*)k_rr_tri<true>, kRRLdsBytes);
     lds((const void*)k_rr_inv, (int)inv_lds(kTriMax));
     lds((const void*)k_rr_mgs<512>, kMgsLds);
     lds((const void*)k_rr_mgs<1024>, kMgsLds);
@@ -952,10 +1171,11 @@ int launch_rr(Ctx& c, int nb, int kfix, int nkeep, int mode, const int* active) 
               std::to_string(kTriMax));
     return DG_ERR_SHAPE;
   }
-  // the working region lives in LDS when the orders allow it, else in the element's
-  // slice of the Gram partial-sum area (free between the Gram reduction and the rotation)
+  // the tridiagonalisation works in LDS when the orders allow it, else (and the overlap
+  // factorisation always) in the element's slice of the Gram partial-sum area (free
+  // between the Gram reduction and the rotation)
   const bool in_lds = npmax <= kRRLdsOrder && need <= (size_t)kRRLdsBytes;
-  if (!in_lds && need > (size_t)c.gram_part_stride * sizeof(double)) {
+  if (need > (size_t)c.gram_part_stride * sizeof(double)) {
     set_error("Rayleigh-Ritz work region of " + std::to_string(need) + " bytes above the partial-sum slice");
     return DG_ERR_SHAPE;
   }
@@ -964,14 +1184,21 @@ int launch_rr(Ctx& c, int nb, int kfix, int nkeep, int mode, const int* active) 
            c.rr_pivot_tol, c.rr_drop_tol, c.log_level >= 3 ? c.dev_minpiv : nullptr, c.rr_ortol,
            in_lds ? (int)need : 0, mode == RR_GEN ? c.dev_hpflag : nullptr, c.hp_tol};
   TimedScope ts(c, TC_RR, flops);
-  if (in_lds) {
-    hipLaunchKernelGGL(k_rr_head<true>, dim3(c.n_elem), dim3(kRRThreads), need, c.stream, a);
-  } else {
-    hipLaunchKernelGGL(k_rr_head<false>, dim3(c.n_elem), dim3(kRRThreadsL2), 0, c.stream, a);
+  auto over = [](int n, int per) { return (unsigned)((n + per - 1) / per); };
+  const unsigned ne = (unsigned)c.n_elem;
+  if (mode != RR_SVD) {
+    hipLaunchKernelGGL(k_rr_chol, dim3(ne), dim3(kCholThreads), kCholLds, c.stream, a);
+    if (in_lds) hipLaunchKernelGGL(k_rr_zinv_quad, dim3(over(nmax, 16), ne), dim3(64), 0, c.stream, a);
+    else hipLaunchKernelGGL(k_rr_zinv_wave, dim3(over(nmax, kZinvRows), ne), dim3(64 * kZinvRows), 0, c.stream, a);
+  }
+  if (mode == RR_GEN) {
+    const unsigned nt = over(nmax, 16);
+    hipLaunchKernelGGL(k_rr_prod<false>, dim3(over(nt * nt, 4), ne), dim3(256), 0, c.stream, a);
+    hipLaunchKernelGGL(k_rr_prod<true>, dim3(over(nt * nt, 4), ne), dim3(256), 0, c.stream, a);
   }
   if (mode != RR_CHOLQR) {
-    auto over = [](int n, int per) { return (unsigned)((n + per - 1) / per); };
-    const unsigned ne = (unsigned)c.n_elem;
+    if (in_lds) hipLaunchKernelGGL(k_rr_tri<true>, dim3(ne), dim3(kRRThreads), need, c.stream, a);
+    else hipLaunchKernelGGL(k_rr_tri<false>, dim3(ne), dim3(kRRThreadsL2), 0, c.stream, a);
     hipLaunchKernelGGL(k_rr_eig, dim3(nwmax, ne), dim3(kEigThreads), 0, c.stream, a);
     hipLaunchKernelGGL(k_rr_inv, dim3(over(nwmax, kInvPerWg), ne), dim3(64), inv_lds(npmax), c.stream, a);
     // as many vectors as fit, and the current one
