@@ -38,6 +38,9 @@ __device__ __forceinline__ double2 gload2(const void* p) {
   const gd2 v = *(const __attribute__((address_space(1))) gd2*)(p);
   return double2{v.x, v.y};
 }
+// FP64 store through a global-address-space pointer (a flat store would make later LDS
+// waits wait for its completion)
+__device__ __forceinline__ void gstore(double* p, double v) { *(__attribute__((address_space(1))) double*)(p) = v; }
 typedef float gf2 __attribute__((ext_vector_type(2)));
 typedef float gf4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float2 gload2f(const void* p) {
@@ -93,6 +96,14 @@ __device__ inline double block_max(double v, double* sh) {
   for (int i = 1; i < nw; ++i) s = fmax(s, sh[i]);
   __syncthreads();
   return s;
+}
+
+// Workgroup barrier that orders LDS only: __syncthreads() also waits for every global
+// store in flight (about a microsecond), which a step that only hands on LDS need not.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 }  // namespace dg

@@ -58,14 +58,14 @@ constexpr int kRRLdsOrder = 132;                  // np * np doubles fit in kRRL
 
 // where the steps leave their matrices (leading dimension np); the inputs are S^T S in
 // slot G and S^T H S in slot A (leading dimension n), the result C is in slot C
-enum RRSlot { kSlotUt, kSlotZ, kSlotT, kSlotAhat, kSlotRefl, kSlotVec };
+enum RRSlot { kSlotUt, kSlotZ, kSlotT, kSlotAhat, kSlotAhatT, kSlotRefl, kSlotVec };
 __device__ __forceinline__ long long rr_slot(RRSlot w, int KP) {
   switch (w) {
     case kSlotZ: return SmallLayout::G(KP);      // S^T S is done with once it is factored
     case kSlotT: return SmallLayout::V(KP);
     case kSlotAhat:                              // S^T H S is done with once T is formed
     case kSlotRefl: return SmallLayout::A(KP);   // A^ is read before the reflectors are written
-    default: return SmallLayout::U(KP);          // U^T until Z is formed, then the eigenvectors
+    default: return SmallLayout::U(KP);          // U^T until Z is formed, (A^)^T, then the eigenvectors
   }
 }
 
@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(kCholThreads) k_rr_chol(RRArgs A) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           Pf[r * kCholPitch + k] = r < nr ? t[r] : 0.0;
-          if (r < nr) Ut[(size_t)k * np + j0 + r] = t[r];
+          if (r < nr) gstore(Ut + (size_t)k * np + j0 + r, t[r]);
         }
       }
       if (wv == 0 && lane < nr) {
@@ -227,12 +227,12 @@ __global__ void __launch_bounds__(kCholThreads) k_rr_chol(RRArgs A) {
         for (int r = 0; r < 16; ++r)
           if (r <= l16 && r < nr) {
             const bool on = !((dropped >> r) & 1);
-            if (r < l16) Ut[(size_t)(j0 + l16) * np + j0 + r] = on ? c[r] : 0.0;
+            if (r < l16) gstore(Ut + (size_t)(j0 + l16) * np + j0 + r, on ? c[r] : 0.0);
             else sdiag[j0 + r] = on ? fmax(c[r], 1e-300) : -1.0;   // -1: left out
           }
       }
     }
-    __syncthreads();
+    lds_barrier();
     // trailing update, upper tiles; the first tile row is the next panel
     const int b0 = j0 + 16, nb = (n - b0 + 15) >> 4;
     for (int tl = wv; b0 < n && tl < nb * (nb + 1) / 2; tl += nw) {
@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(kCholThreads) k_rr_chol(RRArgs A) {
         const int i = i0 + kl + 4 * q;
         if (i >= n || kc >= n) continue;
         if (ti == 0) P[(kl + 4 * q) * kCholPitch + kc] = acc[q];
-        else W[(size_t)i * np + kc] = acc[q];
+        else gstore(W + (size_t)i * np + kc, acc[q]);
       }
     }
   }
@@ -467,6 +467,7 @@ __global__ void __launch_bounds__(256) k_rr_prod(RRArgs A) {
   const double* d = E.small + SmallLayout::vec(s.KP) + VS_D * s.KP;
   double* T = E.small + rr_slot(kSlotT, s.KP);
   double* Ah = E.small + rr_slot(kSlotAhat, s.KP);
+  double* AhT = E.small + rr_slot(kSlotAhatT, s.KP);
   const int lane = threadIdx.x & 63;
   const int nt16 = (n + 15) >> 4, kst = (n + 3) >> 2;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -515,15 +516,151 @@ __global__ void __launch_bounds__(256) k_rr_prod(RRArgs A) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int i = ti * 16 + (lane >> 4) + 4 * q;
-    if (i < n && jb < n) out[(size_t)i * np + jb] = acc[q];
+    if (i < n && jb < n) {
+      out[(size_t)i * np + jb] = acc[q];
+      if (kSecond) AhT[(size_t)jb * np + i] = acc[q];   // for the symmetrisation
+    }
   }
 }
 
 // ---------------------------------------------------------------------------
 // Householder tridiagonalisation of A^ (RR_SVD: of the Gram matrix itself), one workgroup
-// per element.  The working matrix is dynamic LDS for orders up to kRRLdsOrder (kLds =
-// true) and the element's slice of the Gram partial-sum area above that (L2-resident).
+// per element.
+//
+// Per step: the rank-2 update of the step before, the product with the new reflector, and
+// a serial part on one wave that forms w from the product and, ahead of the update, the
+// next column and reflector.  In LDS (odd pitch) the update spreads rows over the waves
+// and the product columns and NS row ranges over the threads (a chain each); while the
+// trailing matrix is too large for LDS it is in L2 and one pass does both, so that an
+// entry is read and written once per step.  The steps in LDS hand on through barriers
+// that order LDS only: __syncthreads() would wait for the reflector's global stores.
+// Bound by the latency of a step (L2 accesses while in L2, then the serial part).  Order
+// 264: 2270 us, 3430 us with two passes and four barriers a step on the L2-resident matrix
+// before; order 132, in LDS: 371 us, 507 us before; order 36: 57 us, 59 us.
 // ---------------------------------------------------------------------------
+// t = v_i w_j + w_i v_j of row i and column j.  Which product is rounded first differs
+// between the two size classes and is fixed, so that results do not hang on the
+// compiler's choice.
+template <bool kLds>
+__device__ __forceinline__ double tri_t(double vi, double wi, double vj, double wj) {
+  return kLds ? fma(vi, wj, wi * vj) : fma(wi, vj, vi * wj);
+}
+
+constexpr int kTriPitch = 133;                                            // LDS pitch (odd)
+constexpr int kTriLdsRows = kRRLdsBytes / (kTriPitch * (int)sizeof(double));   // 133
+static_assert(kRRLdsOrder < kTriPitch && kTriLdsRows >= kTriPitch, "LDS matrix of the tridiagonalisation");
+
+// In LDS: M -= v w^T + w v^T, rows over the waves (NW of them), lanes over columns.
+template <bool kLds, int NW>
+__device__ __forceinline__ void tri_update(double* M, int mr, const double* v, const double* w) {
+  constexpr int NC = (kTriPitch + 63) / 64;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double vj[NC], wj[NC];
+  int c[NC];   // columns past the end repeat the last one: the same value is stored again
+#pragma unroll
+  for (int u = 0; u < NC; ++u) {
+    c[u] = min(lane + 64 * u, mr - 1);
+    vj[u] = v[c[u]];
+    wj[u] = w[c[u]];
+  }
+  for (int j = wv; j < mr; j += NW) {
+    const double vi = v[j], wi = w[j];
+    double* row = M + j * kTriPitch;
+#pragma unroll
+    for (int u = 0; u < NC; ++u)
+      if (64 * u < mr) row[c[u]] -= tri_t<kLds>(vi, wi, vj[u], wj[u]);
+  }
+}
+
+// In LDS: pq[q][i] = sum over row range q of M[j][i] v[j], a chain per thread.
+template <int NS>
+__device__ __forceinline__ void tri_product(const double* M, int mr, const double* v, double (*pq)[kTriMax]) {
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int qn = (mr + NS - 1) / NS;
+  const int j0 = q * qn, j1 = min(mr, j0 + qn);
+  const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x & 192);
+  if (w0 >= mr) return;   // mr <= 256: a wave has at most one range of columns
+  const int i = min(w0 + (int)(threadIdx.x & 63), mr - 1);
+  double acc = 0.0;
+  constexpr int B = 8;
+  int j = j0;
+  for (; j + B <= j1; j += B) {
+    double m[B], x[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      m[u] = M[(j + u) * kTriPitch + i];
+      x[u] = v[j + u];
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) acc = fma(m[u], x[u], acc);
+  }
+  for (; j < j1; ++j) acc = fma(M[j * kTriPitch + i], v[j], acc);
+  pq[q][i] = acc;
+}
+
+// From L2: the update and the product in one pass over the mr x mr matrix at src (pitch
+// sp), into dst (in place, or into LDS).  A thread owns a column and one of NS row
+// ranges; the row's values of v, w and the new reflector come by lane reads.
+// col: the updated first column.
+template <bool kLds, int NS, bool kToLds>
+__device__ __forceinline__ void tri_pass(const double* src, int sp, double* dst, int mr, const double* vo,
+                                         const double* wo, const double* vn, double* col, double (*pq)[kTriMax]) {
+  constexpr int B = 8;   // rows in flight
+  const int lane = threadIdx.x & 63;
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x & 192);
+  const int qn = (mr + NS - 1) / NS;
+  const int j0 = q * qn, j1 = min(mr, j0 + qn);
+  const int dp = kToLds ? kTriPitch : sp;
+  // this range's row values, 64 rows a register
+  double rv[2], rw[2], rn[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int j = min(j0 + lane + 64 * h, mr - 1);
+    rv[h] = vo[j];
+    rw[h] = wo[j];
+    rn[h] = vn[j];
+  }
+  for (int i0 = w0; i0 < mr; i0 += 256) {
+    // whole waves, so that every lane is there for the lane reads; lanes past the last
+    // column repeat it (and store the same values again)
+    const int i = min(i0 + lane, mr - 1);
+    const double vj = vo[i], wj = wo[i];
+    double acc = 0.0;
+    auto rows = [&](int jb, int je, double av, double aw, double an) {
+      auto one = [&](double x, int j) {
+        const int l = (j - j0) & 63;
+        const double b = x - tri_t<kLds>(lane_read(av, l), lane_read(aw, l), vj, wj);
+        acc = fma(b, lane_read(an, l), acc);
+        if (kToLds) dst[j * dp + i] = b;
+        else gstore(dst + (size_t)j * dp + i, b);
+        if (!kToLds && i0 == 0 && lane == 0) col[j] = b;
+      };
+      int j = jb;
+      double nx[B];
+      if (j + B <= je) {
+#pragma unroll
+        for (int u = 0; u < B; ++u) nx[u] = gload<double>(src + (size_t)(j + u) * sp + i);
+      }
+      for (; j + B <= je; j += B) {
+        double cu[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) cu[u] = nx[u];
+        if (j + 2 * B <= je) {
+#pragma unroll
+          for (int u = 0; u < B; ++u) nx[u] = gload<double>(src + (size_t)(j + B + u) * sp + i);
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) one(cu[u], j + u);
+      }
+      for (; j < je; ++j) one(gload<double>(src + (size_t)j * sp + i), j);
+    };
+    rows(j0, min(j1, j0 + 64), rv[0], rw[0], rn[0]);
+    if (j0 + 64 < j1) rows(j0 + 64, j1, rv[1], rw[1], rn[1]);
+    pq[q][i] = acc;
+  }
+}
+
 template <bool kLds>
 __global__ void __launch_bounds__(kLds ? kRRThreads : kRRThreadsL2) k_rr_tri(RRArgs A) {
   const int e = blockIdx.x;
@@ -531,149 +668,171 @@ __global__ void __launch_bounds__(kLds ? kRRThreads : kRRThreadsL2) k_rr_tri(RRA
   if (!rr_on(A, e)) return;
   const RRShape s = rr_shape(A, E);
   rr_stamp(A, e, 3, 0);
-  const int n = s.n, np = s.np, KP = s.KP;
-  const double* G = E.small + SmallLayout::G(KP);
-  const double* Ah = E.small + rr_slot(kSlotAhat, KP);
+  const int m = s.n, np = s.np, KP = s.KP;
   double* vec = E.small + SmallLayout::vec(KP);
   const double* d = vec + VS_D * KP;
-  extern __shared__ double rr_lds[];
-  double* const L = kLds ? rr_lds : A.work + (size_t)e * A.work_stride;
+  double* gd = vec + VS_T0 * KP;
+  double* ge = vec + VS_T1 * KP;
+  double* gtau = vec + VS_T2 * KP;
+  double* Rf = E.small + rr_slot(kSlotRefl, KP);
+  constexpr int NT = kLds ? kRRThreads : kRRThreadsL2;
+  constexpr int NS = NT / 256;
+  constexpr int NR = ((kLds ? kRRLdsOrder : kTriMax) + 63) / 64;   // rows per lane of wave 0
+  extern __shared__ double lm[];
+  __shared__ double vb[2][kTriMax], ws[kTriMax], col[kTriMax], pq[NS][kTriMax];
   __shared__ double sh[16];
-  __shared__ double sd[kTriMax], se[kTriMax], stau[kTriMax];
-  __shared__ double vs[kTriMax], ps[kTriMax], ws[kTriMax];
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int lane = tid & 63, wv = tid >> 6, nw = nt >> 6;
-  if (s.svd) {
-    for (int idx = tid; idx < np * np; idx += nt) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the matrix: in LDS from the start, or in L2 until the trailing part fits
+  double* const gm = A.work + (size_t)e * A.work_stride;
+  bool in_lds = kLds;
+  int base = 0;   // LDS: row and column of the first entry
+  {
+    const double* G = E.small + SmallLayout::G(KP);
+    const double* Ah = E.small + rr_slot(kSlotAhat, KP);
+    const double* AhT = E.small + rr_slot(kSlotAhatT, KP);
+    double* M = kLds ? lm : gm;
+    const int mp = kLds ? kTriPitch : np;
+    for (int idx = tid; idx < m * np; idx += NT) {
       const int i = idx / np, j = idx % np;
-      L[idx] = (i < n && j < n) ? G[(size_t)i * n + j] : 0.0;
+      if (j >= m) continue;
+      M[(size_t)i * mp + j] = s.svd ? G[(size_t)i * m + j] : 0.5 * (Ah[idx] + AhT[idx]);
     }
-    __syncthreads();
-  } else {
-    for (int idx = tid; idx < n * n; idx += nt) {
-      const int i = idx / n, j = idx % n;
-      L[(size_t)i * np + j] = 0.5 * (Ah[(size_t)i * np + j] + Ah[(size_t)j * np + i]);
-    }
-    int ndrop = 0;
-    for (int i = tid; i < n; i += nt) ndrop += d[i] == 0.0;
-    if (__syncthreads_or(ndrop)) {
-      // left-out columns get an eigenvalue above the whole spectrum (Gershgorin bound)
+    for (int i = tid; i < kTriMax; i += NT) vb[0][i] = ws[i] = 0.0;
+    int left = 0;
+    if (!s.svd)
+      for (int i = tid; i < m; i += NT) left |= d[i] == 0.0;
+    if (__syncthreads_or(left)) {
+      // left-out columns get an eigenvalue above the whole spectrum (Gershgorin bound;
+      // the matrix is symmetric, so a row's sum is read down its column)
       double rmax = 0.0;
-      for (int i = tid; i < n; i += nt) {
+      for (int i = tid; i < m; i += NT) {
         double sacc = 0.0;
-        for (int k = 0; k < n; ++k) sacc += fabs(L[(size_t)i * np + k]);
+        for (int k = 0; k < m; ++k) sacc += fabs(M[(size_t)k * mp + i]);
         rmax = fmax(rmax, sacc);
       }
       rmax = block_max(rmax, sh);
-      for (int j = tid; j < n; j += nt)
-        if (d[j] == 0.0) L[(size_t)j * np + j] = 2.0 * rmax + 1.0;
+      for (int j = tid; j < m; j += NT)
+        if (d[j] == 0.0) M[(size_t)j * mp + j] = 2.0 * rmax + 1.0;
       __syncthreads();
     }
+    if (!kLds)
+      for (int i = tid; i < m; i += NT) col[i] = M[(size_t)i * mp];
+    __syncthreads();
   }
-  // ---- Householder tridiagonalisation in LDS; reflector kk kept in column kk below the diagonal
-  const int m = n;
-  __shared__ int skip;
-  // the product p = tau A v splits the rows between sets of 256 threads
-  constexpr int kSets = (kLds ? kRRThreads : kRRThreadsL2) / 256;
-  __shared__ double pq[kSets][kTriMax];
+  int cur = 0;   // buffer of the last reflector
   for (int kk = 0; kk < m - 2; ++kk) {
     const int mr = m - kk - 1;
+    double tau = 0.0;
     if (wv == 0) {
-      // reflector from column kk (one wave)
-      double part = 0.0;
-      for (int i = lane; i < mr; i += 64) {
-        const double x = L[(kk + 1 + i) * np + kk];
-        part += x * x;
+      // column kk after the last update, and the reflector that annihilates it below
+      // row kk + 1: v in vb[cur ^ 1]
+      const double* vo = vb[cur];
+      double* vn = vb[cur ^ 1];
+      auto entry = [&](int r) {
+        const double x = in_lds ? lm[(r - base) * kTriPitch + kk - base] : col[r];
+        return x - tri_t<kLds>(vo[r], ws[r], vo[kk], ws[kk]);
+      };
+      double x[NR], part = 0.0;
+#pragma unroll
+      for (int u = 0; u < NR; ++u) {
+        x[u] = 0.0;
+        if (64 * u < mr) {   // uniform; lanes past the end add zero
+          const int i = lane + 64 * u;
+          const double y = entry(kk + 1 + min(i, mr - 1));
+          x[u] = i < mr ? y : 0.0;
+          part += x[u] * x[u];
+        }
       }
       const double ss = wave_sum_dpp(part);
-      const double x0 = L[(kk + 1) * np + kk];
-      const double alpha = x0 >= 0.0 ? -sqrt(ss) : sqrt(ss);
-      const double vv = ss - x0 * x0 + (x0 - alpha) * (x0 - alpha);
+      const double x0 = lane_read(x[0], 0);
+      const double root = sqrt(ss);
+      const double alpha = x0 >= 0.0 ? -root : root;
+      const double dx = x0 - alpha;
       const bool zero = !(ss > 0.0);
-      for (int i = lane; i < mr; i += 64) vs[i] = (i == 0) ? x0 - alpha : L[(kk + 1 + i) * np + kk];
-      if (lane == 0) {
-        sd[kk] = L[kk * np + kk];
-        stau[kk] = zero ? 0.0 : 2.0 / vv;
-        se[kk] = zero ? 0.0 : alpha;
-        skip = zero ? 1 : 0;
-      }
-    }
-    __syncthreads();
-    if (skip) continue;
-    const double tau = stau[kk];
-    // p = tau A v; A is symmetric, so row i is read as column i (consecutive threads,
-    // consecutive addresses): two threads per row, each over half of the rows
-    {
-      const int q = tid >> 8, qn = (mr + kSets - 1) / kSets;
-      const int j0 = q * qn, j1 = min(mr, j0 + qn);
-      for (int i = tid & 255; i < mr; i += 256) {
-        const double* col = L + (kk + 1) * np + kk + 1 + i;
-        double acc = 0.0;
-        for (int j = j0; j < j1; ++j) acc += col[j * np] * vs[j];
-        pq[q][i] = acc;
-      }
-    }
-    __syncthreads();
-    if (wv == 0) {
-      double kp = 0.0;
-      for (int i = lane; i < mr; i += 64) {
-        double p = 0.0;
+      x[0] = lane == 0 ? dx : x[0];
 #pragma unroll
-        for (int q = 0; q < kSets; ++q) p += pq[q][i];
-        p *= tau;
-        ps[i] = p;
-        kp += vs[i] * p;
-      }
-      const double Kc = 0.5 * tau * wave_sum_dpp(kp);
-      for (int i = lane; i < mr; i += 64) ws[i] = ps[i] - Kc * vs[i];
-    }
-    __syncthreads();
-    {
-      // this lane's entries of v and w stay in registers across the rows
-      constexpr int NQ = ((kLds ? kRRLdsOrder : kTriMax) + 63) / 64;
-      double vj[NQ], wj[NQ];
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int j = lane + 64 * q;
-        vj[q] = j < mr ? vs[j] : 0.0;
-        wj[q] = j < mr ? ws[j] : 0.0;
-      }
-      for (int i = wv; i < mr; i += nw) {
-        double* row = L + (kk + 1 + i) * np + kk + 1;
-        const double vi = vs[i], wi = ws[i];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          const int j = lane + 64 * q;
-          // (which of the two products is rounded first is fixed, so that the result
-          // does not hang on the compiler's choice)
-          const double t = kLds ? fma(vi, wj[q], wi * vj[q]) : fma(wi, vj[q], vi * wj[q]);
-          if (j < mr) row[j] -= t;
+      for (int u = 0; u < NR; ++u)
+        if (64 * u < mr) {
+          if (zero) x[u] = 0.0;
+          if (lane + 64 * u < mr) vn[kk + 1 + lane + 64 * u] = x[u];
         }
-        if (lane == 0) L[(kk + 1 + i) * np + kk] = vi;
+      const double vv = fma(dx, dx, fma(-x0, x0, ss));
+      tau = zero ? 0.0 : 2.0 / vv;
+      const double dk = entry(kk);
+      if (lane == 0) {
+        gstore(gd + kk, dk);
+        gstore(ge + kk, zero ? 0.0 : alpha);
+        gstore(gtau + kk, tau);
+      }
+#pragma unroll
+      for (int u = 0; u < NR; ++u)
+        if (64 * u < mr && lane + 64 * u < mr) gstore(Rf + (size_t)kk * np + kk + 1 + lane + 64 * u, x[u]);
+    }
+    lds_barrier();
+    {
+      const double* vo = vb[cur] + kk + 1;
+      const double* wo = ws + kk + 1;
+      const double* vn = vb[cur ^ 1] + kk + 1;
+      if (in_lds) {
+        double* M = lm + (kk + 1 - base) * kTriPitch + kk + 1 - base;
+        if (kk > 0) tri_update<kLds, NT / 64>(M, mr, vo, wo);
+        lds_barrier();
+        tri_product<NS>(M, mr, vn, pq);
+      } else if constexpr (!kLds) {
+        double* M = gm + (size_t)(kk + 1) * np + kk + 1;
+        if (mr <= kTriLdsRows) {
+          in_lds = true;
+          base = kk + 1;
+          tri_pass<kLds, NS, true>(M, np, lm, mr, vo, wo, vn, nullptr, pq);
+        } else {
+          tri_pass<kLds, NS, false>(M, np, M, mr, vo, wo, vn, col + kk + 1, pq);
+        }
       }
     }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    if (m >= 2) {
-      sd[m - 2] = L[(size_t)(m - 2) * np + m - 2];
-      se[m - 2] = L[(size_t)(m - 1) * np + m - 2];
-      stau[m - 2] = 0.0;
+    // (the matrix moves between threads from pass to pass: in L2 its stores are waited for)
+    if (in_lds) lds_barrier();
+    else __syncthreads();
+    cur ^= 1;
+    if (wv == 0) {
+      // w = tau A v - (tau / 2) (tau v^T A v) v
+      const double* v = vb[cur] + kk + 1;
+      double p[NR], vi[NR], kp = 0.0;
+#pragma unroll
+      for (int u = 0; u < NR; ++u)
+        if (64 * u < mr) {
+          const int i = min(lane + 64 * u, mr - 1);
+          double t = 0.0;
+#pragma unroll
+          for (int q = 0; q < NS; ++q) t += pq[q][i];
+          const double y = v[i];
+          const bool on = lane + 64 * u < mr;
+          p[u] = on ? t * tau : 0.0;
+          vi[u] = on ? y : 0.0;
+          kp += vi[u] * p[u];
+        }
+      const double Kc = 0.5 * tau * wave_sum_dpp(kp);
+#pragma unroll
+      for (int u = 0; u < NR; ++u)
+        if (64 * u < mr && lane + 64 * u < mr)
+          ws[kk + 1 + lane + 64 * u] = tau == 0.0 ? 0.0 : fma(-Kc, vi[u], p[u]);
+      // the next reflector's lanes read rows that other lanes wrote
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    sd[m - 1] = L[(size_t)(m - 1) * np + m - 1];
-    se[m - 1] = 0.0;
   }
-  // T, the reflectors (column kk with zeros in rows <= kk) and tau for the kernels below
-  double* Rf = E.small + rr_slot(kSlotRefl, KP);
   __syncthreads();
-  for (int i = tid; i < m; i += nt) {
-    vec[VS_T0 * KP + i] = sd[i];
-    vec[VS_T1 * KP + i] = se[i];
-    vec[VS_T2 * KP + i] = i < m - 2 ? stau[i] : 0.0;
+  if (tid < 3) {
+    // the last 2 x 2 block: (m-2, m-2), (m-1, m-2), (m-1, m-1)
+    const int r = m - 2 + (tid > 0), c = m - 2 + (tid > 1);
+    if (c >= 0 && r >= 0) {
+      const double x = in_lds ? lm[(r - base) * kTriPitch + c - base] : gm[(size_t)r * np + c];
+      const double y = x - tri_t<kLds>(vb[cur][r], ws[r], vb[cur][c], ws[c]);
+      if (tid == 1) ge[m - 2] = y;
+      else gd[r] = y;
+      if (tid == 0) gtau[m - 2] = 0.0;
+    }
+    if (tid == 2) ge[m - 1] = gtau[m - 1] = 0.0;
   }
-  for (int kk = wv; kk < m - 2; kk += nw)
-    for (int i = lane; i < np; i += 64)
-      Rf[(size_t)kk * np + i] = (i > kk && i < m) ? L[(size_t)i * np + kk] : 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -907,7 +1066,7 @@ __global__ void __launch_bounds__(NT) k_rr_mgs(RRArgs A) {
   for (int j = 1; j < nwant; ++j) {
     // (vector 0 stays as inverse iteration left it)
     for (int i = tid; i < np; i += NT) zj[i] = j < cap ? zl[j * np + i] : Zv[(size_t)j * np + i];
-    __syncthreads();
+    lds_barrier();
     for (int q = wv; q < j; q += nw) {
       double dot = 0.0;
       if (q < cap) {
@@ -920,7 +1079,7 @@ __global__ void __launch_bounds__(NT) k_rr_mgs(RRArgs A) {
       dot = wave_sum_dpp(dot);
       if (lane == 0) ps[q] = dot;
     }
-    __syncthreads();
+    lds_barrier();
     // z_j -= sum_q (z_q . z_j) z_q; per-wave sums of squares for the norm
     const int ql = tid & 3;
     double part = 0.0;
@@ -941,16 +1100,17 @@ __global__ void __launch_bounds__(NT) k_rr_mgs(RRArgs A) {
     }
     part = wave_sum_dpp(part);
     if (lane == 0) sh[wv] = part;
-    __syncthreads();
+    lds_barrier();
     double nn2 = 0.0;
     for (int q = 0; q < nw; ++q) nn2 += sh[q];
     const double nn = 1.0 / sqrt(nn2);
     for (int i = tid; i < m; i += NT) {
       const double v = zj[i] * nn;
       if (j < cap) zl[j * np + i] = v;
-      Zv[(size_t)j * np + i] = v;
+      gstore(Zv + (size_t)j * np + i, v);
     }
-    __syncthreads();
+    if (j < cap) lds_barrier();   // read back from LDS only
+    else __syncthreads();
   }
 }
 
@@ -1136,6 +1296,7 @@ void init_rr_attributes() {
     };
     lds((const void*)k_rr_chol, kCholLds);
     lds((const void*)k_rr_tri<true>, kRRLdsBytes);
+    lds((const void*)k_rr_tri<false>, kRRLdsBytes);
     lds((const void*)k_rr_inv, (int)inv_lds(kTriMax));
     lds((const void*)k_rr_mgs<512>, kMgsLds);
     lds((const void*)k_rr_mgs<1024>, kMgsLds);
@@ -1197,8 +1358,11 @@ int launch_rr(Ctx& c, int nb, int kfix, int nkeep, int mode, const int* active) 
     hipLaunchKernelGGL(k_rr_prod<true>, dim3(over(nt * nt, 4), ne), dim3(256), 0, c.stream, a);
   }
   if (mode != RR_CHOLQR) {
-    if (in_lds) hipLaunchKernelGGL(k_rr_tri<true>, dim3(ne), dim3(kRRThreads), need, c.stream, a);
-    else hipLaunchKernelGGL(k_rr_tri<false>, dim3(ne), dim3(kRRThreadsL2), 0, c.stream, a);
+    if (in_lds) {
+      hipLaunchKernelGGL(k_rr_tri<true>, dim3(ne), dim3(kRRThreads), (size_t)npmax * kTriPitch * sizeof(double), c.stream, a);
+    } else {
+      hipLaunchKernelGGL(k_rr_tri<false>, dim3(ne), dim3(kRRThreadsL2), kRRLdsBytes, c.stream, a);
+    }
     hipLaunchKernelGGL(k_rr_eig, dim3(nwmax, ne), dim3(kEigThreads), 0, c.stream, a);
     hipLaunchKernelGGL(k_rr_inv, dim3(over(nwmax, kInvPerWg), ne), dim3(64), inv_lds(npmax), c.stream, a);
     // as many vectors as fit, and the current one
