@@ -5,10 +5,9 @@
 // element-major) and n_vec columns.  Filter steps, Gram matrices, the Cholesky /
 // projected eigenproblem and the rotations are the element solver's own kernels; two
 // pieces are specific to H^DG:
-//   * k_dg_bsr: Y = H^DG X for a block of columns, one workgroup per (element row k,
-//     16 columns): Y_k = sum over the nonzero blocks (k, k') of H_{k,k'} X_{k'} (Eq.
-//     (8)), X_{k'} staged through LDS, the J_k x J_k' block read from HBM column by
-//     column (coalesced along the rows of the block);
+//   * k_dg_bsr: Y = H^DG X for a block of columns, one workgroup per (element row k, 16
+//     or 32 columns), a wave per 16 x 16 tile: Y_k = sum over the nonzero blocks (k, k')
+//     of H_{k,k'} X_{k'} (Eq. (8)) on FP64 matrix cores, both staged through LDS;
 //   * the upper bound b_up by a k-step Lanczos run (Algorithm 2, step 1): seeded start,
 //     H v by k_dg_bsr, one single-workgroup update kernel per step, and the largest
 //     eigenvalue of the Lanczos tridiagonal (Sturm bisection) plus the last residual
@@ -20,64 +19,170 @@
 #include <string>
 #include <vector>
 
-#include "dg_internal.h"
+#include "dense_ops.h"
 
 namespace dg {
 
 int run_chfsi(Ctx& c, int prec, double tol, int max_iter, int degree, int* iters, int* n_done);
 
-constexpr int kBsrCols = 16;
-constexpr int kBsrThreads = 128;   // >= the largest J_k (88)
+constexpr int kBsrWaves = 8;
+constexpr int kBsrThreads = 64 * kBsrWaves;
+constexpr int kBsrCols = 32;      // columns of X a workgroup stages at most
+constexpr int kBsrChunk = 40;     // block columns staged at a time at most,
+constexpr int kBsrEntries = 2048; // and their entries
 constexpr int kLanczosMax = 64;
 
-// H^DG X for columns [16 y, 16 y + 16) of block in_blk into out_blk
+// H^DG X of block in_blk into out_blk: workgroup (k, y) forms the rows of element k in
+// 16-column tiles y, or 2 y and 2 y + 1 where the rows leave waves for both (J_k <= 64).
+//
+// The operator (some MB) comes from beyond L2 at each product, so what counts is the
+// latency along a row's blocks and the number of load instructions per CU (operand
+// fragments straight from memory: 30 us at any prefetch depth).  A chunk of up to 40 columns of a block is
+// one contiguous range: the workgroup stages it and its rows of X in LDS, with three
+// chunks in flight in registers and one barrier a chunk.  The block list is read 64
+// blocks at a time, one a lane.  An entry's products are summed in the order of the
+// blocks and of their columns.  8x8 elements of 40 functions, 13 blocks a row, 86
+// columns: 24 us; 96 us with a thread per row and two barriers per block before.
 __global__ void __launch_bounds__(kBsrThreads) k_dg_bsr(const ElemDev* elems, DgOp op, int in_blk, int out_blk,
                                                         int ncols, const int* active) {
-  if (active && !active[0]) return;
+  // the loads that the block list hangs on go out together, before any test
   const ElemDev& E = elems[0];
-  const int K = ncols > 0 ? ncols : E.K;
-  const int c0 = blockIdx.y * kBsrCols;
-  if (c0 >= K) return;
   const int k = blockIdx.x;
   const int Jk = op.J[k];
-  const long long r0 = op.roff[k];
-  const double* X = reinterpret_cast<const double*>(E.blk[in_blk]);
-  double* Y = reinterpret_cast<double*>(E.blk[out_blk]);
-  const int i = threadIdx.x;
-  __shared__ double xs[88][kBsrCols + 1];
-  double acc[kBsrCols];
+  const long long b0 = op.row_ptr[k], b1 = op.row_ptr[k + 1], y0 = op.roff[k], ld = E.ld;
+  const double* const X = reinterpret_cast<const double*>(E.blk[in_blk]);
+  double* const Y = reinterpret_cast<double*>(E.blk[out_blk]);
+  const int EK = E.K;
+  const bool run = !active || active[0];
+  const int K = ncols > 0 ? ncols : EK;
+  const int nrt = (Jk + 15) / 16;                 // row tiles, at most 6
+  const int nct = 2 * nrt <= kBsrWaves ? 2 : 1;   // column tiles
+  const int c0 = 16 * nct * blockIdx.y;
+  if (!run || Jk == 0 || c0 >= K) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kq = lane >> 4, l16 = lane & 15;
+  const int ct = w / nrt, r0 = 16 * (w - ct * nrt);
+  const bool on = ct < nct && c0 + 16 * ct < K;
+  constexpr int XP = kBsrChunk + 1;   // odd pitch
+  __shared__ double hs[2][kBsrEntries], xs[2][kBsrCols][XP];
+  // rows past the end repeat the last one and are not stored
+  const int i = min(r0 + l16, Jk - 1);
+  const int chunk = min(kBsrChunk, (kBsrEntries / Jk) & ~3);
+  // staged per thread: entries tid + kBsrThreads u of the chunk, and of X rows xr of
+  // columns xc (columns past the end repeat the last one and are not stored)
+  constexpr int NH = kBsrEntries / kBsrThreads;
+  constexpr int NX = (kBsrCols * kBsrChunk + kBsrThreads - 1) / kBsrThreads;
+  int xr[NX], xc[NX];
+  const double* xcol[NX];
 #pragma unroll
-  for (int c = 0; c < kBsrCols; ++c) acc[c] = 0.0;
-  for (long long b = op.row_ptr[k]; b < op.row_ptr[k + 1]; ++b) {
-    const int nb = op.col_idx[b];
-    const int Jn = op.J[nb];
-    const long long rn = op.roff[nb];
-    const double* Hb = op.H + op.boff[b];
-    __syncthreads();
-    for (int x = threadIdx.x; x < Jn * kBsrCols; x += kBsrThreads) {
-      const int l = x % Jn, c = x / Jn;
-      xs[l][c] = c0 + c < K ? X[rn + l + (long long)(c0 + c) * E.ld] : 0.0;
-    }
-    __syncthreads();
-    if (i < Jk) {
-      for (int l = 0; l < Jn; ++l) {
-        const double h = Hb[i + (long long)l * Jk];
+  for (int u = 0; u < NX; ++u) {
+    const int idx = min(tid + kBsrThreads * u, 16 * nct * kBsrChunk - 1);
+    xr[u] = idx % kBsrChunk;
+    xc[u] = idx / kBsrChunk;
+    xcol[u] = X + (long long)min(c0 + xc[u], K - 1) * ld;
+  }
+  d4v acc = {0.0, 0.0, 0.0, 0.0};
+  int buf = 0;
+  for (long long g = b0; g < b1; g += 64) {
+    const int ng = (int)(b1 - g < 64 ? b1 - g : 64);
+    const long long bl = g + min(lane, ng - 1);
+    const int nbl = op.col_idx[bl];
+    const int Jl = op.J[nbl];
+    const long long hl = op.boff[bl], xl = op.roff[nbl];
+    auto lane64 = [](long long v, int u) {
+      const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)v, u);
+      const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), u);
+      return (long long)(((unsigned long long)hi << 32) | lo);
+    };
+    // the next chunk: columns l .. of block blk
+    int blk = -1, l = 0, Jn = 0;
+    const double* hp = op.H;
+    long long xo = 0;
+    auto next_block = [&] {
+      do {
+        if (++blk >= ng) {   // past the end the same entry is loaded, so that the count of loads in flight is fixed
+          Jn = l = 0;
+          hp = op.H;
+          xo = 0;
+          return;
+        }
+        Jn = __builtin_amdgcn_readlane(Jl, blk);
+      } while (Jn == 0);
+      l = 0;
+      hp = op.H + lane64(hl, blk);
+      xo = lane64(xl, blk);
+    };
+    struct Staged {
+      double h[NH], x[NX];
+      int cols;   // 0: past the end
+    };
+    auto fetch = [&](Staged& f) {
+      f.cols = min(chunk, Jn - l);
+      const int last = max(f.cols, 1) - 1, n1 = max(f.cols * Jk, 1) - 1;
 #pragma unroll
-        for (int c = 0; c < kBsrCols; ++c) acc[c] += h * xs[l][c];
+      for (int u = 0; u < NH; ++u) f.h[u] = gload<double>(hp + min(tid + kBsrThreads * u, n1));
+#pragma unroll
+      for (int u = 0; u < NX; ++u) f.x[u] = gload<double>(xcol[u] + xo + min(xr[u], last));
+      l += chunk;
+      hp += chunk * Jk;
+      xo += chunk;
+      if (l >= Jn) next_block();
+    };
+    auto step = [&](Staged& f) {
+      const int cols = f.cols, n1 = cols * Jk - 1;
+      const double* hb = hs[buf];
+#pragma unroll
+      for (int u = 0; u < NH; ++u) hs[buf][min(tid + kBsrThreads * u, n1)] = f.h[u];
+#pragma unroll
+      for (int u = 0; u < NX; ++u) xs[buf][xc[u]][xr[u]] = f.x[u];
+      lds_barrier();
+      fetch(f);
+      constexpr int H = kBsrChunk / 8;   // k-steps of half a chunk, without branches between
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (!on || 4 * H * h >= cols) continue;
+        double a[H], b[H];
+#pragma unroll
+        for (int s = 0; s < H; ++s) {
+          const int j = 4 * (H * h + s) + kq;
+          a[s] = hb[min(j, cols - 1) * Jk + i];
+          b[s] = xs[buf][16 * ct + l16][j];
+        }
+#pragma unroll
+        for (int s = 0; s < H; ++s) {
+          const bool in = 4 * (H * h + s) + kq < cols;
+          acc = mfma16x16x4(in ? a[s] : 0.0, in ? b[s] : 0.0, acc);
+        }
       }
+      buf ^= 1;
+    };
+    next_block();
+    Staged f0, f1, f2;   // by name: a copy from one to the next would wait for its loads
+    if (blk >= ng) continue;
+    fetch(f0);
+    fetch(f1);
+    fetch(f2);
+    for (;;) {
+      if (f0.cols <= 0) break;
+      step(f0);
+      if (f1.cols <= 0) break;
+      step(f1);
+      if (f2.cols <= 0) break;
+      step(f2);
     }
   }
-  if (i < Jk) {
+  const int c = c0 + 16 * ct + l16;
+  if (!on || c >= K) return;
+  double* y = Y + y0 + (long long)c * ld;
 #pragma unroll
-    for (int c = 0; c < kBsrCols; ++c)
-      if (c0 + c < K) Y[r0 + i + (long long)(c0 + c) * E.ld] = acc[c];
-  }
+  for (int q = 0; q < 4; ++q)
+    if (r0 + kq + 4 * q < Jk) gstore(y + r0 + kq + 4 * q, acc[q]);
 }
 
 int launch_dg_bsr(Ctx& c, int in_blk, int out_blk, int ncols, const int* active) {
   const int K = ncols > 0 ? ncols : c.K[0];
   TimedScope ts(c, TC_OTHER);
-  hipLaunchKernelGGL(k_dg_bsr, dim3(c.dg_op.M, (K + kBsrCols - 1) / kBsrCols), dim3(kBsrThreads), 0, c.stream,
+  hipLaunchKernelGGL(k_dg_bsr, dim3(c.dg_op.M, (K + 15) / 16), dim3(kBsrThreads), 0, c.stream,
                      c.elems_dev, c.dg_op, in_blk, out_blk, ncols, active);
   DG_HIP(hipGetLastError());
   return DG_OK;

@@ -353,3 +353,46 @@ def test_chefsi_on_the_gpu_built_hamiltonian(c2_slab):
           f"(H difference {dev:.1e})", flush=True)
     assert st == 0
     assert np.max(np.abs(th - lam[:60])) <= 2e-9 + 10 * dev
+
+
+@pytest.mark.parametrize("Js", [[87, 17, 40, 1, 16, 3], [1, 4, 5, 2, 3] * 14], ids=["uneven", "70_blocks_a_row"])
+@pytest.mark.parametrize("n_vec", [1, 17, 33])
+def test_chefsi_block_product_at_tile_edges(Js, n_vec):
+    """H^DG of uneven random blocks: block sizes on both sides of the 16-row tiles and of
+    the four columns of a k-step, a row with its diagonal block alone, rows of more than 64 blocks.
+    After one pass the returned values and residuals are those of the returned vectors:
+    sums of N_b products and a rotation of n_vec terms, so 4 N_b eps ||H|| bounds the
+    rounding of either."""
+    torch = need_torch_cuda()
+    from paper_2003_00407_amd import dgalb as D
+    rng = np.random.default_rng(7)
+    M = len(Js)
+    els = [W._box_element((8, 8, 8), (6.0, 6.0, 6.0), rng.uniform(0.0, 6.0, size=(2, 3)), J) for J in Js]
+    print(f"[chefsi] blocks {Js[:6]} x {M}, {n_vec} columns", flush=True)
+    off = np.concatenate([[0], np.cumsum(Js)])
+    Nb = int(off[-1])
+    H = rng.standard_normal((Nb, Nb))
+    H = 0.5 * (H + H.T)
+    H[off[1]:off[2], :off[1]] = 0.0          # row 1 keeps its diagonal block only
+    H[off[1]:off[2], off[2]:] = 0.0
+    H[:off[1], off[1]:off[2]] = 0.0
+    H[off[2]:, off[1]:off[2]] = 0.0
+    row_ptr, col, boff, flat = [0], [], [0], []
+    for k in range(M):
+        for n in range(M):
+            if k != n and 1 in (k, n):
+                continue
+            col.append(n)
+            flat.append(H[off[k]:off[k + 1], off[n]:off[n + 1]].T.ravel())
+            boff.append(boff[-1] + Js[k] * Js[n])
+        row_ptr.append(len(col))
+    E = D.Elements(els, n_guard=1)
+    x0 = torch.tensor(W.initial_block(Nb, n_vec, 5), dtype=torch.float64, device="cuda")
+    X, eig, res, it, st = E.chefsi(torch.tensor(np.concatenate(flat), device="cuda"), (row_ptr, col, boff), x0, n_vec,
+                                   degree=8, tol=1e-12, max_iter=1)
+    Xg, th = X.cpu().numpy().T, eig.cpu().numpy()
+    bound = 4 * Nb * np.finfo(float).eps * np.linalg.norm(H, 2)
+    HX = H @ Xg
+    assert np.max(np.abs(Xg.T @ Xg - np.eye(n_vec))) <= 4 * Nb * np.finfo(float).eps
+    assert np.max(np.abs(np.sum(Xg * HX, axis=0) - th)) <= bound
+    assert np.max(np.abs(np.linalg.norm(HX - Xg * th, axis=0) - res.cpu().numpy())) <= bound
