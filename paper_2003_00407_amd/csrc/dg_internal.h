@@ -364,7 +364,9 @@ int launch_permute(Ctx& c, const int* perm, const int* active);
 int query_workspace(int n_elem, const dg_element_desc* d, const dg_options* opt, size_t* bytes);
 int create(Ctx** out, int n_elem, const dg_element_desc* d, const dg_options* opt, void* arena,
            size_t arena_bytes, void* stream);
-int apply_h(Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx, void* y, long long ldy);
+// overlap: x and y share memory
+int apply_h(Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx, void* y, long long ldy,
+            bool overlap);
 int solve(Ctx& c, const dg_solve_params* p, double* eig, double* resid, int* iters);
 int get_vectors(Ctx& c, double* x);
 int make_alb(Ctx& c, double* alb, double* sval);

@@ -73,3 +73,35 @@ def test_hpsi_c2_full_size_elements_fp64():
     els = W.make_config("c2").elements[:2]
     assert _run(els, 4, 0) < FP64_TOL
     assert _run(els, 4, 2) < FP32_TOL
+
+
+@pytest.mark.parametrize("prec", [0, 2])
+@pytest.mark.parametrize("elem", [-1, 1])
+@pytest.mark.parametrize("n_vec", [1, 4])
+def test_hpsi_in_place_and_through_copies_agree(prec, elem, n_vec):
+    """Disjoint caller buffers are read and written in place, overlapping ones go through
+    the context's blocks: the same kernels, so the same bits, packed, with odd leading
+    dimensions, and with y in x's own memory or in its gaps."""
+    torch = need_torch_cuda()
+    from paper_2003_00407_amd import dgalb as D
+    els = W.small_slab(n_states=8)[:3]
+    E = D.Elements(els)
+    N, ne = els[0].npts, len(els) if elem < 0 else 1
+    print(f"[hpsi] routes prec {prec} elem {elem} n_vec {n_vec}", flush=True)
+    dt = torch.float64 if prec == D.DG_FP64 else torch.float32
+    x = torch.tensor(np.random.default_rng(8).standard_normal(N * n_vec * ne), dtype=dt, device="cuda")
+    y = E.apply_H(x, n_vec, prec, elem=elem)
+    own = x.clone()
+    E.apply_H(own, n_vec, prec, elem=elem, y=own)
+    assert torch.equal(own, y)
+    ld = 2 * N + 3                       # x in the first N values of a column, y in the last N
+    both = torch.zeros(ld * n_vec * ne + N + 3, dtype=dt, device="cuda")
+    cols = both[:ld * n_vec * ne].view(ne, n_vec, ld)
+    cols[:, :, :N] = x.view(ne, n_vec, N)
+    E.apply_H(both, n_vec, prec, elem=elem, ldx=ld, ldy=ld, y=both[N + 3:])
+    assert torch.equal(cols[:, :, N + 3:], y.view(ne, n_vec, N))
+    assert torch.equal(cols[:, :, :N], x.view(ne, n_vec, N))
+    out = torch.zeros((N + 1) * n_vec * ne, dtype=dt, device="cuda")
+    E.apply_H(both, n_vec, prec, elem=elem, ldx=ld, ldy=N + 1, y=out)
+    assert torch.equal(out.view(ne, n_vec, N + 1)[:, :, :N], y.view(ne, n_vec, N))
+    assert torch.count_nonzero(out.view(ne, n_vec, N + 1)[:, :, N:]).item() == 0
