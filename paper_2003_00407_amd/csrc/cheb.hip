@@ -9,14 +9,11 @@
 
 namespace dg {
 
-int launch_cheb_step(Ctx& c, int prec, int y_blk, int hy_blk, int prev_blk, int k, int ncols, const int* active,
-                     const double* bounds);
-int launch_adj_step(Ctx& c, int prec, int a1_blk, int t_blk, int a2_blk, int k, int m, int ncols,
-                    const double* bounds);
+int launch_cheb_coef(Ctx& c, int m, const double* bounds);
 int launch_weighted_dot(Ctx& c, int prec, int u_blk, int w_blk, int ncols, const double* f, double scale,
                         double* E);
-int launch_vbar(Ctx& c, int prec, int u_blk, int y_blk, int ncols, const double* f, const double* scale, int k,
-                int m, const double* bounds, double beta, double* vbar);
+int launch_vbar(Ctx& c, int prec, int u_blk, int y_blk, int ncols, const double* f, const double* scale,
+                const FilterStep& step, double beta, double* vbar);
 int launch_scale_cols(Ctx& c, int prec, int in_blk, int out_blk, int ncols, const double* f, const double* scale,
                       double mult);
 int launch_copy_cols(Ctx& c, int prec, const void* const* src_tab, void* const* dst_tab, int src_blk, int dst_blk,
@@ -28,6 +25,15 @@ static int sync_read_c(Ctx& c, void* dst, const void* src, size_t bytes) {
   DG_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c.stream));
   DG_HIP(hipStreamSynchronize(c.stream));
   return DG_OK;
+}
+
+// step k of the filter whose coefficients launch_cheb_coef left (Y_{k+1} from Y_k and
+// Y_{k-1} in prev), and of its adjoint (A_k from A_{k+1} and A_{k+2} in prev)
+static FilterStep filter_step(const Ctx& c, int k, int prev) {
+  return FilterStep{c.gram_part + 3 * k, c.gram_part_stride, 2, prev};
+}
+static FilterStep adjoint_step(const Ctx& c, int k, int prev) {
+  return FilterStep{c.gram_part + 3 * k, c.gram_part_stride, 5, prev};
 }
 
 // pick a block from the pool that is none of the excluded ones
@@ -112,11 +118,11 @@ int run_chfsi(Ctx& c, int prec, double tol, int max_iter, int degree, int* iters
     }
     if (cnt[0] == 0) break;
     // filter Y_m = p_m(H) X  (Algorithm 2 step 2)
+    if ((st = launch_cheb_coef(c, degree, nullptr))) return st;
     int prev = -1, cur = B_X;
     for (int k = 0; k < degree; ++k) {
       const int t = pick(pool, prev, cur);
-      if ((st = launch_hpsi(c, -1, 0, prec, cur, t, active))) return st;
-      if ((st = launch_cheb_step(c, prec, cur, t, prev, k, 0, active, nullptr))) return st;
+      if ((st = launch_hpsi_step(c, 0, prec, cur, t, active, filter_step(c, k, prev)))) return st;
       prev = cur;
       cur = t;
     }
@@ -148,11 +154,17 @@ int run_chfsi(Ctx& c, int prec, double tol, int max_iter, int degree, int* iters
 // ---------------------------------------------------------------------------
 struct BELayout {
   int nseg, s, m;
-  int ck_prev(int j) const { return kMaxBlocks + 2 * j; }      // Y_{js-1}
-  int ck_cur(int j) const { return kMaxBlocks + 2 * j + 1; }   // Y_{js}
+  int ck_prev(int j) const { return s == 1 ? ck_cur(j - 1) : kMaxBlocks + 2 * j; }   // Y_{js-1}, j >= 1
+  int ck_cur(int j) const { return kMaxBlocks + 2 * j + 1; }                         // Y_{js}
   int ym() const { return kMaxBlocks + 2 * nseg; }
   int hym() const { return ym() + 1; }
   int seg(int i) const { return hym() + 1 + i; }
+  // where the forward pass keeps Y_k: a checkpoint, the result, or nowhere (-1)
+  int kept(int k) const {
+    if (k == m) return ym();
+    if (k % s == 0) return ck_cur(k / s);
+    return (k + 1) % s == 0 && k + 1 < m ? ck_prev((k + 1) / s) : -1;
+  }
 };
 
 int band_energy(Ctx& c, int prec, int degree, const double* bounds_host, int n_vec, const void* psi0,
@@ -187,24 +199,17 @@ int band_energy(Ctx& c, int prec, int degree, const double* bounds_host, int n_v
   DG_HIP(hipMemcpyAsync(c.dev_bounds, c.be_bounds_host.data(), sizeof(double) * 3 * c.n_elem,
                         hipMemcpyHostToDevice, c.stream));
   const double* bd = c.dev_bounds;
-  // Y_0 = Psi_0 into X
-  if ((st = launch_copy_ext(c, prec, B_X, psi0, -1, n_vec, 0))) return st;
-  if ((st = launch_copy_cols(c, prec, nullptr, nullptr, B_X, L.ck_cur(0), n_vec))) return st;
+  // iterates that are kept are written where they stay
+  if ((st = launch_copy_ext(c, prec, L.kept(0), psi0, -1, n_vec, 0))) return st;
+  if ((st = launch_cheb_coef(c, degree, bd))) return st;
   const std::vector<int> ypool = {B_X, B_W, B_P};
-  int prev = -1, cur = B_X;
+  int prev = -1, cur = L.kept(0);
   for (int k = 0; k < degree; ++k) {
-    const int t = pick(ypool, prev, cur);
-    if ((st = launch_hpsi(c, -1, n_vec, prec, cur, t, nullptr))) return st;
-    if ((st = launch_cheb_step(c, prec, cur, t, prev, k, n_vec, nullptr, bd))) return st;
+    const int t = L.kept(k + 1) >= 0 ? L.kept(k + 1) : pick(ypool, prev, cur);
+    if ((st = launch_hpsi_step(c, n_vec, prec, cur, t, nullptr, filter_step(c, k, prev)))) return st;
     prev = cur;
     cur = t;
-    if ((k + 1) % L.s == 0 && k + 1 < degree) {
-      const int j = (k + 1) / L.s;
-      if ((st = launch_copy_cols(c, prec, nullptr, nullptr, prev, L.ck_prev(j), n_vec))) return st;
-      if ((st = launch_copy_cols(c, prec, nullptr, nullptr, cur, L.ck_cur(j), n_vec))) return st;
-    }
   }
-  if ((st = launch_copy_cols(c, prec, nullptr, nullptr, cur, L.ym(), n_vec))) return st;
   if ((st = launch_hpsi(c, -1, n_vec, prec, L.ym(), L.hym(), nullptr))) return st;
   // f lives on the device (caller buffer)
   if ((st = launch_weighted_dot(c, prec, L.ym(), L.hym(), n_vec, f, 1.0, E))) return st;
@@ -238,24 +243,24 @@ int band_energy_backward(Ctx& c, const double* dE_host, void* dpsi0, void* dv) {
   // A_m = 2 dE H Y_m F ;  Vbar = dE sum_i f_i y_{m,i}^2
   int a1 = B_X, a2 = -1;
   if ((st = launch_scale_cols(c, prec, L.hym(), a1, n_vec, c.be_f, c.dev_de, 2.0))) return st;
-  if ((st = launch_vbar(c, prec, L.ym(), L.ym(), n_vec, c.be_f, c.dev_de, -1, m, bd, 0.0, vbar))) return st;
+  if ((st = launch_vbar(c, prec, L.ym(), L.ym(), n_vec, c.be_f, c.dev_de, FilterStep(), 0.0, vbar))) return st;
+  if ((st = launch_cheb_coef(c, m, bd))) return st;
   const std::vector<int> apool = {B_X, B_W, B_P};
   for (int j = L.nseg - 1; j >= 0; --j) {
     const int k0 = j * L.s, k1 = std::min(k0 + L.s, m);
-    // recompute Y_{k0} .. Y_{k1-1} from the checkpoint pair of segment j
-    if ((st = launch_copy_cols(c, prec, nullptr, nullptr, L.ck_cur(j), L.seg(0), n_vec))) return st;
+    // recompute Y_{k0+1} .. Y_{k1-1} from the checkpoint pair of segment j
+    auto y = [&](int i) { return i == 0 ? L.ck_cur(j) : L.seg(i); };
     for (int i = 1; i < k1 - k0; ++i) {
       const int k = k0 + i - 1;
-      const int prv = (i == 1) ? (j == 0 ? -1 : L.ck_prev(j)) : L.seg(i - 2);
-      if ((st = launch_hpsi(c, -1, n_vec, prec, L.seg(i - 1), L.seg(i), nullptr))) return st;
-      if ((st = launch_cheb_step(c, prec, L.seg(i - 1), L.seg(i), prv, k, n_vec, nullptr, bd))) return st;
+      const int prv = (i == 1) ? (j == 0 ? -1 : L.ck_prev(j)) : y(i - 2);
+      if ((st = launch_hpsi_step(c, n_vec, prec, y(i - 1), y(i), nullptr, filter_step(c, k, prv)))) return st;
     }
     for (int k = k1 - 1; k >= k0; --k) {
       // Vbar += alpha_k sum_i a_{k+1,i} y_{k,i}
-      if ((st = launch_vbar(c, prec, a1, L.seg(k - k0), n_vec, nullptr, nullptr, k, m, bd, 1.0, vbar))) return st;
+      if ((st = launch_vbar(c, prec, a1, y(k - k0), n_vec, nullptr, nullptr, filter_step(c, k, -1), 1.0, vbar)))
+        return st;
       const int t = pick(apool, a1, a2);
-      if ((st = launch_hpsi(c, -1, n_vec, prec, a1, t, nullptr))) return st;
-      if ((st = launch_adj_step(c, prec, a1, t, a2, k, m, n_vec, bd))) return st;
+      if ((st = launch_hpsi_step(c, n_vec, prec, a1, t, nullptr, adjoint_step(c, k, a2)))) return st;
       a2 = a1;
       a1 = t;
     }

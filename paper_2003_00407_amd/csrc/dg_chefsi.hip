@@ -32,7 +32,7 @@ constexpr int kBsrChunk = 40;     // block columns staged at a time at most,
 constexpr int kBsrEntries = 2048; // and their entries
 constexpr int kLanczosMax = 64;
 
-// H^DG X of block in_blk into out_blk: workgroup (k, y) forms the rows of element k in
+// H^DG X (or the filter step on it) of block in_blk into out_blk: workgroup (k, y) forms the rows of element k in
 // 16-column tiles y, or 2 y and 2 y + 1 where the rows leave waves for both (J_k <= 64).
 //
 // The operator (some MB) comes from beyond L2 at each product, so what counts is the
@@ -44,7 +44,7 @@ constexpr int kLanczosMax = 64;
 // blocks and of their columns.  8x8 elements of 40 functions, 13 blocks a row, 86
 // columns: 24 us; 96 us with a thread per row and two barriers per block before.
 __global__ void __launch_bounds__(kBsrThreads) k_dg_bsr(const ElemDev* elems, DgOp op, int in_blk, int out_blk,
-                                                        int ncols, const int* active) {
+                                                        int ncols, const int* active, FilterStep f) {
   // the loads that the block list hangs on go out together, before any test
   const ElemDev& E = elems[0];
   const int k = blockIdx.x;
@@ -173,17 +173,25 @@ __global__ void __launch_bounds__(kBsrThreads) k_dg_bsr(const ElemDev* elems, Dg
   }
   const int c = c0 + 16 * ct + l16;
   if (!on || c >= K) return;
-  double* y = Y + y0 + (long long)c * ld;
+  const long long o = y0 + (long long)c * ld + r0 + kq;
+  const double* pv = f.prev_blk >= 0 ? reinterpret_cast<const double*>(E.blk[f.prev_blk]) : nullptr;
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (r0 + kq + 4 * q < Jk) gstore(y + r0 + kq + 4 * q, acc[q]);
+  for (int q = 0; q < 4; ++q) {
+    if (r0 + kq + 4 * q >= Jk) continue;
+    double v = acc[q];
+    if (f.coef) {
+      v = f.coef[0] * (v - f.coef[1] * gload<double>(X + o + 4 * q));
+      if (pv) v -= f.coef[f.beta_at] * gload<double>(pv + o + 4 * q);
+    }
+    gstore(Y + o + 4 * q, v);
+  }
 }
 
-int launch_dg_bsr(Ctx& c, int in_blk, int out_blk, int ncols, const int* active) {
+int launch_dg_bsr(Ctx& c, int in_blk, int out_blk, int ncols, const int* active, const FilterStep& f) {
   const int K = ncols > 0 ? ncols : c.K[0];
   TimedScope ts(c, TC_OTHER);
   hipLaunchKernelGGL(k_dg_bsr, dim3(c.dg_op.M, (K + 15) / 16), dim3(kBsrThreads), 0, c.stream,
-                     c.elems_dev, c.dg_op, in_blk, out_blk, ncols, active);
+                     c.elems_dev, c.dg_op, in_blk, out_blk, ncols, active, f);
   DG_HIP(hipGetLastError());
   return DG_OK;
 }

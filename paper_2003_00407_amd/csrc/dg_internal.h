@@ -294,6 +294,15 @@ const char* get_error();
 // ---- kernel launchers (k_hpsi.hip) ----
 bool grid_supported(int nx, int ny, int nz);
 int launch_hpsi(Ctx& c, int elem, int ncols, int prec, int in_blk, int out_blk, const int* active);
+// One step of a Chebyshev recurrence: out <- alpha (H in - c in) - beta prev, the
+// coefficients of element e at coef[e stride + {0, 1, beta_at}] (k_cheb.hip).
+struct FilterStep {
+  const double* coef = nullptr;
+  long long stride = 0;
+  int beta_at = 2;
+  int prev_blk = -1;   // < 0: no third term
+};
+int launch_hpsi_step(Ctx& c, int ncols, int prec, int in_blk, int out_blk, const int* active, const FilterStep& f);
 // H*psi on caller buffers (ext.x -> ext.y), projector overlaps in ext.nlc
 int launch_hpsi_ext(Ctx& c, int elem, int ncols, int prec, const ExtBufs& ext);
 int launch_teter(Ctx& c, int prec, int x_blk, int hx_blk, int w_blk, int k3, const int* active,
@@ -371,7 +380,7 @@ int solve(Ctx& c, const dg_solve_params* p, double* eig, double* resid, int* ite
 int get_vectors(Ctx& c, double* x);
 int make_alb(Ctx& c, double* alb, double* sval);
 int density(Ctx& c, const double* alb, const double* C, long long ldc, int n_e, double* P, double* rho);
-int launch_dg_bsr(Ctx& c, int in_blk, int out_blk, int ncols, const int* active);
+int launch_dg_bsr(Ctx& c, int in_blk, int out_blk, int ncols, const int* active, const FilterStep& f = FilterStep());
 size_t chefsi_work_bytes(int M, int Nb, int K, int n_blocks);
 int chefsi(hipStream_t stream, const std::vector<int>& Js, const dg_chefsi_params& p, int n_blocks,
            const int64_t* row_ptr, const int32_t* col_idx, const int64_t* block_off, const double* hdg,

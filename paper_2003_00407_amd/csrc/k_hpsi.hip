@@ -299,7 +299,8 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
 // ---------------------------------------------------------------------------
 // z-column pass
 // ---------------------------------------------------------------------------
-enum ZMode { ZM_HPSI = 0, ZM_TETER = 1, ZM_DZ = 2 };
+// STEP: HPSI, and the other terms of a filter step on its result
+enum ZMode { ZM_HPSI = 0, ZM_TETER = 1, ZM_DZ = 2, ZM_STEP = 3 };
 
 struct ZArgs {
   const ElemDev* elems;
@@ -309,6 +310,7 @@ struct ZArgs {
   int ncols;
   int k3;
   ExtBufs ext;
+  FilterStep f;
 };
 
 template <typename T, int NZ, int TL, int MODE>
@@ -328,7 +330,7 @@ __global__ void __launch_bounds__(256) k_zcol(ZArgs A) {
   const cplx<T> wz = FZ::root(t);   // one root selection for both transforms
 
   cplx<T> v[M];
-  if constexpr (MODE == ZM_HPSI) {
+  if constexpr (MODE == ZM_HPSI || MODE == ZM_STEP) {
     PairCols<T> in = pair_cols<T>(E, e, A.in_blk, pair, ncols, A.ext);
     sfor<0, M>([&](auto i) {
       const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
@@ -344,11 +346,31 @@ __global__ void __launch_bounds__(256) k_zcol(ZArgs A) {
     });
     FZ::inverse(v, t, wz);
     PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
-    sfor<0, M>([&](auto i) {
-      const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
-      out.a[o] += v[CV(i)].re;
-      if (out.b) out.b[o] += v[CV(i)].im;
-    });
+    if constexpr (MODE == ZM_HPSI) {
+      sfor<0, M>([&](auto i) {
+        const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
+        out.a[o] += v[CV(i)].re;
+        if (out.b) out.b[o] += v[CV(i)].im;
+      });
+    } else {
+      // FP64: the three-term recurrence on the spot (x comes from the caches, it was read
+      // above).  As a kernel of its own (k_filter_step) it read y, x and the third term and
+      // wrote y again: 240 us of 1000 us a step for 48 vectors on six elements of 48x48x64
+      const double* cf = A.f.coef + e * A.f.stride;
+      const T al = cf[0], c = cf[1], be = A.f.prev_blk >= 0 ? cf[A.f.beta_at] : 0.0;
+      const PairCols<T> pv = pair_cols<T>(E, e, A.f.prev_blk >= 0 ? A.f.prev_blk : A.in_blk, pair, ncols, A.ext);
+      sfor<0, M>([&](auto i) {
+        const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
+        T ra = al * (out.a[o] + v[CV(i)].re - c * in.a[o]);
+        if (A.f.prev_blk >= 0) ra -= be * pv.a[o];
+        out.a[o] = ra;
+        if (out.b) {
+          T rb = al * (out.b[o] + v[CV(i)].im - c * in.b[o]);
+          if (A.f.prev_blk >= 0) rb -= be * pv.b[o];
+          out.b[o] = rb;
+        }
+      });
+    }
   } else if constexpr (MODE == ZM_DZ) {
     // d/dz along the columns of z
     PairCols<T> in = pair_cols<T>(E, e, A.in_blk, pair, ncols, A.ext);
@@ -414,6 +436,7 @@ struct NlArgs {
   int ncols;
   int elem_only;   // >= 0: only this element (gridDim.z == 1)
   ExtBufs ext;
+  FilterStep f;
 };
 
 // projector overlaps of element e: the element's own slice (nproj x kmax3), or the
@@ -489,7 +512,8 @@ __global__ void __launch_bounds__(256) k_nl_overlap(NlArgs A) {
   }
 }
 
-// y[r, j] += sum_{p in row r} b_p(r) gamma_p C[p, j] over the active points
+// y[r, j] += sum_{p in row r} b_p(r) gamma_p C[p, j] over the active points (times the
+// step's alpha after a filter step)
 constexpr int kNlApplyCols = 16;
 // LDS row pitch of the gamma C table: odd in doubles, so that lanes reading the rows
 // of different projectors fall in different banks
@@ -528,11 +552,37 @@ __global__ void __launch_bounds__(256) k_nl_apply(NlArgs A) {
 #pragma unroll
     for (int j = 0; j < kNlApplyCols; ++j) acc[j] += bv * gc[p * kNlApplyPitch + j];
   }
+  if (A.f.coef) {
+    const double al = A.f.coef[e * A.f.stride];
+#pragma unroll
+    for (int j = 0; j < kNlApplyCols; ++j) acc[j] *= al;
+  }
   long long ldy;
   T* Y = block_base<T>(E, e, A.out_blk, A.ext, ldy);
 #pragma unroll
   for (int j = 0; j < kNlApplyCols; ++j)
     if (j < nc) Y[(size_t)(c0 + j) * ldy + r] += T(acc[j]);
+}
+
+// hy <- alpha (hy - c x) - beta prev on H x in FP32: H x is rounded to FP32, projector
+// term included, before the step, which the fused pass could not keep
+__global__ void __launch_bounds__(256) k_filter_step(const ElemDev* elems, const int* active, int x_blk, int hy_blk,
+                                                     int cols, FilterStep f) {
+  const int e = blockIdx.z;
+  const ElemDev& E = elems[e];
+  if (active && !active[e]) return;
+  const int j = blockIdx.y;
+  if (j >= (cols > 0 ? cols : E.K)) return;
+  const double* cf = f.coef + e * f.stride;
+  const double al = cf[0], c = cf[1], be = f.prev_blk >= 0 ? cf[f.beta_at] : 0.0;
+  const float* x = reinterpret_cast<const float*>(E.blk[x_blk]) + (size_t)j * E.ld;
+  float* hy = reinterpret_cast<float*>(E.blk[hy_blk]) + (size_t)j * E.ld;
+  const float* pv = f.prev_blk >= 0 ? reinterpret_cast<const float*>(E.blk[f.prev_blk]) + (size_t)j * E.ld : nullptr;
+  for (int r = blockIdx.x * 256 + threadIdx.x; r < E.N; r += gridDim.x * 256) {
+    double v = al * (double(hy[r]) - c * double(x[r]));
+    if (pv) v -= be * double(pv[r]);
+    hy[r] = float(v);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -594,14 +644,14 @@ struct HpsiWork {
 };
 
 static HpsiWork hpsi_work(Ctx& c, int elem, int ncols, size_t sz, const std::vector<int>& members,
-                          const int* active_host) {
+                          const int* active_host, bool third = false) {
   HpsiWork w;
   for (int e : members) {
     if (elem >= 0 && e != elem) continue;
     if (active_host && !active_host[e]) continue;
     const double N = c.N[e], k = ncols > 0 ? ncols : c.K[e];
     w.plane += (2.0 * k + 1.0) * N * sz;          // read x, write y1, read V
-    w.zcol += 3.0 * k * N * sz;                   // read x, read y1, write y
+    w.zcol += (third ? 4.0 : 3.0) * k * N * sz;   // read x, read y1 (and a step's third term), write y
     const double nnz = c.nnz[e], nact = c.elems_host[e].nact;
     w.nl += nnz * (sz + 4) + 3.0 * nact * k * sz;  // projectors; x read, y read+write at active points
   }
@@ -610,7 +660,7 @@ static HpsiWork hpsi_work(Ctx& c, int elem, int ncols, size_t sz, const std::vec
 
 template <typename T>
 static int hpsi_typed(Ctx& c, int elem, int ncols, int in_blk, int out_blk, const int* active,
-                      const ExtBufs& ext = ExtBufs()) {
+                      const ExtBufs& ext = ExtBufs(), const FilterStep& f = FilterStep()) {
   hipStream_t s = c.stream;
   const int* act_host = (active && !c.active_host.empty()) ? c.active_host.data() : nullptr;
   const int* iota = c.iota_dev;
@@ -660,7 +710,7 @@ static int hpsi_typed(Ctx& c, int elem, int ncols, int in_blk, int out_blk, cons
     }
     const int npairs = (maxk + 1) / 2;
     PlaneArgs pa{c.elems_dev, list, active, in_blk, out_blk, -1, ncols, nullptr, 0, ext};
-    const HpsiWork hw = hpsi_work(c, elem, ncols, sizeof(T), sc.elem_list_host, act_host);
+    const HpsiWork hw = hpsi_work(c, elem, ncols, sizeof(T), sc.elem_list_host, act_host, f.prev_blk >= 0);
     {
       TimedScope ts(c, TC_PLANE, hw.plane);
       if (!dispatch_plane<T, PM_HPSI>(sc.nx, pa, sc.nz, npairs, nel, s)) {
@@ -668,17 +718,23 @@ static int hpsi_typed(Ctx& c, int elem, int ncols, int in_blk, int out_blk, cons
         return DG_ERR_SHAPE;
       }
     }
-    ZArgs za{c.elems_dev, list, active, in_blk, out_blk, ncols, 0, ext};
+    ZArgs za{c.elems_dev, list, active, in_blk, out_blk, ncols, 0, ext, f};
     {
       TimedScope ts(c, TC_ZCOL, hw.zcol);
-      if (!dispatch_z<T, ZM_HPSI>(sc.nz, za, sc.nx * sc.ny, npairs, nel, s)) {
+      bool ok;
+      if constexpr (sizeof(T) == 8)
+        ok = f.coef ? dispatch_z<T, ZM_STEP>(sc.nz, za, sc.nx * sc.ny, npairs, nel, s)
+                    : dispatch_z<T, ZM_HPSI>(sc.nz, za, sc.nx * sc.ny, npairs, nel, s);
+      else
+        ok = dispatch_z<T, ZM_HPSI>(sc.nz, za, sc.nx * sc.ny, npairs, nel, s);
+      if (!ok) {
         set_error("unsupported grid");
         return DG_ERR_SHAPE;
       }
     }
   }
   if (c.nl_pending_np > 0) {
-    NlArgs na{c.elems_dev, active, in_blk, out_blk, ncols, elem, ext};
+    NlArgs na{c.elems_dev, active, in_blk, out_blk, ncols, elem, ext, f};
     int nact = 0;
     for (int e = 0; e < c.n_elem; ++e)
       if (elem < 0 || e == elem) nact = std::max(nact, c.elems_host[e].nact);
@@ -696,6 +752,22 @@ int launch_hpsi(Ctx& c, int elem, int ncols, int prec, int in_blk, int out_blk, 
   if (c.dg_op.active) return launch_dg_bsr(c, in_blk, out_blk, ncols, active);
   return prec == DG_FP64 ? hpsi_typed<double>(c, elem, ncols, in_blk, out_blk, active)
                          : hpsi_typed<float>(c, elem, ncols, in_blk, out_blk, active);
+}
+
+int launch_hpsi_step(Ctx& c, int ncols, int prec, int in_blk, int out_blk, const int* active, const FilterStep& f) {
+  if (c.dg_op.active) return launch_dg_bsr(c, in_blk, out_blk, ncols, active, f);
+  if (prec == DG_FP64) return hpsi_typed<double>(c, -1, ncols, in_blk, out_blk, active, ExtBufs(), f);
+  if (int st = hpsi_typed<float>(c, -1, ncols, in_blk, out_blk, active)) return st;
+  int n = 0, k = std::max(ncols, 0);
+  for (int e = 0; e < c.n_elem; ++e) {
+    n = std::max(n, c.N[e]);
+    if (ncols <= 0) k = std::max(k, c.K[e]);
+  }
+  TimedScope ts(c, TC_OTHER);
+  hipLaunchKernelGGL(k_filter_step, dim3(std::min(64, (n + 255) / 256), k, c.n_elem), dim3(256), 0, c.stream,
+                     c.elems_dev, active, in_blk, out_blk, ncols, f);
+  DG_HIP(hipGetLastError());
+  return DG_OK;
 }
 
 int launch_hpsi_ext(Ctx& c, int elem, int ncols, int prec, const ExtBufs& ext) {

@@ -102,6 +102,23 @@ def test_checkpointed_equals_stored():
     assert rel_err(outs[1][2], outs[0][2]) < 1e-12
 
 
+@pytest.mark.parametrize("prec", [0, 2])
+@pytest.mark.parametrize("degree,stride", [(1, 1), (1, 4), (5, 2), (6, 3), (7, 3), (4, 9)])
+def test_kept_iterates_at_segment_edges(degree, stride, prec):
+    """Iterates are written where they are kept (checkpoint pairs, the result): segments
+    that divide the degree, leave a remainder, or hold it whole give the stored run's
+    values, since the recomputed iterates come from the same kernels."""
+    need_torch_cuda()
+    from paper_2003_00407_amd import dgalb as D
+    els = W.small_slab(n_states=8)[:2]
+    psi, f, bounds = _be_case(els, seed=4)
+    print(f"[band energy] degree {degree} stride {stride} prec {prec}", flush=True)
+    outs = [_gpu_be(D.Elements(els, max_cheb_degree=degree, ckpt_stride=s), psi, f, degree, bounds, prec,
+                    dE=np.array([1.0, -0.5])) for s in (1, stride)]
+    for a, b in zip(*outs):
+        assert np.all(np.isfinite(a)) and np.array_equal(a, b)
+
+
 def _atom_bump(el, centre, width=1.2):
     """Unit-norm Gaussian bump on el's grid around centre (a direction in V)."""
     nx, ny, nz = el.n
