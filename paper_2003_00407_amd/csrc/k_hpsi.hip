@@ -15,11 +15,11 @@
 //
 // Real vectors are processed in pairs (columns 2p, 2p+1) packed as one complex
 // line; an odd last column pairs with zero.
-#include "dg_internal.h"
+#include "dense_ops.h"
 #include "fft_line.h"
-#include "wave_ops.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace dg {
 
@@ -451,8 +451,15 @@ __device__ __forceinline__ double* nlc_base(const ElemDev& E, int e, const ExtBu
 }
 
 constexpr int kNlCols = 8;
-
-template <typename T>
+// NC: columns per workgroup; U: support points of a thread in flight (4 or 8 columns and
+// 1 to 4 points measure the same within 3 %).
+//
+// Bound by latency (index, then x) and by the number of loads.  A workgroup has one
+// group's four projectors; thread t sums the points t, t + 256, .. in that order, whatever
+// NC.  48 vectors, 16 elements of 48x48x64 with 40 groups of 2000 points: 248 us, 270 us
+// with one point in flight and a wave sum for each of the 32 values before; one element,
+// 40 vectors: 20 us, 46 us.
+template <typename T, int NC, int U>
 __global__ void __launch_bounds__(256) k_nl_overlap(NlArgs A) {
   const int e = A.elem_only >= 0 ? A.elem_only : blockIdx.z;
   const ElemDev& E = A.elems[e];
@@ -460,7 +467,7 @@ __global__ void __launch_bounds__(256) k_nl_overlap(NlArgs A) {
   const int g = blockIdx.x;
   if (g >= E.ngrp) return;
   const int ncols = A.ncols > 0 ? A.ncols : (A.ncols == kNcolsJ ? E.J : E.K);
-  const int c0 = blockIdx.y * kNlCols;
+  const int c0 = blockIdx.y * NC;
   if (c0 >= ncols) return;
   const int s0 = E.grp_sptr[g], s1 = E.grp_sptr[g + 1];
   const int len = s1 - s0;
@@ -473,95 +480,144 @@ __global__ void __launch_bounds__(256) k_nl_overlap(NlArgs A) {
   const T* val = nullptr;
   if constexpr (sizeof(T) == 8) val = reinterpret_cast<const T*>(E.grp_val64);
   else val = reinterpret_cast<const T*>(E.grp_val32);
-  double acc[4][kNlCols];
+  // columns and projectors past the end repeat the last one and are not stored
+  const T* xc[NC];
+  const T* bq[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int j = 0; j < NC; ++j) xc[j] = X + (size_t)min(c0 + j, ncols - 1) * ldx;
 #pragma unroll
-    for (int j = 0; j < kNlCols; ++j) acc[q][j] = 0.0;
-  for (int s = threadIdx.x; s < len; s += blockDim.x) {
-    const int r = E.grp_idx[s0 + s];
-    T b[4];
+  for (int q = 0; q < 4; ++q) bq[q] = val + vb + (long long)min(q, np - 1) * len;
+  const int* idx = E.grp_idx + s0;
+  double acc[4 * NC];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) b[q] = (q < np) ? val[vb + (long long)q * len + s] : T(0);
+  for (int i = 0; i < 4 * NC; ++i) acc[i] = 0.0;
+  const int full = len / (256 * U) * (256 * U);   // points in whole steps of the workgroup
+  int s = threadIdx.x;
+  for (; s < full; s += 256 * U) {
+    int r[U];
+    T b[U][4], x[U][NC];
 #pragma unroll
-    for (int j = 0; j < kNlCols; ++j) {
-      if (c0 + j < ncols) {
-        const T x = X[(size_t)(c0 + j) * ldx + r];
+    for (int u = 0; u < U; ++u) r[u] = idx[s + 256 * u];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q][j] += double(b[q]) * double(x);
-      }
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b[u][q] = bq[q][s + 256 * u];
+#pragma unroll
+      for (int j = 0; j < NC; ++j) x[u][j] = xc[j][r[u]];
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q * NC + j] += double(b[u][q]) * double(x[u][j]);
   }
-  // block reduction in a fixed order: DPP wave sums, then across waves
-  __shared__ double red[4][4 * kNlCols];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (; s < len; s += 256) {
+    const int r = idx[s];
+    T b[4], x[NC];
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < 4; ++q) b[q] = bq[q][s];
 #pragma unroll
-    for (int j = 0; j < kNlCols; ++j) {
-      const double v = wave_sum_dpp(acc[q][j]);
-      if (lane == 0) red[wv][q * kNlCols + j] = v;
-    }
+    for (int j = 0; j < NC; ++j) x[j] = xc[j][r];
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q * NC + j] += double(b[q]) * double(x[j]);
+  }
+  // block reduction in a fixed order: rows of 16 lanes, then rows, then waves
+  __shared__ double red[16][4 * NC];
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int h = 0; h < NC / 4; ++h) {
+    double v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = acc[16 * h + i];
+    red[threadIdx.x >> 4][16 * h + (lane & 15)] = row_sums16(v);
+  }
   __syncthreads();
-  const int nw = (blockDim.x + 63) >> 6;
-  for (int w = threadIdx.x; w < 4 * kNlCols; w += blockDim.x) {
-    double s = 0.0;
-    for (int i = 0; i < nw; ++i) s += red[i][w];
-    const int q = w / kNlCols, j = w % kNlCols;
-    if (q < np && c0 + j < ncols) nlc[(size_t)(p0 + q) * nld + c0 + j] = s;
+  for (int i = threadIdx.x; i < 4 * NC; i += blockDim.x) {
+    double t = 0.0;
+    for (int w = 0; w < 16; w += 4) t += (red[w][i] + red[w + 1][i]) + (red[w + 2][i] + red[w + 3][i]);
+    const int q = i / NC, j = i % NC;
+    if (q < np && c0 + j < ncols) nlc[(size_t)(p0 + q) * nld + c0 + j] = t;
   }
 }
 
 // y[r, j] += sum_{p in row r} b_p(r) gamma_p C[p, j] over the active points (times the
 // step's alpha after a filter step)
-constexpr int kNlApplyCols = 16;
-// LDS row pitch of the gamma C table: odd in doubles, so that lanes reading the rows
-// of different projectors fall in different banks
-constexpr int kNlApplyPitch = kNlApplyCols + 1;
+// NC: columns per thread.  Bound by latency: y and the entries of a point are loaded
+// ahead of the sums.  LDS row pitch of the gamma C table: NC + 2, so that a row is read
+// in 16-byte pairs.  48 vectors, 16 elements of 48x48x64, 43000 points with about eight
+// entries each: 199 us, 374 us with y loaded last and one entry at a time before; one
+// element, 40 vectors: 17 us, 29 us.
+constexpr int kNlApplyPad = 2;
+constexpr size_t nl_apply_lds(int nproj, int nc) { return (size_t)nproj * (nc + kNlApplyPad) * sizeof(double); }
 
-template <typename T>
+template <typename T, int NC>
 __global__ void __launch_bounds__(256) k_nl_apply(NlArgs A) {
+  constexpr int kPitch = NC + kNlApplyPad, B = 4;   // B: entries in flight
   const int e = A.elem_only >= 0 ? A.elem_only : blockIdx.z;
   const ElemDev& E = A.elems[e];
   if (A.active && !A.active[e]) return;
   const int ncols = A.ncols > 0 ? A.ncols : (A.ncols == kNcolsJ ? E.J : E.K);
-  const int c0 = blockIdx.y * kNlApplyCols;
-  if (c0 >= ncols || E.nact == 0) return;
-  const int nc = min(kNlApplyCols, ncols - c0);
-  extern __shared__ double gc[];   // nproj x kNlApplyPitch: gamma_p C[p, c0 + j]
+  const int c0 = blockIdx.y * NC;
+  if (c0 >= ncols || E.nact == 0 || blockIdx.x * 256 >= E.nact) return;
+  const int nc = min(NC, ncols - c0);
+  extern __shared__ __align__(16) double gc[];   // nproj x kPitch: gamma_p C[p, c0 + j]
+  // points past the end repeat the last one and are not stored
+  const int a = blockIdx.x * 256 + threadIdx.x;
+  const int ac = min(a, E.nact - 1);
+  const int r = E.act_idx[ac];
+  const int q0 = E.act_ptr[ac], q1 = E.act_ptr[ac + 1];
+  long long ldy;
+  T* Y = block_base<T>(E, e, A.out_blk, A.ext, ldy);
+  T y[NC];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) y[j] = Y[(size_t)(c0 + min(j, nc - 1)) * ldy + r];
   int nld;
   const double* nlc = nlc_base(E, e, A.ext, nld);
-  for (int i = threadIdx.x; i < E.nproj * kNlApplyCols; i += blockDim.x) {
-    const int p = i / kNlApplyCols, j = i % kNlApplyCols;
-    gc[p * kNlApplyPitch + j] = (j < nc) ? E.gamma[p] * nlc[(size_t)p * nld + c0 + j] : 0.0;
+  for (int i = threadIdx.x; i < E.nproj * NC; i += 256) {
+    const int p = i / NC, j = i % NC;
+    gc[p * kPitch + j] = (j < nc) ? E.gamma[p] * nlc[(size_t)p * nld + c0 + j] : 0.0;
   }
-  __syncthreads();
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= E.nact) return;
-  const int r = E.act_idx[a];
-  const int q0 = E.act_ptr[a], q1 = E.act_ptr[a + 1];
-  double acc[kNlApplyCols];
+  lds_barrier();
+  double acc[NC];
 #pragma unroll
-  for (int j = 0; j < kNlApplyCols; ++j) acc[j] = 0.0;
+  for (int j = 0; j < NC; ++j) acc[j] = 0.0;
   const T* ev = nullptr;
   if constexpr (sizeof(T) == 8) ev = reinterpret_cast<const T*>(E.ent_val64);
   else ev = reinterpret_cast<const T*>(E.ent_val32);
-  for (int q = q0; q < q1; ++q) {
-    const int p = E.ent_proj[q];
-    const double bv = double(ev[q]);
+  auto add = [&](int p, double bv) {
+    const double2* row = reinterpret_cast<const double2*>(gc + p * kPitch);
 #pragma unroll
-    for (int j = 0; j < kNlApplyCols; ++j) acc[j] += bv * gc[p * kNlApplyPitch + j];
+    for (int m = 0; m < NC / 2; ++m) {
+      const double2 v = row[m];
+      acc[2 * m] += bv * v.x;
+      acc[2 * m + 1] += bv * v.y;
+    }
+  };
+  int q = q0;
+  for (; q + B <= q1; q += B) {
+    int p[B];
+    double bv[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      p[u] = E.ent_proj[q + u];
+      bv[u] = double(ev[q + u]);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) add(p[u], bv[u]);
   }
+  for (; q < q1; ++q) add(E.ent_proj[q], double(ev[q]));
+  if (a >= E.nact) return;
   if (A.f.coef) {
     const double al = A.f.coef[e * A.f.stride];
 #pragma unroll
-    for (int j = 0; j < kNlApplyCols; ++j) acc[j] *= al;
+    for (int j = 0; j < NC; ++j) acc[j] *= al;
   }
-  long long ldy;
-  T* Y = block_base<T>(E, e, A.out_blk, A.ext, ldy);
 #pragma unroll
-  for (int j = 0; j < kNlApplyCols; ++j)
-    if (j < nc) Y[(size_t)(c0 + j) * ldy + r] += T(acc[j]);
+  for (int j = 0; j < NC; ++j)
+    if (j < nc) Y[(size_t)(c0 + j) * ldy + r] = y[j] + T(acc[j]);
 }
 
 // hy <- alpha (hy - c x) - beta prev on H x in FP32: H x is rounded to FP32, projector
@@ -688,8 +744,8 @@ static int hpsi_typed(Ctx& c, int elem, int ncols, int in_blk, int out_blk, cons
       std::vector<int> all(c.n_elem);
       for (int e = 0; e < c.n_elem; ++e) all[e] = e;
       TimedScope ts(c, TC_NL, hpsi_work(c, elem, ncols, sizeof(T), all, act_host).nl);
-      dim3 g1(ng, (kk + kNlCols - 1) / kNlCols, elem >= 0 ? 1 : c.n_elem);
-      hipLaunchKernelGGL(k_nl_overlap<T>, g1, dim3(256), 0, s, na);
+      const int nel = elem >= 0 ? 1 : c.n_elem;
+      hipLaunchKernelGGL((k_nl_overlap<T, kNlCols, 2>), dim3(ng, (kk + kNlCols - 1) / kNlCols, nel), dim3(256), 0, s, na);
     }
     c.nl_pending_np = np;
     c.nl_pending_kk = kk;
@@ -738,11 +794,16 @@ static int hpsi_typed(Ctx& c, int elem, int ncols, int in_blk, int out_blk, cons
     int nact = 0;
     for (int e = 0; e < c.n_elem; ++e)
       if (elem < 0 || e == elem) nact = std::max(nact, c.elems_host[e].nact);
-    dim3 g2((nact + 255) / 256, (c.nl_pending_kk + kNlApplyCols - 1) / kNlApplyCols,
-            elem >= 0 ? 1 : c.n_elem);
-    size_t shm = (size_t)c.nl_pending_np * kNlApplyPitch * sizeof(double);
     TimedScope ts(c, TC_NL);
-    hipLaunchKernelGGL(k_nl_apply<T>, g2, dim3(256), shm, s, na);
+    const int nel = elem >= 0 ? 1 : c.n_elem;
+    // 16 columns, and 8 where the table of the most projectors (480) exceeds 64 KB of LDS
+    auto apply = [&](auto nc) {
+      constexpr int NC = decltype(nc)::value;
+      hipLaunchKernelGGL((k_nl_apply<T, NC>), dim3((nact + 255) / 256, (c.nl_pending_kk + NC - 1) / NC, nel), dim3(256),
+                         nl_apply_lds(c.nl_pending_np, NC), s, na);
+    };
+    if (nl_apply_lds(c.nl_pending_np, 16) <= 65536) apply(std::integral_constant<int, 16>());
+    else apply(std::integral_constant<int, 8>());
   }
   DG_HIP(hipGetLastError());
   return DG_OK;

@@ -31,6 +31,33 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 }
 
 
+// Row sums of 16 values per lane at once: lane l returns the sum over its row of 16
+// lanes of value l % 16, added in the order of wave_sum_dpp's rows (each level sends away
+// the half of the values that the other lane keeps: 15 exchanges instead of 64).
+__device__ __forceinline__ double dpp_xor4(double v) {
+  auto mov = [](int x) {   // lanes with bit 2 clear take lane + 4 (row_shl), the others lane - 4 (row_shr)
+    const int y = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xF, 0x5, false);
+    return __builtin_amdgcn_update_dpp(y, x, 0x114, 0xF, 0xA, false);
+  };
+  return __hiloint2double(mov(__double2hiint(v)), mov(__double2loint(v)));
+}
+__device__ __forceinline__ double row_sums16(double (&v)[16]) {
+  const int lane = threadIdx.x & 63;
+  auto halve = [&](int n, bool up, auto mov) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (k >= n) continue;
+      const double keep = up ? v[2 * k + 1] : v[2 * k], send = up ? v[2 * k] : v[2 * k + 1];
+      v[k] = keep + mov(send);
+    }
+  };
+  halve(8, lane & 1, [](double x) { return dpp_mov<0xB1>(x); });    // quad_perm [1,0,3,2]
+  halve(4, lane & 2, [](double x) { return dpp_mov<0x4E>(x); });    // quad_perm [2,3,0,1]
+  halve(2, lane & 4, [](double x) { return dpp_xor4(x); });
+  halve(1, lane & 8, [](double x) { return dpp_mov<0x128>(x); });   // row_ror:8
+  return v[0];
+}
+
 // sum over each group of 8 consecutive lanes (all 8 active), the same value on every
 // lane of the group: two quad permutes, then the xor-4 partner through ds_bpermute
 __device__ __forceinline__ double group8_sum(double v) {

@@ -105,3 +105,33 @@ def test_hpsi_in_place_and_through_copies_agree(prec, elem, n_vec):
     E.apply_H(both, n_vec, prec, elem=elem, ldx=ld, ldy=N + 1, y=out)
     assert torch.equal(out.view(ne, n_vec, N + 1)[:, :, :N], y.view(ne, n_vec, N))
     assert torch.count_nonzero(out.view(ne, n_vec, N + 1)[:, :, N:]).item() == 0
+
+
+def _with_projectors(el, lens, rng):
+    """el with projectors on random supports of the given lengths, grouped in runs of equal
+    support: (support points, projectors sharing it) per entry of lens."""
+    idx, val, ptr, gam = [], [], [0], []
+    for n, count in lens:
+        pts = np.sort(rng.choice(el.npts, size=n, replace=False)).astype(np.int32)
+        for _ in range(count):
+            idx.append(pts)
+            val.append(rng.standard_normal(n) / np.sqrt(n))
+            ptr.append(ptr[-1] + n)
+            gam.append(rng.uniform(-1.0, 1.0))
+    return dataclasses.replace(el, proj_ptr=np.array(ptr, dtype=np.int64), proj_idx=np.concatenate(idx),
+                               proj_val=np.concatenate(val), gamma=np.array(gam))
+
+
+@pytest.mark.parametrize("prec,tol", [(0, FP64_TOL), (2, FP32_TOL)])
+@pytest.mark.parametrize("n_vec", [1, 8, 9, 17])
+def test_hpsi_projector_shapes(n_vec, prec, tol):
+    """Projector groups of one to four with supports around the 256-point steps and two
+    steps in flight, points with no, few and many entries, and an element whose table of
+    projectors is too large for 16 columns in LDS (456 and more)."""
+    rng = np.random.default_rng(5)
+    box = W._box_element((12, 12, 12), (8.0, 8.0, 8.0), rng.uniform(0.0, 8.0, size=(2, 3)), 16)
+    els = [_with_projectors(box, [(1, 1), (255, 2), (256, 3), (257, 4), (511, 1), (512, 4), (513, 2), (1728, 4)], rng),
+           _with_projectors(box, [(40, 4)] * 116 + [(700, 1)], rng)]
+    assert els[1].n_proj == 465
+    for some in (els[:1], els):
+        assert _run(some, n_vec, prec) < tol
