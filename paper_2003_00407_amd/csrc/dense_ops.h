@@ -38,9 +38,10 @@ __device__ __forceinline__ double2 gload2(const void* p) {
   const gd2 v = *(const __attribute__((address_space(1))) gd2*)(p);
   return double2{v.x, v.y};
 }
-// FP64 store through a global-address-space pointer (a flat store would make later LDS
-// waits wait for its completion)
-__device__ __forceinline__ void gstore(double* p, double v) { *(__attribute__((address_space(1))) double*)(p) = v; }
+// store through a global-address-space pointer (a flat store would make later LDS waits
+// wait for its completion)
+template <typename V>
+__device__ __forceinline__ void gstore(V* p, V v) { *(__attribute__((address_space(1))) V*)(p) = v; }
 typedef float gf2 __attribute__((ext_vector_type(2)));
 typedef float gf4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float2 gload2f(const void* p) {

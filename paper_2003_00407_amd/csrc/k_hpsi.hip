@@ -62,11 +62,25 @@ struct PlaneArgs {
   int r_given = 0;        // TFWD: aux already holds r = HX - X theta (in_blk is not read)
 };
 
-// Columns 2p and 2p+1 of a block (the second may be absent).
+// Columns 2p and 2p+1 of a block.  Where the second is absent, b repeats a: it is loaded
+// without a branch, taken as zero and not stored.  Loads and stores go through the global
+// address space: the pointers come from memory, and flat accesses also count as LDS
+// accesses, so that LDS waits wait for them.
 template <typename T>
 struct PairCols {
   T* a;
   T* b;
+  bool two;
+  __device__ __forceinline__ cplx<T> load(size_t o) const {
+    const T re = gload<T>(a + o), im = gload<T>(b + o);
+    return {re, two ? im : T(0)};
+  }
+  // v[i] to at(i), i < N: one branch for the second column
+  template <int N, typename F>
+  __device__ __forceinline__ void store(const cplx<T> (&v)[N], F at) const {
+    sfor<0, N>([&](auto i) { gstore(a + at(i), v[CV(i)].re); });
+    if (two) sfor<0, N>([&](auto i) { gstore(b + at(i), v[CV(i)].im); });
+  }
 };
 
 // First value and leading dimension of element e's columns in block blk, or in a
@@ -91,7 +105,8 @@ __device__ __forceinline__ PairCols<T> pair_cols(const ElemDev& E, int e, int bl
   T* base = block_base<T>(E, e, blk, X, ld);
   PairCols<T> pc;
   pc.a = base + (size_t)(2 * pair) * ld;
-  pc.b = (2 * pair + 1 < ncols) ? pc.a + ld : nullptr;
+  pc.two = 2 * pair + 1 < ncols;
+  pc.b = pc.two ? pc.a + ld : pc.a;
   return pc;
 }
 
@@ -127,42 +142,50 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
   const size_t zoff = (size_t)z * NXY;
   cplx<T>* P = sm + (slot < PPW ? slot : 0) * NY * PITCH;
 
-  // ---- load the plane (pair) into LDS
+  // ---- load the plane (pair) into LDS: this thread's values are column lt % NX of the
+  // rows lt / NX + TL i.  All loads go out before the first wait, and the stores at the
+  // end without a branch each.  48 vectors on 16 elements of 48x48x64: 725 us, 757 us as a
+  // loop with a wait per row and V read after the barrier (the first Teter pass 459 us,
+  // 490 us; the last 296 us, 345 us).  The rest is the transforms: about 1400 vector
+  // instructions and 120 LDS accesses a wave.
+  constexpr int NI = NXY / TPP;
+  static_assert(NX == NY && NXY % TPP == 0, "square planes, a whole number of rows per pass");
+  const int lr = lt / NX, lc = lt % NX;
+  auto at = [&](auto i) { return zoff + lt + TPP * CV(i); };
+  const T* V = vptr<T>(E);
+  T vv[MODE == PM_HPSI ? MY : 1];
+  cplx<T> ld[NI];
   if constexpr (MODE == PM_HPSI || MODE == PM_TINV || MODE == PM_DX || MODE == PM_DY) {
     const int blk = (MODE == PM_TINV) ? A.out_blk : A.in_blk;
-    PairCols<T> in = pair_cols<T>(E, e, blk, pair, MODE == PM_TINV ? 2 * pair + 2 : ncols, A.ext);
+    const PairCols<T> in = pair_cols<T>(E, e, blk, pair, MODE == PM_TINV ? 2 * pair + 2 : ncols, A.ext);
     if (zok) {
-      for (int i = lt; i < NXY; i += TPP) {
-        T re = in.a[zoff + i];
-        T im = in.b ? in.b[zoff + i] : T(0);
-        P[(i / NX) * PITCH + (i % NX)] = {re, im};
-      }
+      sfor<0, NI>([&](auto i) { ld[CV(i)] = in.load(at(i)); });
+      if constexpr (MODE == PM_HPSI)
+        sfor<0, MY>([&](auto i) { vv[CV(i)] = gload<T>(V + zoff + (t + TL * CV(i)) * NX + line); });
     }
   } else {  // PM_TFWD: r = HX - theta X
-    PairCols<T> xx = pair_cols<T>(E, e, A.in_blk, pair, ncols, A.ext);
-    PairCols<T> hx = pair_cols<T>(E, e, A.aux_blk, pair, ncols, A.ext);
+    const PairCols<T> xx = pair_cols<T>(E, e, A.in_blk, pair, ncols, A.ext);
+    const PairCols<T> hx = pair_cols<T>(E, e, A.aux_blk, pair, ncols, A.ext);
     const int KP = E.kmax3 + 2;
     const double* th = E.small + SmallLayout::vec(KP) + VS_THETA * KP;
     const T ta = T(th[2 * pair]);
-    const T tb = xx.b ? T(th[2 * pair + 1]) : T(0);
-    if (zok && A.r_given) {
-      for (int i = lt; i < NXY; i += TPP) {
-        T re = hx.a[zoff + i];
-        T im = hx.b ? hx.b[zoff + i] : T(0);
-        P[(i / NX) * PITCH + (i % NX)] = {re, im};
-      }
-    } else if (zok) {
-      for (int i = lt; i < NXY; i += TPP) {
-        T re = hx.a[zoff + i] - ta * xx.a[zoff + i];
-        T im = xx.b ? (hx.b[zoff + i] - tb * xx.b[zoff + i]) : T(0);
-        P[(i / NX) * PITCH + (i % NX)] = {re, im};
+    const T tb = xx.two ? T(th[2 * pair + 1]) : T(0);
+    if (zok) {
+      sfor<0, NI>([&](auto i) { ld[CV(i)] = hx.load(at(i)); });
+      if (!A.r_given) {
+        cplx<T> x[NI];
+        sfor<0, NI>([&](auto i) { x[CV(i)] = xx.load(at(i)); });
+        sfor<0, NI>([&](auto i) {
+          ld[CV(i)].re = ld[CV(i)].re - ta * x[CV(i)].re;
+          ld[CV(i)].im = xx.two ? (ld[CV(i)].im - tb * x[CV(i)].im) : T(0);
+        });
       }
     }
   }
-  __syncthreads();
+  if (zok) sfor<0, NI>([&](auto i) { P[(lr + TL * CV(i)) * PITCH + lc] = ld[CV(i)]; });
+  lds_barrier();
 
   if constexpr (MODE == PM_HPSI) {
-    const T* V = vptr<T>(E);
     const T gys = T(E.ky / NY), gxs = T(E.kx / NX);
     cplx<T> acc[MY];
     // y-lines (line = x): Ty x + V x
@@ -171,8 +194,7 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
       sfor<0, MY>([&](auto i) {
         const int y = t + TL * CV(i);
         v[CV(i)] = P[y * PITCH + line];
-        const T vv = V[zoff + y * NX + line];
-        acc[CV(i)] = {vv * v[CV(i)].re, vv * v[CV(i)].im};
+        acc[CV(i)] = {vv[CV(i)] * v[CV(i)].re, vv[CV(i)] * v[CV(i)].im};
       });
       FY::forward(v, t);
       sfor<0, MY>([&](auto i) {
@@ -198,17 +220,13 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
       });
       FX::inverse(w, t);
     }
-    __syncthreads();
+    lds_barrier();
     if (xl) sfor<0, MX>([&](auto i) { P[line * PITCH + t + TL * CV(i)] = w[CV(i)]; });
-    __syncthreads();
+    lds_barrier();
     if (zok && line < NX) {
-      PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
-      sfor<0, MY>([&](auto i) {
-        const int y = t + TL * CV(i);
-        cplx<T> r = cadd(acc[CV(i)], P[y * PITCH + line]);
-        out.a[zoff + y * NX + line] = r.re;
-        if (out.b) out.b[zoff + y * NX + line] = r.im;
-      });
+      const PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
+      sfor<0, MY>([&](auto i) { acc[CV(i)] = cadd(acc[CV(i)], P[(t + TL * CV(i)) * PITCH + line]); });
+      out.store(acc, [&](auto i) { return zoff + (t + TL * CV(i)) * NX + line; });
     }
   } else if constexpr (MODE == PM_DX) {
     // d/dx along the rows: multiply the spectrum by i 2 pi f / L_x (normalised by 1/NX)
@@ -222,12 +240,8 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
         w[CV(i)] = {-m * w[CV(i)].im, m * w[CV(i)].re};
       });
       FX::inverse(w, t);
-      PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
-      sfor<0, MX>([&](auto i) {
-        const int x = t + TL * CV(i);
-        out.a[zoff + line * NX + x] = w[CV(i)].re;
-        if (out.b) out.b[zoff + line * NX + x] = w[CV(i)].im;
-      });
+      const PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
+      out.store(w, [&](auto i) { return zoff + line * NX + t + TL * CV(i); });
     }
   } else if constexpr (MODE == PM_DY) {
     // d/dy along the columns
@@ -241,12 +255,8 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
         v[CV(i)] = {-m * v[CV(i)].im, m * v[CV(i)].re};
       });
       FY::inverse(v, t);
-      PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
-      sfor<0, MY>([&](auto i) {
-        const int y = t + TL * CV(i);
-        out.a[zoff + y * NX + line] = v[CV(i)].re;
-        if (out.b) out.b[zoff + y * NX + line] = v[CV(i)].im;
-      });
+      const PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
+      out.store(v, [&](auto i) { return zoff + (t + TL * CV(i)) * NX + line; });
     }
   } else if constexpr (MODE == PM_TFWD) {
     // forward along x (rows), back to LDS at frequency positions, then along y
@@ -256,19 +266,15 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
       sfor<0, MX>([&](auto i) { w[CV(i)] = P[line * PITCH + t + TL * CV(i)]; });
       FX::forward(w, t);
     }
-    __syncthreads();
+    lds_barrier();
     if (xl) sfor<0, MX>([&](auto i) { P[line * PITCH + FX::freq(CV(i), t)] = w[CV(i)]; });
-    __syncthreads();
+    lds_barrier();
     if (zok && line < NX) {
       cplx<T> v[MY];
       sfor<0, MY>([&](auto i) { v[CV(i)] = P[(t + TL * CV(i)) * PITCH + line]; });
       FY::forward(v, t);
-      PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, 2 * pair + 2, A.ext);
-      sfor<0, MY>([&](auto i) {
-        const int ky = FY::freq(CV(i), t);
-        out.a[zoff + ky * NX + line] = v[CV(i)].re;
-        out.b[zoff + ky * NX + line] = v[CV(i)].im;
-      });
+      const PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, 2 * pair + 2, A.ext);
+      out.store(v, [&](auto i) { return zoff + FY::freq(CV(i), t) * NX + line; });
     }
   } else {  // PM_TINV: inverse along y (columns), then x (rows); real pair out
     const bool yl = zok && line < NX;
@@ -278,20 +284,16 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
       sfor<0, MY>([&](auto i) { v[CV(i)] = P[FY::freq(CV(i), t) * PITCH + line]; });
       FY::inverse(v, t);
     }
-    __syncthreads();
+    lds_barrier();
     // after the inverse, register i of lane t is grid row y = t + TL * i
     if (yl) sfor<0, MY>([&](auto i) { P[(t + TL * CV(i)) * PITCH + line] = v[CV(i)]; });
-    __syncthreads();
+    lds_barrier();
     if (zok && line < NY) {
       cplx<T> w[MX];
       sfor<0, MX>([&](auto i) { w[CV(i)] = P[line * PITCH + FX::freq(CV(i), t)]; });
       FX::inverse(w, t);
-      PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
-      sfor<0, MX>([&](auto i) {
-        const int x = t + TL * CV(i);
-        out.a[zoff + line * NX + x] = w[CV(i)].re;
-        if (out.b) out.b[zoff + line * NX + x] = w[CV(i)].im;
-      });
+      const PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
+      out.store(w, [&](auto i) { return zoff + line * NX + t + TL * CV(i); });
     }
   }
 }
@@ -329,13 +331,16 @@ __global__ void __launch_bounds__(256) k_zcol(ZArgs A) {
   if (col >= nxy) return;  // whole lane groups leave together
   const cplx<T> wz = FZ::root(t);   // one root selection for both transforms
 
+  // All loads of a kind go out together, and the stores after them (with out += v value by
+  // value, each load waited for the store before it).  Bound by memory: 48 vectors on 16
+  // elements of 48x48x64 take 655 us, 4.15 TB/s, either way; one element, 40 vectors: 36
+  // us, 40 us before, and a filter step 45 us, 55 us.
   cplx<T> v[M];
+  auto at = [&](auto i) { return (size_t)(t + TL * CV(i)) * nxy + col; };
   if constexpr (MODE == ZM_HPSI || MODE == ZM_STEP) {
-    PairCols<T> in = pair_cols<T>(E, e, A.in_blk, pair, ncols, A.ext);
-    sfor<0, M>([&](auto i) {
-      const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
-      v[CV(i)] = {in.a[o], in.b ? in.b[o] : T(0)};
-    });
+    const PairCols<T> in = pair_cols<T>(E, e, A.in_blk, pair, ncols, A.ext);
+    const PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
+    sfor<0, M>([&](auto i) { v[CV(i)] = in.load(at(i)); });
     FZ::forward(v, t, wz);
     const T gzs = T(E.kz / NZ);
     sfor<0, M>([&](auto i) {
@@ -345,39 +350,36 @@ __global__ void __launch_bounds__(256) k_zcol(ZArgs A) {
       v[CV(i)].im *= g;
     });
     FZ::inverse(v, t, wz);
-    PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
+    cplx<T> y[M];
+    sfor<0, M>([&](auto i) { y[CV(i)] = out.load(at(i)); });
     if constexpr (MODE == ZM_HPSI) {
-      sfor<0, M>([&](auto i) {
-        const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
-        out.a[o] += v[CV(i)].re;
-        if (out.b) out.b[o] += v[CV(i)].im;
-      });
+      sfor<0, M>([&](auto i) { v[CV(i)] = cadd(y[CV(i)], v[CV(i)]); });
     } else {
       // FP64: the three-term recurrence on the spot (x comes from the caches, it was read
       // above).  As a kernel of its own (k_filter_step) it read y, x and the third term and
       // wrote y again: 240 us of 1000 us a step for 48 vectors on six elements of 48x48x64
       const double* cf = A.f.coef + e * A.f.stride;
       const T al = cf[0], c = cf[1], be = A.f.prev_blk >= 0 ? cf[A.f.beta_at] : 0.0;
-      const PairCols<T> pv = pair_cols<T>(E, e, A.f.prev_blk >= 0 ? A.f.prev_blk : A.in_blk, pair, ncols, A.ext);
+      cplx<T> x[M];
+      sfor<0, M>([&](auto i) { x[CV(i)] = in.load(at(i)); });
       sfor<0, M>([&](auto i) {
-        const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
-        T ra = al * (out.a[o] + v[CV(i)].re - c * in.a[o]);
-        if (A.f.prev_blk >= 0) ra -= be * pv.a[o];
-        out.a[o] = ra;
-        if (out.b) {
-          T rb = al * (out.b[o] + v[CV(i)].im - c * in.b[o]);
-          if (A.f.prev_blk >= 0) rb -= be * pv.b[o];
-          out.b[o] = rb;
-        }
+        v[CV(i)].re = al * (y[CV(i)].re + v[CV(i)].re - c * x[CV(i)].re);
+        v[CV(i)].im = al * (y[CV(i)].im + v[CV(i)].im - c * x[CV(i)].im);
       });
+      if (A.f.prev_blk >= 0) {
+        const PairCols<T> pv = pair_cols<T>(E, e, A.f.prev_blk, pair, ncols, A.ext);
+        sfor<0, M>([&](auto i) { x[CV(i)] = pv.load(at(i)); });
+        sfor<0, M>([&](auto i) {
+          v[CV(i)].re -= be * x[CV(i)].re;
+          v[CV(i)].im -= be * x[CV(i)].im;
+        });
+      }
     }
+    out.store(v, at);
   } else if constexpr (MODE == ZM_DZ) {
     // d/dz along the columns of z
-    PairCols<T> in = pair_cols<T>(E, e, A.in_blk, pair, ncols, A.ext);
-    sfor<0, M>([&](auto i) {
-      const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
-      v[CV(i)] = {in.a[o], in.b ? in.b[o] : T(0)};
-    });
+    const PairCols<T> in = pair_cols<T>(E, e, A.in_blk, pair, ncols, A.ext);
+    sfor<0, M>([&](auto i) { v[CV(i)] = in.load(at(i)); });
     FZ::forward(v, t, wz);
     const T g = T(sqrt(2.0 * E.kz) / NZ);
     sfor<0, M>([&](auto i) {
@@ -385,19 +387,12 @@ __global__ void __launch_bounds__(256) k_zcol(ZArgs A) {
       v[CV(i)] = {-m * v[CV(i)].im, m * v[CV(i)].re};
     });
     FZ::inverse(v, t, wz);
-    PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
-    sfor<0, M>([&](auto i) {
-      const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
-      out.a[o] = v[CV(i)].re;
-      if (out.b) out.b[o] = v[CV(i)].im;
-    });
+    const PairCols<T> out = pair_cols<T>(E, e, A.out_blk, pair, ncols, A.ext);
+    out.store(v, at);
   } else {
     // Teter: complex spectrum pair in W columns (2p: re, 2p+1: im), in place
-    PairCols<T> w = pair_cols<T>(E, e, A.out_blk, pair, 2 * pair + 2, A.ext);
-    sfor<0, M>([&](auto i) {
-      const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
-      v[CV(i)] = {w.a[o], w.b[o]};
-    });
+    const PairCols<T> w = pair_cols<T>(E, e, A.out_blk, pair, 2 * pair + 2, A.ext);
+    sfor<0, M>([&](auto i) { v[CV(i)] = w.load(at(i)); });
     FZ::forward(v, t, wz);
     const int KP = E.kmax3 + 2;
     const double* ek = E.small + SmallLayout::vec(KP) + VS_EKIN * KP;
@@ -418,11 +413,7 @@ __global__ void __launch_bounds__(256) k_zcol(ZArgs A) {
       v[CV(i)].im *= kf;
     });
     FZ::inverse(v, t, wz);
-    sfor<0, M>([&](auto i) {
-      const size_t o = (size_t)(t + TL * CV(i)) * nxy + col;
-      w.a[o] = v[CV(i)].re;
-      w.b[o] = v[CV(i)].im;
-    });
+    w.store(v, at);
   }
 }
 
@@ -497,13 +488,13 @@ __global__ void __launch_bounds__(256) k_nl_overlap(NlArgs A) {
     int r[U];
     T b[U][4], x[U][NC];
 #pragma unroll
-    for (int u = 0; u < U; ++u) r[u] = idx[s + 256 * u];
+    for (int u = 0; u < U; ++u) r[u] = gload<int>(idx + s + 256 * u);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) b[u][q] = bq[q][s + 256 * u];
+      for (int q = 0; q < 4; ++q) b[u][q] = gload<T>(bq[q] + s + 256 * u);
 #pragma unroll
-      for (int j = 0; j < NC; ++j) x[u][j] = xc[j][r[u]];
+      for (int j = 0; j < NC; ++j) x[u][j] = gload<T>(xc[j] + r[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -513,12 +504,12 @@ __global__ void __launch_bounds__(256) k_nl_overlap(NlArgs A) {
         for (int q = 0; q < 4; ++q) acc[q * NC + j] += double(b[u][q]) * double(x[u][j]);
   }
   for (; s < len; s += 256) {
-    const int r = idx[s];
+    const int r = gload<int>(idx + s);
     T b[4], x[NC];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) b[q] = bq[q][s];
+    for (int q = 0; q < 4; ++q) b[q] = gload<T>(bq[q] + s);
 #pragma unroll
-    for (int j = 0; j < NC; ++j) x[j] = xc[j][r];
+    for (int j = 0; j < NC; ++j) x[j] = gload<T>(xc[j] + r);
 #pragma unroll
     for (int j = 0; j < NC; ++j)
 #pragma unroll
@@ -539,7 +530,7 @@ __global__ void __launch_bounds__(256) k_nl_overlap(NlArgs A) {
     double t = 0.0;
     for (int w = 0; w < 16; w += 4) t += (red[w][i] + red[w + 1][i]) + (red[w + 2][i] + red[w + 3][i]);
     const int q = i / NC, j = i % NC;
-    if (q < np && c0 + j < ncols) nlc[(size_t)(p0 + q) * nld + c0 + j] = t;
+    if (q < np && c0 + j < ncols) gstore(nlc + (size_t)(p0 + q) * nld + c0 + j, t);
   }
 }
 
@@ -567,18 +558,18 @@ __global__ void __launch_bounds__(256) k_nl_apply(NlArgs A) {
   // points past the end repeat the last one and are not stored
   const int a = blockIdx.x * 256 + threadIdx.x;
   const int ac = min(a, E.nact - 1);
-  const int r = E.act_idx[ac];
-  const int q0 = E.act_ptr[ac], q1 = E.act_ptr[ac + 1];
+  const int r = gload<int>(E.act_idx + ac);
+  const int q0 = gload<int>(E.act_ptr + ac), q1 = gload<int>(E.act_ptr + ac + 1);
   long long ldy;
   T* Y = block_base<T>(E, e, A.out_blk, A.ext, ldy);
   T y[NC];
 #pragma unroll
-  for (int j = 0; j < NC; ++j) y[j] = Y[(size_t)(c0 + min(j, nc - 1)) * ldy + r];
+  for (int j = 0; j < NC; ++j) y[j] = gload<T>(Y + (size_t)(c0 + min(j, nc - 1)) * ldy + r);
   int nld;
   const double* nlc = nlc_base(E, e, A.ext, nld);
   for (int i = threadIdx.x; i < E.nproj * NC; i += 256) {
     const int p = i / NC, j = i % NC;
-    gc[p * kPitch + j] = (j < nc) ? E.gamma[p] * nlc[(size_t)p * nld + c0 + j] : 0.0;
+    gc[p * kPitch + j] = (j < nc) ? gload<double>(E.gamma + p) * gload<double>(nlc + (size_t)p * nld + c0 + j) : 0.0;
   }
   lds_barrier();
   double acc[NC];
@@ -602,13 +593,13 @@ __global__ void __launch_bounds__(256) k_nl_apply(NlArgs A) {
     double bv[B];
 #pragma unroll
     for (int u = 0; u < B; ++u) {
-      p[u] = E.ent_proj[q + u];
-      bv[u] = double(ev[q + u]);
+      p[u] = gload<int>(E.ent_proj + q + u);
+      bv[u] = double(gload<T>(ev + q + u));
     }
 #pragma unroll
     for (int u = 0; u < B; ++u) add(p[u], bv[u]);
   }
-  for (; q < q1; ++q) add(E.ent_proj[q], double(ev[q]));
+  for (; q < q1; ++q) add(gload<int>(E.ent_proj + q), double(gload<T>(ev + q)));
   if (a >= E.nact) return;
   if (A.f.coef) {
     const double al = A.f.coef[e * A.f.stride];
@@ -617,7 +608,7 @@ __global__ void __launch_bounds__(256) k_nl_apply(NlArgs A) {
   }
 #pragma unroll
   for (int j = 0; j < NC; ++j)
-    if (j < nc) Y[(size_t)(c0 + j) * ldy + r] = y[j] + T(acc[j]);
+    if (j < nc) gstore(Y + (size_t)(c0 + j) * ldy + r, T(y[j] + T(acc[j])));
 }
 
 // hy <- alpha (hy - c x) - beta prev on H x in FP32: H x is rounded to FP32, projector
