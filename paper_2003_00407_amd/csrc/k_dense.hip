@@ -692,9 +692,23 @@ constexpr int RT_NCT = RT_MAXC / 16;
 // move as one 16-byte access.
 constexpr int RT_CP = RT_CC + 2;
 
+// with three column tiles three workgroups of 256 threads share a CU (<= 168 VGPRs; at 512
+// threads one does, or with 128 VGPRs two that spill), with six one of 512
+constexpr int rt_threads(int nct) { return nct <= 3 ? 256 : 512; }
+constexpr int rt_rows(int nct) { return rt_threads(nct) / 64 * RT_RT * 16; }
+
+// Bound by memory with few columns, by the matrix cores with many; in between by how well
+// the two overlap.  A lane's S values of a chunk are two halves (k-steps 0..3, 4..7): each
+// half of the next chunk is loaded as soon as this one's is used, without a branch, so
+// that no wait comes before its use.  C chunks alternate
+// between two LDS buffers with one barrier each.
+// 16 elements of 48x48x64, 144 to 2 x 48 columns: 998 us, 4.5 TB/s (1275 us with a copy of
+// the prefetched chunk and one workgroup of 512 threads per CU); twelve uneven elements up
+// to 264 to 2 x 88 columns: 1380 us, 1475 us; one of 16^3, 36 to 2 x 12: 8.4 us, 9.3 us.
 template <typename T, int NCT>
-__global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 3 : 2) k_rotate(RotArgs A) {
+__global__ void __launch_bounds__(rt_threads(NCT), NCT <= 3 ? 3 : 2) k_rotate(RotArgs A) {
   static_assert(sizeof(T) == 8 && RT_RT == 2, "FP64 rotation with two interleaved row tiles per lane");
+  constexpr int TH = rt_threads(NCT);
   const int e = blockIdx.y;
   const ElemDev& E = A.elems[e];
   if (A.active && !A.active[e]) return;
@@ -702,14 +716,14 @@ __global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 3 : 2) k_rotate(RotArgs
   const int ncol = kcode(A.ncol, E);
   const int cld = A.c_ld > 0 ? A.c_ld : ncol;
   const int nrows = nrows_of(E, A.rows_e);
-  const int r0 = blockIdx.x * RT_ROWS;
+  const int r0 = blockIdx.x * rt_rows(NCT);
   if (r0 >= nrows) return;
   int c0[2], c1[2];
   for (int o = 0; o < 2; ++o) {
     c0[o] = A.c_blockrows > 0 ? A.c0[o] * kS : A.c0[o];
     c1[o] = A.c_blockrows > 0 ? A.c1[o] * kS : A.c1[o];
   }
-  __shared__ double sc[NCT * 16][RT_CP];
+  __shared__ double sc[2][NCT * 16][RT_CP];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int kl = lane >> 4;
   // rows of this lane: rr0, rr0 + 1 (u = 0, 1)
@@ -723,6 +737,7 @@ __global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 3 : 2) k_rotate(RotArgs
 #pragma unroll
     for (int t = 0; t < NCT; ++t) acc[u][t] = d4v{0.0, 0.0, 0.0, 0.0};
   const int nseg = A.nout > 1 ? 2 : 1;
+  int buf = 0;
   for (int sg = 0; sg < nseg; ++sg) {
     // segment bounds
     int lo, hi;
@@ -733,7 +748,6 @@ __global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 3 : 2) k_rotate(RotArgs
       lo = c0[0];
       hi = c1[0];
     }
-    // S values of the next C chunk are loaded while the current one is multiplied.
     // The (at most three) block bases of S are resolved once: a per-column lookup of
     // the block table would put a dependent pointer load before every column load.
     const T* sb0 = reinterpret_cast<const T*>(E.blk[A.S.blk[0]]);
@@ -745,83 +759,87 @@ __global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 3 : 2) k_rotate(RotArgs
       const long long off = (in2 ? d2 : (in1 ? d1 : 0LL)) + (long long)(c - (in2 ? 2 * kS : (in1 ? kS : 0))) * ldS;
       return sb0 + off;
     };
-    double av[RT_CC / 4][RT_RT], an[RT_CC / 4][RT_RT];
-    // branch-free: every lane loads one 16-byte pair from a valid address (the column
-    // clamped to lo, the row pair to 0; a lone last row's partner lies inside the
-    // leading dimension, which is even and at least N + 1 for odd N) and zeroes what
-    // is out of range
-    auto load_s = [&](int cb, double (&dst)[RT_CC / 4][RT_RT]) {
+    constexpr int KH = RT_CC / 8;   // k-steps of half a chunk
+    double2 s0[KH], s1[KH];
+    // every lane loads one 16-byte pair from a valid address (the column clamped to lo, the
+    // row pair to 0; a lone last row's partner lies inside the leading dimension, which is
+    // even and at least N + 1 for odd N): rows past the end are not stored, columns past
+    // the segment are multiplied as zero
+    const int rv = in0 ? rr0 : 0;
+    auto load_s = [&](int cb, int h, double2 (&dst)[KH]) {
 #pragma unroll
-      for (int ks = 0; ks < RT_CC / 4; ++ks) {
-        const int c = cb + kl * (RT_CC / 4) + ks;
-        const bool cin = c < hi;
-        const T* col = scol(cin ? c : lo);
-        const double2 v = gload2(col + (in0 ? rr0 : 0));
-        dst[ks][0] = (cin && in0) ? v.x : 0.0;
-        dst[ks][1] = (cin && in1) ? v.y : 0.0;
+      for (int ks = 0; ks < KH; ++ks) {
+        const int c = cb + kl * (RT_CC / 4) + h * KH + ks;
+        dst[ks] = gload2(scol(c < hi ? c : lo) + rv);
       }
     };
-    // with six column tiles (two waves per SIMD, registers to spare) the C rows of the
-    // next chunk are prefetched into registers as well; with three (three waves per
-    // SIMD) they are read when staged
-    constexpr bool kPrefC = NCT > 3;
-    constexpr int CPT = kPrefC ? (RT_CC * NCT * 16 + RT_THREADS - 1) / RT_THREADS : 1;
+    constexpr int CPT = (RT_CC * NCT * 16 + TH - 1) / TH;
     double cn[CPT];
     auto load_c = [&](int cb) {
 #pragma unroll
       for (int u = 0; u < CPT; ++u) {
-        const int idx = threadIdx.x + u * RT_THREADS;
-        const int cc = idx / (NCT * 16), j = idx % (NCT * 16);
-        const int c = cb + cc;
-        const bool ok = idx < RT_CC * NCT * 16 && c < hi && j < ncol;
-        const double v = gload<double>(Cm + (ok ? (size_t)c * cld + j : 0));
-        cn[u] = ok ? v : 0.0;
+        const int idx = threadIdx.x + u * TH;
+        const int c = cb + idx / (NCT * 16), j = idx % (NCT * 16);
+        cn[u] = gload<double>(Cm + (c < hi && j < ncol ? (size_t)c * cld + j : 0));
       }
     };
     if (lo < hi) {
-      load_s(lo, an);
-      if constexpr (kPrefC) load_c(lo);
+      load_c(lo);
+      load_s(lo, 0, s0);
+      load_s(lo, 1, s1);
     }
-    for (int cb = lo; cb < hi; cb += RT_CC) {
-      __syncthreads();
-      if constexpr (kPrefC) {
+    auto chunk = [&](int cb, auto more) {
 #pragma unroll
-        for (int u = 0; u < CPT; ++u) {
-          const int idx = threadIdx.x + u * RT_THREADS;
-          if (idx < RT_CC * NCT * 16) sc[idx % (NCT * 16)][idx / (NCT * 16)] = cn[u];
-        }
-      } else {
-        for (int idx = threadIdx.x; idx < RT_CC * NCT * 16; idx += RT_THREADS) {
-          const int cc = idx / (NCT * 16), j = idx % (NCT * 16);
-          const int c = cb + cc;
-          sc[j][cc] = (c < hi && j < ncol) ? Cm[(size_t)c * cld + j] : 0.0;
-        }
+      for (int u = 0; u < CPT; ++u) {
+        const int idx = threadIdx.x + u * TH;
+        const int cc = idx / (NCT * 16), j = idx % (NCT * 16);
+        if (idx < RT_CC * NCT * 16) sc[buf][j][cc] = cb + cc < hi && j < ncol ? cn[u] : 0.0;
       }
+      lds_barrier();
+      if (decltype(more)::value) load_c(cb + RT_CC);
+      auto half = [&](int h, double2 (&sv)[KH]) {
+        double av[KH][RT_RT];
 #pragma unroll
-      for (int ks = 0; ks < RT_CC / 4; ++ks)
-#pragma unroll
-        for (int u = 0; u < RT_RT; ++u) av[ks][u] = an[ks][u];
-      __syncthreads();
-      if (cb + RT_CC < hi) {
-        load_s(cb + RT_CC, an);
-        if constexpr (kPrefC) load_c(cb + RT_CC);
-      }
-#pragma unroll
-      for (int t = 0; t < NCT; ++t) {
-        if (t >= nct) continue;
-        const double2* q = reinterpret_cast<const double2*>(&sc[t * 16 + (lane & 15)][kl * (RT_CC / 4)]);
-        double cf[RT_CC / 4];
-#pragma unroll
-        for (int m = 0; m < RT_CC / 8; ++m) {
-          const double2 v = q[m];
-          cf[2 * m] = v.x;
-          cf[2 * m + 1] = v.y;
+        for (int ks = 0; ks < KH; ++ks) {
+          const bool in = cb + kl * (RT_CC / 4) + h * KH + ks < hi;
+          av[ks][0] = in ? sv[ks].x : 0.0;
+          av[ks][1] = in ? sv[ks].y : 0.0;
         }
+        double cf[2][KH];
+        auto coef = [&](int t) {
+          const double2* q = reinterpret_cast<const double2*>(&sc[buf][t * 16 + (lane & 15)][kl * (RT_CC / 4) + h * KH]);
 #pragma unroll
-        for (int ks = 0; ks < RT_CC / 4; ++ks)
+          for (int m = 0; m < KH / 2; ++m) {
+            const double2 v = q[m];
+            cf[t & 1][2 * m] = v.x;
+            cf[t & 1][2 * m + 1] = v.y;
+          }
+        };
+        coef(0);
 #pragma unroll
-          for (int u = 0; u < RT_RT; ++u) acc[u][t] = mfma16x16x4(cf[ks], av[ks][u], acc[u][t]);
-      }
+        for (int t = 0; t < NCT; ++t) {
+          if (t + 1 < NCT) coef(t + 1);   // one tile ahead (zeros past the last)
+          __builtin_amdgcn_sched_barrier(0);
+          if (t < nct) {
+#pragma unroll
+            for (int ks = 0; ks < KH; ++ks)
+#pragma unroll
+              for (int u = 0; u < RT_RT; ++u) acc[u][t] = mfma16x16x4(cf[t & 1][ks], av[ks][u], acc[u][t]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      half(0, s0);
+      if (decltype(more)::value) load_s(cb + RT_CC, 0, s0);
+      half(1, s1);
+      if (decltype(more)::value) load_s(cb + RT_CC, 1, s1);
+      buf ^= 1;
+    };
+    // (all but the last chunk load ahead without a branch)
+    if (lo < hi) {
+      const int last = lo + (hi - lo - 1) / RT_CC * RT_CC;
+      for (int cb = lo; cb < last; cb += RT_CC) chunk(cb, std::true_type());
+      chunk(last, std::false_type());
     }
     // store the output this segment completes: lane holds out[rows rr0, rr0 + 1][col 16 t + kl + 4 q]
     const int o = (A.nout > 1 && sg == 0) ? 1 : 0;
@@ -1826,7 +1844,6 @@ int launch_rotate(Ctx& c, int prec, const RotArgs& a_in) {
   int k, maxN, maxE;
   max_dims(c, a.ncol, &k, &maxN, &maxE);
   const int rows = a.rows_e ? maxE : maxN;
-  dim3 g((rows + RT_ROWS - 1) / RT_ROWS, c.n_elem);
   double flops = 0.0;
   for (int e = 0; e < c.n_elem; ++e) {
     if (a.active && !c.active_host.empty() && !c.active_host[e]) continue;
@@ -1842,9 +1859,12 @@ int launch_rotate(Ctx& c, int prec, const RotArgs& a_in) {
   // output column tiles: 3 (up to 48 columns) or 6 (up to 96); FP32 blocks on FP32 matrix
   // cores (BF16 matrix cores with DG_BF16=1)
   const bool k3 = k <= 48;
+  const dim3 g((rows + RT_ROWS - 1) / RT_ROWS, c.n_elem);
   if (prec == DG_FP64) {
-    if (k3) hipLaunchKernelGGL((k_rotate<double, 3>), g, dim3(RT_THREADS), 0, c.stream, a);
-    else hipLaunchKernelGGL((k_rotate<double, 6>), g, dim3(RT_THREADS), 0, c.stream, a);
+    const int rr = rt_rows(k3 ? 3 : 6);
+    const dim3 g64((rows + rr - 1) / rr, c.n_elem);
+    if (k3) hipLaunchKernelGGL((k_rotate<double, 3>), g64, dim3(rt_threads(3)), 0, c.stream, a);
+    else hipLaunchKernelGGL((k_rotate<double, 6>), g64, dim3(rt_threads(6)), 0, c.stream, a);
   } else if (!c.bf16) {
     if (k3) hipLaunchKernelGGL((k_rotate32<3>), g, dim3(RT_THREADS), 0, c.stream, a);
     else hipLaunchKernelGGL((k_rotate32<6>), g, dim3(RT_THREADS), 0, c.stream, a);

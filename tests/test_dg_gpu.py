@@ -355,7 +355,7 @@ def test_chefsi_on_the_gpu_built_hamiltonian(c2_slab):
     assert np.max(np.abs(th - lam[:60])) <= 2e-9 + 10 * dev
 
 
-@pytest.mark.parametrize("Js", [[87, 17, 40, 1, 16, 3], [1, 4, 5, 2, 3] * 14], ids=["uneven", "70_blocks_a_row"])
+@pytest.mark.parametrize("Js", [[87, 17, 40, 1, 16, 4], [1, 4, 5, 2, 3] * 14], ids=["uneven", "70_blocks_a_row"])
 @pytest.mark.parametrize("n_vec", [1, 17, 33])
 def test_chefsi_block_product_at_tile_edges(Js, n_vec):
     """H^DG of uneven random blocks: block sizes on both sides of the 16-row tiles and of
