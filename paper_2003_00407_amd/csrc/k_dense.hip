@@ -349,7 +349,9 @@ __device__ __forceinline__ f4v mfma32_16x16x4(float a, float b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// PF: staged values per thread and step (16 columns per pass of the workgroup)
+// Six uneven elements up to order 264: 1187 us, 1624 us with a value a thread, loads behind
+// branches and two barriers a panel.
+// PF: 16-byte pieces staged per thread and step (64 columns per pass of the workgroup)
 template <int MAXB, int PF>
 __global__ void __launch_bounds__(GP_THREADS, 4) k_gram32(GramArgs A) {
   const GramItem item = gram_item(A);
@@ -372,27 +374,8 @@ __global__ void __launch_bounds__(GP_THREADS, 4) k_gram32(GramArgs A) {
   const int nc = g.ncA + g.ncB + g.ncC;
   const int offB = (A.same && g.diag) ? 0 : g.ncA;
   const int offC = g.diag ? 0 : g.ncA + g.ncB;
-  extern __shared__ double gsm[];
-  float* sm = reinterpret_cast<float*>(gsm);                              // [nc][G3_RP]
-  const float** cp = reinterpret_cast<const float**>(sm + (size_t)nc * G3_RP);   // [nc]
-  for (int c = threadIdx.x; c < nc; c += GP_THREADS) {
-    const float* ptr = nullptr;
-    if (c < g.ncA) {
-      const int v = 16 * g.P0 + c;
-      if (v < ni) ptr = vcol<float>(E, A.S, v, kS);
-    } else if (c < g.ncA + g.ncB) {
-      const int v = 16 * g.Q0 + c - g.ncA;
-      if (A.same) {
-        if (v < ni) ptr = vcol<float>(E, A.S, v, kS);
-      } else if (v < nj) {
-        ptr = vcol<float>(E, A.T, v, kT);
-      }
-    } else {
-      const int v = 16 * g.Q0 + c - g.ncA - g.ncB;
-      if (v < ni) ptr = vcol<float>(E, A.S, v, kS);
-    }
-    cp[c] = ptr;
-  }
+  extern __shared__ __align__(16) double gsm[];
+  float* const sm0 = reinterpret_cast<float*>(gsm);   // two panels of [nc][G3_RP]
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int cs = (nblk_all + 7) >> 3;
   int bp[MAXB], bq[MAXB], bo[MAXB];
@@ -409,60 +392,94 @@ __global__ void __launch_bounds__(GP_THREADS, 4) k_gram32(GramArgs A) {
   d4v acc[MAXB];
 #pragma unroll
   for (int t = 0; t < MAXB; ++t) acc[t] = d4v{0.0, 0.0, 0.0, 0.0};
-  __syncthreads();
-  constexpr int kCPP = GP_THREADS / G3_R;   // columns per pass of the workgroup
-  const int srow = threadIdx.x & (G3_R - 1), scol = threadIdx.x / G3_R;
-  float pre[PF];
-  auto load = [&](int rbase) {
-    const int rr = rbase + srow;
+  // staging and the straight line of blocks as in k_gram: thread -> rows srow .. srow + 3 of
+  // columns tid / 8 + 64 u
+  constexpr int kCPP = GP_THREADS / (G3_R / 4);   // columns per pass of the workgroup
+  const int srow = 4 * (threadIdx.x & (G3_R / 4 - 1)), scol = threadIdx.x / (G3_R / 4);
+  const float* cp[PF];
 #pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      const int c = scol + kCPP * u;
-      float v = 0.f;
-      if (c < nc) {
-        const float* ptr = cp[c];
-        if (ptr && rr < r1) v = gload<float>(ptr + rr);
-      }
-      pre[u] = v;
-    }
+  for (int u = 0; u < PF; ++u) {
+    const int c = min(scol + kCPP * u, nc - 1);
+    const bool inT = c >= g.ncA && c < g.ncA + g.ncB && !A.same;
+    const int v = c < g.ncA ? 16 * g.P0 + c : 16 * g.Q0 + c - g.ncA - (c < g.ncA + g.ncB ? 0 : g.ncB);
+    cp[u] = (inT ? vcol<float>(E, A.T, v < nj ? v : 0, kT) : vcol<float>(E, A.S, v < ni ? v : 0, kS)) + srow;
+  }
+  f4v pre[PF];
+  auto load = [&](int r) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) pre[u] = gload<f4v>(cp[u] + r);
   };
   constexpr int KF = G3_R / 4;   // k-steps per panel = values per lane and fragment
-  auto frag = [&](int col, float (&f)[KF]) {
-    const float4* q = reinterpret_cast<const float4*>(sm + (size_t)(col + l16) * G3_RP + lrow);
+  int buf = 0;
+  auto stage = [&] {
+    float* st = sm0 + buf * nc * G3_RP;
 #pragma unroll
-    for (int m = 0; m < KF / 4; ++m) {
-      const float4 x = q[m];
-      f[4 * m] = x.x;
-      f[4 * m + 1] = x.y;
-      f[4 * m + 2] = x.z;
-      f[4 * m + 3] = x.w;
+    for (int u = 0; u < PF; ++u)
+      *reinterpret_cast<f4v*>(st + (size_t)min(scol + kCPP * u, nc - 1) * G3_RP + srow) = pre[u];
+    lds_barrier();
+  };
+  const int full = r0 < r1 ? (r1 - r0) / G3_R : 0, rl = r0 + full * G3_R;
+  auto run = [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    auto multiply = [&] {
+      const float* sm = sm0 + buf * nc * G3_RP + l16 * G3_RP + lrow;
+      auto frag = [&](int col, float (&f)[KF]) {
+        const f4v* q = reinterpret_cast<const f4v*>(sm + col * G3_RP);
+#pragma unroll
+        for (int m = 0; m < KF / 4; ++m) {
+          const f4v x = q[m];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) f[4 * m + i] = x[i];
+        }
+      };
+      float fa[2][KF], fb[2][KF];
+      frag(bp[0], fa[0]);
+      frag(bq[0], fb[0]);
+#pragma unroll
+      for (int t = 0; t < N; ++t) {
+        if (t + 1 < N) {
+          frag(bp[t + 1], fa[(t + 1) & 1]);
+          frag(bq[t + 1], fb[(t + 1) & 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        f4v s = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < KF; ++j) s = mfma32_16x16x4(fa[t & 1][j], fb[t & 1][j], s);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[t][q] += (double)s[q];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      buf ^= 1;
+    };
+    if (full > 0) {
+      load(r0);
+      for (int r = r0; r < rl; r += G3_R) {
+        stage();
+        load(min(r + G3_R, rl - G3_R));
+        multiply();
+      }
+    }
+    if (rl < r1) {
+      // the last rows: zero past the end
+#pragma unroll
+      for (int u = 0; u < PF; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool in = rl + srow + i < r1;
+          const float x = gload<float>(cp[u] + (in ? rl + i : -srow));
+          pre[u][i] = in ? x : 0.f;
+        }
+      stage();
+      multiply();
     }
   };
-  if (r0 < r1) load(r0);
-  for (int r = r0; r < r1; r += G3_R) {
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      const int c = scol + kCPP * u;
-      if (c < nc) sm[(size_t)c * G3_RP + srow] = pre[u];
-    }
-    __syncthreads();
-    if (r + G3_R < r1) load(r + G3_R);
-    float fa[KF];
-#pragma unroll
-    for (int j = 0; j < KF; ++j) fa[j] = 0.f;
-#pragma unroll
-    for (int t = 0; t < MAXB; ++t) {
-      if (!bv[t]) continue;
-      if (t == 0 || bp[t] != bp[t - 1]) frag(bp[t], fa);   // uniform branch: bp is wave-uniform
-      float fb[KF];
-      frag(bq[t], fb);
-      f4v s = f4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < KF; ++j) s = mfma32_16x16x4(fa[j], fb[j], s);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[t][q] += (double)s[q];
-    }
+  switch (cs) {
+    case 1: run(std::integral_constant<int, 1>()); break;
+    case 2: if constexpr (MAXB >= 2) run(std::integral_constant<int, 2>()); break;
+    case 3: if constexpr (MAXB >= 3) run(std::integral_constant<int, 3>()); break;
+    case 4: if constexpr (MAXB >= 4) run(std::integral_constant<int, 4>()); break;
+    case 5: if constexpr (MAXB >= 5) run(std::integral_constant<int, 5>()); break;
+    default: if constexpr (MAXB >= 6) run(std::integral_constant<int, 6>());
   }
   double* out = A.part + (size_t)e * A.part_stride + (size_t)split * A.part_ld * A.part_ld;
 #pragma unroll
@@ -474,7 +491,7 @@ __global__ void __launch_bounds__(GP_THREADS, 4) k_gram32(GramArgs A) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int i = i0 + 4 * (lane >> 4) + q;
-      if (i < ni && j < (second ? ni : nj)) o[(size_t)i * A.part_ld + j] = acc[t][q];
+      if (i < ni && j < (second ? ni : nj)) gstore(o + (size_t)i * A.part_ld + j, acc[t][q]);
     }
   }
 }
@@ -904,7 +921,7 @@ __global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 4 : 2) k_rotate32(RotAr
     c0[o] = A.c_blockrows > 0 ? A.c0[o] * kS : A.c0[o];
     c1[o] = A.c_blockrows > 0 ? A.c1[o] * kS : A.c1[o];
   }
-  __shared__ __attribute__((aligned(16))) float sc[NCT * 16][R3_CP];
+  __shared__ __attribute__((aligned(16))) float sc[2][NCT * 16][R3_CP];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int kl = lane >> 4;
   const int rr0 = r0 + w * RT_RT * 16 + 2 * (lane & 15);
@@ -917,6 +934,7 @@ __global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 4 : 2) k_rotate32(RotAr
 #pragma unroll
     for (int t = 0; t < NCT; ++t) acc[u][t] = f4v{0.f, 0.f, 0.f, 0.f};
   const int nseg = A.nout > 1 ? 2 : 1;
+  int buf = 0;
   for (int sg = 0; sg < nseg; ++sg) {
     int lo, hi;
     if (A.nout > 1) {
@@ -935,17 +953,16 @@ __global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 4 : 2) k_rotate32(RotAr
       const long long off = (b2 ? d2 : (b1 ? d1 : 0LL)) + (long long)(c - (b2 ? 2 * kS : (b1 ? kS : 0))) * ldS;
       return sb0 + off;
     };
-    float av[RT_CC / 4][RT_RT], an[RT_CC / 4][RT_RT];
-    // branch-free, as in k_rotate: one 8-byte pair from a valid address per column
-    auto load_s = [&](int cb, float (&dst)[RT_CC / 4][RT_RT]) {
+    // as in k_rotate: halves of the next chunk loaded as this one's are used, coefficients in
+    // two LDS buffers
+    constexpr int KH = RT_CC / 8;
+    float2 s0[KH], s1[KH];
+    const int rv = in0 ? rr0 : 0;
+    auto load_s = [&](int cb, int h, float2 (&dst)[KH]) {
 #pragma unroll
-      for (int ks = 0; ks < RT_CC / 4; ++ks) {
-        const int c = cb + kl * (RT_CC / 4) + ks;
-        const bool cin = c < hi;
-        const float* col = scol(cin ? c : lo);
-        const float2 v = gload2f(col + (in0 ? rr0 : 0));
-        dst[ks][0] = (cin && in0) ? v.x : 0.f;
-        dst[ks][1] = (cin && in1) ? v.y : 0.f;
+      for (int ks = 0; ks < KH; ++ks) {
+        const int c = cb + kl * (RT_CC / 4) + h * KH + ks;
+        dst[ks] = gload2f(scol(c < hi ? c : lo) + rv);
       }
     };
     constexpr int CPT = (RT_CC * NCT * 16 + RT_THREADS - 1) / RT_THREADS;
@@ -954,51 +971,61 @@ __global__ void __launch_bounds__(RT_THREADS, NCT <= 3 ? 4 : 2) k_rotate32(RotAr
 #pragma unroll
       for (int u = 0; u < CPT; ++u) {
         const int idx = threadIdx.x + u * RT_THREADS;
-        const int cc = idx / (NCT * 16), j = idx % (NCT * 16);
-        const int c = cb + cc;
-        const bool ok = idx < RT_CC * NCT * 16 && c < hi && j < ncol;
-        const double v = gload<double>(Cm + (ok ? (size_t)c * cld + j : 0));
-        cn[u] = ok ? v : 0.0;
+        const int c = cb + idx / (NCT * 16), j = idx % (NCT * 16);
+        cn[u] = gload<double>(Cm + (c < hi && j < ncol ? (size_t)c * cld + j : 0));
       }
     };
     if (lo < hi) {
-      load_s(lo, an);
       load_c(lo);
+      load_s(lo, 0, s0);
+      load_s(lo, 1, s1);
     }
-    for (int cb = lo; cb < hi; cb += RT_CC) {
-      __syncthreads();
+    auto chunk = [&](int cb, auto more) {
 #pragma unroll
       for (int u = 0; u < CPT; ++u) {
         const int idx = threadIdx.x + u * RT_THREADS;
-        if (idx < RT_CC * NCT * 16) sc[idx % (NCT * 16)][idx / (NCT * 16)] = (float)cn[u];
+        const int cc = idx / (NCT * 16), j = idx % (NCT * 16);
+        if (idx < RT_CC * NCT * 16) sc[buf][j][cc] = cb + cc < hi && j < ncol ? (float)cn[u] : 0.f;
       }
+      lds_barrier();
+      if (decltype(more)::value) load_c(cb + RT_CC);
+      auto half = [&](int h, float2 (&sv)[KH]) {
+        float av[KH][RT_RT];
 #pragma unroll
-      for (int ks = 0; ks < RT_CC / 4; ++ks)
-#pragma unroll
-        for (int u = 0; u < RT_RT; ++u) av[ks][u] = an[ks][u];
-      __syncthreads();
-      if (cb + RT_CC < hi) {
-        load_s(cb + RT_CC, an);
-        load_c(cb + RT_CC);
-      }
-#pragma unroll
-      for (int t = 0; t < NCT; ++t) {
-        if (t >= nct) continue;
-        const float4* q = reinterpret_cast<const float4*>(&sc[t * 16 + (lane & 15)][kl * (RT_CC / 4)]);
-        float cf[RT_CC / 4];
-#pragma unroll
-        for (int m = 0; m < RT_CC / 16; ++m) {
-          const float4 v = q[m];
-          cf[4 * m] = v.x;
-          cf[4 * m + 1] = v.y;
-          cf[4 * m + 2] = v.z;
-          cf[4 * m + 3] = v.w;
+        for (int ks = 0; ks < KH; ++ks) {
+          const bool in = cb + kl * (RT_CC / 4) + h * KH + ks < hi;
+          av[ks][0] = in ? sv[ks].x : 0.f;
+          av[ks][1] = in ? sv[ks].y : 0.f;
         }
+        f4v cf[2];
+        static_assert(KH == 4, "a half chunk's coefficients are one 16-byte piece");
+        auto coef = [&](int t) {
+          cf[t & 1] = *reinterpret_cast<const f4v*>(&sc[buf][t * 16 + (lane & 15)][kl * (RT_CC / 4) + h * KH]);
+        };
+        coef(0);
 #pragma unroll
-        for (int ks = 0; ks < RT_CC / 4; ++ks)
+        for (int t = 0; t < NCT; ++t) {
+          if (t + 1 < NCT) coef(t + 1);   // one tile ahead (zeros past the last)
+          __builtin_amdgcn_sched_barrier(0);
+          if (t < nct) {
 #pragma unroll
-          for (int u = 0; u < RT_RT; ++u) acc[u][t] = mfma32_16x16x4(cf[ks], av[ks][u], acc[u][t]);
-      }
+            for (int ks = 0; ks < KH; ++ks)
+#pragma unroll
+              for (int u = 0; u < RT_RT; ++u) acc[u][t] = mfma32_16x16x4(cf[t & 1][ks], av[ks][u], acc[u][t]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      half(0, s0);
+      if (decltype(more)::value) load_s(cb + RT_CC, 0, s0);
+      half(1, s1);
+      if (decltype(more)::value) load_s(cb + RT_CC, 1, s1);
+      buf ^= 1;
+    };
+    if (lo < hi) {
+      const int last = lo + (hi - lo - 1) / RT_CC * RT_CC;
+      for (int cb = lo; cb < last; cb += RT_CC) chunk(cb, std::true_type());
+      chunk(last, std::false_type());
     }
     // store the output this segment completes: lane holds out[rows rr0, rr0 + 1][col 16 t + 4 kl + q]
     const int o = (A.nout > 1 && sg == 0) ? 1 : 0;
@@ -1576,9 +1603,8 @@ static bool set_lds_limit(const void* fn, int bytes) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
 }
 
-// Gram instantiations: blocks per wave 1..6 x staging per thread (FP64: 16-byte pieces of
-// 64 columns a pass, 1, 2, 3, 4 or 6; FP32: values of 16 columns a pass, 8, 16 or 24;
-// BF16x3: 8 or 18).
+// Gram instantiations: blocks per wave 1..6 x staging per thread (FP64 and FP32: 16-byte
+// pieces of 64 columns a pass, 1, 2, 3, 4 or 6; BF16x3: values of 16 columns, 8 or 18).
 template <int MB>
 static void gram_attrs() {
   set_lds_limit((const void*)k_gram<double, MB, 1>, GP_LDS_LIMIT);
@@ -1588,17 +1614,23 @@ static void gram_attrs() {
   set_lds_limit((const void*)k_gram<double, MB, 6>, GP_LDS_LIMIT);
   set_lds_limit((const void*)k_gram_bf16<MB, 8>, 96000);
   set_lds_limit((const void*)k_gram_bf16<MB, 18>, 96000);
-  set_lds_limit((const void*)k_gram32<MB, 8>, GP_LDS_LIMIT);
-  set_lds_limit((const void*)k_gram32<MB, 16>, GP_LDS_LIMIT);
-  set_lds_limit((const void*)k_gram32<MB, 24>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram32<MB, 1>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram32<MB, 2>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram32<MB, 3>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram32<MB, 4>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram32<MB, 6>, GP_LDS_LIMIT);
 }
 
 template <int MB>
 static void launch_gram_mb(int prec, int pf, dim3 g, size_t lds, hipStream_t s, const GramArgs& ga, bool bf16) {
   if (prec != DG_FP64 && !bf16) {
-    if (pf <= 8) hipLaunchKernelGGL((k_gram32<MB, 8>), g, dim3(GP_THREADS), lds, s, ga);
-    else if (pf <= 16) hipLaunchKernelGGL((k_gram32<MB, 16>), g, dim3(GP_THREADS), lds, s, ga);
-    else hipLaunchKernelGGL((k_gram32<MB, 24>), g, dim3(GP_THREADS), lds, s, ga);
+    switch (pf) {
+      case 1: hipLaunchKernelGGL((k_gram32<MB, 1>), g, dim3(GP_THREADS), lds, s, ga); break;
+      case 2: hipLaunchKernelGGL((k_gram32<MB, 2>), g, dim3(GP_THREADS), lds, s, ga); break;
+      case 3: hipLaunchKernelGGL((k_gram32<MB, 3>), g, dim3(GP_THREADS), lds, s, ga); break;
+      case 4: hipLaunchKernelGGL((k_gram32<MB, 4>), g, dim3(GP_THREADS), lds, s, ga); break;
+      default: hipLaunchKernelGGL((k_gram32<MB, 6>), g, dim3(GP_THREADS), lds, s, ga);
+    }
     return;
   }
   if (prec == DG_FP64) {
@@ -1708,9 +1740,8 @@ static int gram_impl(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T,
     return DG_ERR_SHAPE;
   }
   const int maxb = (pl.maxblk + 7) / 8;   // blocks per wave, at most cap_blocks
-  // staged pieces per thread: FP64 two rows of 64 columns per pass; FP32 and BF16: a value of 16
-  const int pf = prec == DG_FP64 ? (pl.maxnc + 2 * GP_THREADS / GP_R - 1) / (2 * GP_THREADS / GP_R)
-                                 : (pl.maxnc + 15) / 16;
+  // staged per thread: FP64 and FP32 a 16-byte piece of 64 columns per pass; BF16 a value of 16
+  const int pf = bf16 ? (pl.maxnc + 15) / 16 : (pl.maxnc + 63) / 64;
   const int groups = pl.ntiles;
   // row-range split: row ranges of about 8192 rows of the largest element, and at least
   // 2048 workgroups over the launch (long single ranges leave the launch to a tail of
@@ -1738,7 +1769,7 @@ static int gram_impl(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T,
     flops += (sym ? r * ni * (ni + 1.0) : 2.0 * r * ni * nj) * (pair ? 2.0 : 1.0);
   }
   const size_t lds = prec == DG_FP64 ? (size_t)2 * GP_RP * pl.maxnc * sizeof(double)
-                     : !bf16       ? (size_t)G3_RP * pl.maxnc * sizeof(float) + (size_t)pl.maxnc * sizeof(void*)
+                     : !bf16       ? (size_t)2 * G3_RP * pl.maxnc * sizeof(float)
                                    : (size_t)3 * pl.maxnc * GB_PITCH * 2 + (size_t)pl.maxnc * sizeof(void*);
   auto launch = [&](int ns) -> int {
     ga.nsplit = ns;
