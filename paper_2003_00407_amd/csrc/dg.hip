@@ -21,7 +21,7 @@
 #include <string>
 #include <vector>
 
-#include "dg_internal.h"
+#include "dense_ops.h"
 
 namespace dg {
 
@@ -149,99 +149,138 @@ __global__ void __launch_bounds__(256) k_dg_overlap(const ElemDev* elems, const 
   }
 }
 
-constexpr int kAsmThreads = 256;
-constexpr int kAsmEntries = (88 * 88 + kAsmThreads - 1) / kAsmThreads;   // entries per thread
-constexpr int kAsmChunk = 16;                                             // face points per LDS stage
+constexpr int kAsmThreads = 512;
+constexpr int kAsmRows = 96;    // 16-row tiles of the largest J (88)
+constexpr int kAsmChunk = 16;   // points (or shared projectors) per LDS stage
 
 // block b of H^DG: local block (nb = k), shared projectors, interior-penalty terms
+//
+// Every term but the local block is a sum of products a_i b_j over face points or shared
+// projectors, so the 16 x 16 tiles of the block are FP64 matrix products; wave w has tiles
+// w, w + 8, ..  Per face, with outward derivatives d: va (c1 db + c2 vb)^T + da (c1 vb)^T.
+// A chunk is staged function by function (points contiguous) while the one before is
+// multiplied.  Bound by the matrix cores of the one CU that has a diagonal block's four
+// faces: 16 elements of 40 functions, faces of 16 x 64 points: 394 us; 1980 us with an
+// entry a thread, four LDS reads for three operations, before.
 __global__ void __launch_bounds__(kAsmThreads) k_dg_assemble(const DgElem* del, const DgBlock* blocks,
                                                              const int* pairs, const double* work, double* H,
                                                              double alpha) {
   const DgBlock& bk = blocks[blockIdx.x];
   const DgElem& A = del[bk.k];
   const DgElem& B = del[bk.nb];
-  const int Ja = A.J, Jb = B.J, nent = Ja * Jb;
-  double acc[kAsmEntries];
+  const int Ja = A.J, Jb = B.J;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int ti = (Ja + 15) / 16, nt = ti * ((Jb + 15) / 16);
+  constexpr int NT = 5;   // tiles per wave: 36 over 8 waves
+  d4v acc[NT];
 #pragma unroll
-  for (int u = 0; u < kAsmEntries; ++u) {
-    const int ent = threadIdx.x + u * kAsmThreads;
-    acc[u] = 0.0;
-    if (bk.face == 4 && ent < nent) acc[u] = work[A.l_off + ent];   // ent = i + Ja j
+  for (int u = 0; u < NT; ++u) {
+    const int tile = w + 8 * u, i0 = 16 * (tile % ti) + kq, j = 16 * (tile / ti) + l16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      acc[u][q] = bk.face == 4 && tile < nt && i0 + 4 * q < Ja && j < Jb
+                      ? work[A.l_off + i0 + 4 * q + (long long)Ja * j] : 0.0;
   }
-  // nonlocal couplings through shared projectors
-  for (int m = bk.pair_lo; m < bk.pair_hi; ++m) {
-    const int p = pairs[2 * m], q = pairs[2 * m + 1];
-    const double g = work[A.pval_off - A.np + p];   // gamma stored just before the values
-    const double* oa = work + A.ovl_off + (size_t)p * Ja;
-    const double* ob = work + B.ovl_off + (size_t)q * Jb;
+  // the operands of a chunk, rows past the last function zero: a1 b1^T + a2 b2^T
+  constexpr int P = kAsmChunk + 1;
+  __shared__ double a1[kAsmRows][P], a2[kAsmRows][P], b1[kAsmRows][P], b2[kAsmRows][P];
+  constexpr int NL = kAsmRows * kAsmChunk / kAsmThreads;   // staged per thread and operand
+  const int c = tid % kAsmChunk, jr = tid / kAsmChunk;     // point, first function
+  constexpr int JS = kAsmThreads / kAsmChunk;
+  auto multiply = [&](bool two) {
 #pragma unroll
-    for (int u = 0; u < kAsmEntries; ++u) {
-      const int ent = threadIdx.x + u * kAsmThreads;
-      if (ent < nent) acc[u] += g * oa[ent % Ja] * ob[ent / Ja];
+    for (int u = 0; u < NT; ++u) {
+      const int tile = w + 8 * u;
+      if (tile >= nt) continue;
+      const int i = 16 * (tile % ti) + l16, j = 16 * (tile / ti) + l16;
+      double x[kAsmChunk / 4], y[kAsmChunk / 4];
+#pragma unroll
+      for (int s = 0; s < kAsmChunk / 4; ++s) {
+        x[s] = a1[i][4 * s + kq];
+        y[s] = b1[j][4 * s + kq];
+      }
+#pragma unroll
+      for (int s = 0; s < kAsmChunk / 4; ++s) acc[u] = mfma16x16x4(x[s], y[s], acc[u]);
+      if (!two) continue;
+#pragma unroll
+      for (int s = 0; s < kAsmChunk / 4; ++s) {
+        x[s] = a2[i][4 * s + kq];
+        y[s] = b2[j][4 * s + kq];
+      }
+#pragma unroll
+      for (int s = 0; s < kAsmChunk / 4; ++s) acc[u] = mfma16x16x4(x[s], y[s], acc[u]);
     }
+  };
+  // nonlocal couplings through shared projectors
+  for (int m0 = bk.pair_lo; m0 < bk.pair_hi; m0 += kAsmChunk) {
+    const int m = m0 + c;
+    const bool in = m < bk.pair_hi;
+    const int p = in ? pairs[2 * m] : 0, q = in ? pairs[2 * m + 1] : 0;
+    const double g = in ? work[A.pval_off - A.np + p] : 0.0;   // gamma stored just before the values
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int j = jr + JS * u;
+      a1[j][c] = in && j < Ja ? g * work[A.ovl_off + (size_t)p * Ja + j] : 0.0;
+      b1[j][c] = in && j < Jb ? work[B.ovl_off + (size_t)q * Jb + j] : 0.0;
+    }
+    __syncthreads();
+    multiply(false);
   }
   // interior-penalty face terms: (face of k, face of nb, c1, c2); outward derivatives.
   // Same element on both sides (its four faces): -1/4 (v d' + d v') + alpha v v';
   // across a face: +1/4 (v d' + d v') - alpha v v'; each over the face sum / h_normal
-  int nf = 0, fa[4], fb[4];
-  double c1[4], c2[4];
-  if (bk.face == 4) {
-    for (int f = 0; f < 4; ++f) {
-      fa[nf] = f;
-      fb[nf] = f;
-      c1[nf] = -0.25 * A.inv_h[f >> 1];
-      c2[nf] = alpha * A.inv_h[f >> 1];
-      ++nf;
-    }
-  } else if (bk.face >= 0) {
-    const int f = bk.face;
-    fa[0] = f;
-    fb[0] = f ^ 1;
-    c1[0] = 0.25 * A.inv_h[f >> 1];
-    c2[0] = -alpha * A.inv_h[f >> 1];
-    nf = 1;
-  }
-  __shared__ double va[kAsmChunk][88], da[kAsmChunk][88], vb[kAsmChunk][88], db[kAsmChunk][88];
-  for (int t = 0; t < nf; ++t) {
-    const int npts = A.npts[fa[t]];
+  const int f0 = bk.face == 4 ? 0 : bk.face, f1 = bk.face == 4 ? 4 : bk.face + 1;
+  for (int f = f0; f >= 0 && f < f1; ++f) {
+    const int fb = bk.face == 4 ? f : f ^ 1;
+    const double sg = bk.face == 4 ? -1.0 : 1.0;
+    const double c1 = 0.25 * sg * A.inv_h[f >> 1], c2 = -sg * alpha * A.inv_h[f >> 1];
+    const int npts = A.npts[f];
     long long ba = A.tr_off, bb = B.tr_off;
-    for (int g = 0; g < fa[t]; ++g) ba += 2LL * Ja * A.npts[g];
-    for (int g = 0; g < fb[t]; ++g) bb += 2LL * Jb * B.npts[g];
+    for (int g = 0; g < f; ++g) ba += 2LL * Ja * A.npts[g];
+    for (int g = 0; g < fb; ++g) bb += 2LL * Jb * B.npts[g];
     const double* tva = work + ba;
-    const double* tda = work + ba + (size_t)Ja * npts;
+    const double* tda = tva + (size_t)Ja * npts;
     const double* tvb = work + bb;
-    const double* tdb = work + bb + (size_t)Jb * npts;
+    const double* tdb = tvb + (size_t)Jb * npts;
+    double va[NL], da[NL], vb[NL], db[NL];
+    auto load = [&](int p0) {   // functions past the last repeat it, points past the face its last
+      const int p = min(p0 + c, npts - 1);
+#pragma unroll
+      for (int u = 0; u < NL; ++u) {
+        const size_t oa = (size_t)min(jr + JS * u, Ja - 1) * npts + p, ob = (size_t)min(jr + JS * u, Jb - 1) * npts + p;
+        va[u] = gload<double>(tva + oa);
+        da[u] = gload<double>(tda + oa);
+        vb[u] = gload<double>(tvb + ob);
+        db[u] = gload<double>(tdb + ob);
+      }
+    };
+    if (npts > 0) load(0);
     for (int p0 = 0; p0 < npts; p0 += kAsmChunk) {
       __syncthreads();
-      for (int x = threadIdx.x; x < kAsmChunk * 88; x += kAsmThreads) {
-        const int c = x % kAsmChunk, j = x / kAsmChunk;
-        const bool in = p0 + c < npts;
-        va[c][j] = (in && j < Ja) ? tva[(size_t)j * npts + p0 + c] : 0.0;
-        da[c][j] = (in && j < Ja) ? tda[(size_t)j * npts + p0 + c] : 0.0;
-        vb[c][j] = (in && j < Jb) ? tvb[(size_t)j * npts + p0 + c] : 0.0;
-        db[c][j] = (in && j < Jb) ? tdb[(size_t)j * npts + p0 + c] : 0.0;
-      }
-      __syncthreads();
+      const bool in = p0 + c < npts;
 #pragma unroll
-      for (int u = 0; u < kAsmEntries; ++u) {
-        const int ent = threadIdx.x + u * kAsmThreads;
-        if (ent >= nent) continue;
-        const int i = ent % Ja, j = ent / Ja;
-        double s1 = 0.0, s2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < kAsmChunk; ++c) {
-          s1 += va[c][i] * db[c][j] + da[c][i] * vb[c][j];
-          s2 += va[c][i] * vb[c][j];
-        }
-        acc[u] += c1[t] * s1 + c2[t] * s2;
+      for (int u = 0; u < NL; ++u) {
+        const int j = jr + JS * u;
+        a1[j][c] = in && j < Ja ? va[u] : 0.0;
+        a2[j][c] = in && j < Ja ? da[u] : 0.0;
+        b1[j][c] = in && j < Jb ? c1 * db[u] + c2 * vb[u] : 0.0;
+        b2[j][c] = in && j < Jb ? c1 * vb[u] : 0.0;
       }
+      lds_barrier();
+      load(p0 + kAsmChunk);
+      multiply(true);
     }
   }
   double* out = H + bk.off;
 #pragma unroll
-  for (int u = 0; u < kAsmEntries; ++u) {
-    const int ent = threadIdx.x + u * kAsmThreads;
-    if (ent < nent) out[ent] = acc[u];
+  for (int u = 0; u < NT; ++u) {
+    const int tile = w + 8 * u, i0 = 16 * (tile % ti) + kq, j = 16 * (tile / ti) + l16;
+    if (tile >= nt || j >= Jb) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i0 + 4 * q < Ja) out[i0 + 4 * q + (long long)Ja * j] = acc[u][q];
   }
 }
 
