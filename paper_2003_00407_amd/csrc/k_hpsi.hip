@@ -113,8 +113,16 @@ __device__ __forceinline__ PairCols<T> pair_cols(const ElemDev& E, int e, int bl
 // ---------------------------------------------------------------------------
 // plane pass: x-lines and y-lines of one z-plane, several planes per block
 // ---------------------------------------------------------------------------
+// Waves per SIMD asked of the compiler.  FP64 planes of 48 points take workgroups of six
+// waves and 38 KB of LDS: at 100 VGPRs two share a CU, at 96 (five spilled) three: 681 us
+// for 48 vectors on 16 elements of 48x48x64, 725 us.  The other sizes are below a step of
+// the register file, or bound by LDS (64 points).
+template <typename T, int NX, int MODE>
+constexpr int plane_waves() {
+  return sizeof(T) == 8 && NX == 48 && MODE == PM_HPSI ? 5 : 1;
+}
 template <typename T, int NX, int NY, int TL, int MODE>
-__global__ void __launch_bounds__(512) k_plane(PlaneArgs A) {
+__global__ void __launch_bounds__(512, (plane_waves<T, NX, MODE>())) k_plane(PlaneArgs A) {
   constexpr int NL = NX > NY ? NX : NY;
   constexpr int TPP = NL * TL;
   constexpr int PPW = (256 / TPP) > 0 ? 256 / TPP : 1;
