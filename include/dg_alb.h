@@ -179,15 +179,19 @@ int32_t dg_query_offsets(const dg_ctx *ctx, int32_t kind, int64_t *offsets);
  * ldx > 0: every element's block is ldx x n_vec column-major (ldx >= N_k of
  * every element applied), element blocks ldx * n_vec values apart (elem >= 0:
  * the one block at x_dev).  prec = DG_FP64: double buffers; DG_FP32: float
- * buffers.  x and y must not overlap.  n_vec must not exceed J_k + g_k of any
+ * buffers.  x is read and y written in place; where the two buffers (first to
+ * last value, over every element applied) overlap, all of x is copied to the
+ * context's blocks before y is written, so that y holds what it would hold
+ * apart from x.  y's own columns must not overlap each other.  The values of y
+ * between columns stay as they are.  n_vec must not exceed J_k + g_k of any
  * element applied.  Errors: DG_ERR_ARG (NULL, ranges, ld too small), DG_ERR_HIP. */
 int32_t dg_apply_H(dg_ctx *ctx, int32_t elem, int32_t n_vec, int32_t prec,
                    const void *x_dev, int64_t ldx, void *y_dev, int64_t ldy);
 
 /* dg_apply_H for callers that cannot allocate device memory (code under HIP
  * stream capture, tight serving loops): the same y = H x, arguments and layouts
- * as dg_apply_H, but x is read and y written in place, without staging through
- * the context's workspace, and the only scratch, the projector overlaps
+ * as dg_apply_H, but x and y must not overlap, nothing in the context's
+ * workspace is written, and the only scratch, the projector overlaps
  * C = B^T x (nproj_k x n_vec FP64 values per applied element), lives in a
  * library-owned static device array of 16 MiB per GPU, resolved when the
  * context is created.  No device memory is allocated by the call.  Calls that

@@ -332,23 +332,29 @@ int32_t dg_apply_H(dg_ctx* ctx, int32_t elem, int32_t n_vec, int32_t prec, const
     const uintptr_t xb = reinterpret_cast<uintptr_t>(x_dev);
     const uintptr_t yb = reinterpret_cast<uintptr_t>(y_dev);
     const bool overlap = xb < yb + span(ldy) && yb < xb + span(ldx);
-    if (int st = ctx->fork()) return st;
-    int st = each_group(ctx, [&](int i) {
-      const int a = ctx->lo[i], z = ctx->lo[i + 1];
-      if (elem >= 0) {
-        if (elem < a || elem >= z) return (int)DG_OK;
-        return dg::apply_h(ctx->g[i], elem - a, n_vec, prec, x_dev, ldx, y_dev, ldy, overlap);
-      }
-      // this group's first element block: packed offsets, or a elements of ld * n_vec
-      const int64_t nv = std::max(n_vec, 0);
-      const int64_t ox = ldx > 0 ? (int64_t)a * ldx * nv : ctx->off[DG_OFF_GRID][a] * nv;
-      const int64_t oy = ldy > 0 ? (int64_t)a * ldy * nv : ctx->off[DG_OFF_GRID][a] * nv;
-      return dg::apply_h(ctx->g[i], -1, n_vec, prec, shift(x_dev, ox, sz), ldx, shift(y_dev, oy, sz), ldy,
-                         overlap);
-    });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    auto apply = [&](dg::ApplyPart part) -> int {
+      if (int st = ctx->fork()) return st;
+      const int st = each_group(ctx, [&](int i) {
+        const int a = ctx->lo[i], z = ctx->lo[i + 1];
+        if (elem >= 0) {
+          if (elem < a || elem >= z) return (int)DG_OK;
+          return dg::apply_h(ctx->g[i], elem - a, n_vec, prec, x_dev, ldx, y_dev, ldy, part);
+        }
+        // this group's first element block: packed offsets, or a elements of ld * n_vec
+        const int64_t nv = std::max(n_vec, 0);
+        const int64_t ox = ldx > 0 ? (int64_t)a * ldx * nv : ctx->off[DG_OFF_GRID][a] * nv;
+        const int64_t oy = ldy > 0 ? (int64_t)a * ldy * nv : ctx->off[DG_OFF_GRID][a] * nv;
+        return dg::apply_h(ctx->g[i], -1, n_vec, prec, shift(x_dev, ox, sz), ldx, shift(y_dev, oy, sz), ldy, part);
+      });
+      if (st < 0) return st;
+      if (int s2 = ctx->join()) return s2;
+      return st;
+    };
+    if (!overlap) return apply(dg::AP_IN_PLACE);
+    // one group's y may lie in another's x: the join and fork between the parts have every
+    // x copied before the first y is written
+    if (int st = apply(dg::AP_COPY_X)) return st;
+    return apply(dg::AP_WRITE_Y);
   })
 }
 

@@ -373,9 +373,11 @@ int launch_permute(Ctx& c, const int* perm, const int* active);
 int query_workspace(int n_elem, const dg_element_desc* d, const dg_options* opt, size_t* bytes);
 int create(Ctx** out, int n_elem, const dg_element_desc* d, const dg_options* opt, void* arena,
            size_t arena_bytes, void* stream);
-// overlap: x and y share memory
+// y = H x on caller buffers: in place, or where x and y share memory in two parts, between
+// which the caller has every group's x copied before any group's y is written
+enum ApplyPart { AP_IN_PLACE, AP_COPY_X, AP_WRITE_Y };
 int apply_h(Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx, void* y, long long ldy,
-            bool overlap);
+            ApplyPart part);
 int solve(Ctx& c, const dg_solve_params* p, double* eig, double* resid, int* iters);
 int get_vectors(Ctx& c, double* x);
 int make_alb(Ctx& c, double* alb, double* sval);

@@ -29,7 +29,7 @@ static int sync_read(Ctx& c, void* dst, const void* src, size_t bytes) {
 static long long small_code(int which) { return -1 - which; }
 
 int apply_h(Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx, void* y, long long ldy,
-            bool overlap) {
+            ApplyPart part) {
   if (!x || !y) {
     set_error("x or y is NULL");
     return DG_ERR_ARG;
@@ -61,9 +61,10 @@ int apply_h(Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx,
     }
   }
   // x is read and y written in place (with copies through the blocks W and HW, 48
-  // vectors on 16 elements of 48x48x64 took 2.72 ms, without 1.98 ms).  Only where the
-  // caller's buffers overlap is y written last: the passes read x after y's first values.
-  if (!overlap) {
+  // vectors on 16 elements of 48x48x64 took 2.72 ms, without 1.98 ms).  Where the caller's
+  // buffers overlap, all of x is copied to the blocks first: the passes read x again after
+  // y's first values.
+  if (part == AP_IN_PLACE) {
     ExtBufs ext;
     ext.x = x;
     ext.y = y;
@@ -74,11 +75,10 @@ int apply_h(Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx,
     ext.off_grid = c.dev_off_grid;
     return launch_hpsi_ext(c, elem, n_vec, prec, ext);
   }
+  if (part == AP_COPY_X) return launch_copy_ext(c, prec, B_W, x, elem, n_vec, 0, ldx);
   int st;
-  if ((st = launch_copy_ext(c, prec, B_W, x, elem, n_vec, 0, ldx))) return st;
   if ((st = launch_hpsi(c, elem, n_vec, prec, B_W, B_HW, nullptr))) return st;
-  if ((st = launch_copy_ext(c, prec, B_HW, y, elem, n_vec, 1, ldy))) return st;
-  return DG_OK;
+  return launch_copy_ext(c, prec, B_HW, y, elem, n_vec, 1, ldy);
 }
 
 // ---------------------------------------------------------------------------

@@ -135,3 +135,36 @@ def test_hpsi_projector_shapes(n_vec, prec, tol):
     assert els[1].n_proj == 465
     for some in (els[:1], els):
         assert _run(some, n_vec, prec) < tol
+
+
+@pytest.mark.parametrize("shift", ["first_y_on_last_x", "ldx_above_ldy", "ldx_below_ldy"])
+def test_hpsi_overlap_across_element_groups(shift):
+    """Overlapping buffers whose overlap crosses element groups (a stream each): every
+    group's x is read before any group's y is written.  The first element is small, so its
+    group has finished while the second one's 184 MB of x are still being copied."""
+    torch = need_torch_cuda()
+    from paper_2003_00407_amd import dgalb as D
+    els = [W._box_element((n, n, n), (0.4 * n,) * 3, np.array([[1.0, 1.0, 1.0]]), 80) for n in (12, 64)]
+    n_vec = 88
+    print(f"[hpsi] overlap across groups: {shift}", flush=True)
+    E = D.Elements(els, n_streams=2)
+    small, big = els[0].npts, els[1].npts
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    if shift == "first_y_on_last_x":     # packed; y of the small element on the last columns of the big one's x
+        total = (small + big) * n_vec
+        ldx = ldy = 0
+        x_at, y_at, size = 0, total - small * n_vec, 2 * total
+    else:                                # one start, an element's blocks further apart in one than in the other
+        a, b = big, big + small
+        ldx, ldy = (b, a) if shift == "ldx_above_ldy" else (a, b)
+        x_at = y_at = 0
+        size = 2 * b * n_vec
+    buf = torch.randn(size, dtype=torch.float64, device="cuda", generator=gen)
+    nx = total if ldx == 0 else 2 * ldx * n_vec
+    ny = total if ldy == 0 else 2 * ldy * n_vec
+    x = buf[x_at:x_at + nx].clone()
+    for _ in range(3):
+        buf[x_at:x_at + nx] = x
+        ref = E.apply_H(x, n_vec, ldx=ldx, ldy=ldy, y=buf[y_at:y_at + ny].clone())   # y's padding stays as it is
+        E.apply_H(buf[x_at:x_at + nx], n_vec, ldx=ldx, ldy=ldy, y=buf[y_at:y_at + ny])
+        assert torch.equal(buf[y_at:y_at + ny], ref)
