@@ -37,8 +37,10 @@
  *    dg_query_workspace reports.
  *  - Environment variables read by dg_create_elements (tuning and
  *    diagnostics): DG_STREAMS (element groups when n_streams <= 0);
- *    DG_TUNE=0 (no timing of the Gram row split, the size heuristic is
- *    used); DG_LOG (progress on stderr: 1 residuals per iteration and the
+ *    DG_TUNE=1 (the Gram row split is chosen by timing three candidates on
+ *    the first launch of a shape, so that the last bits of the results can
+ *    differ from one context to the next; by default it follows from the
+ *    sizes); DG_LOG (progress on stderr: 1 residuals per iteration and the
  *    tuner's choices, 2 Rayleigh-Ritz phase times, 3 Cholesky pivots; any
  *    level > 0 turns graph capture off); DG_RR_ORTOL (inverse-iteration
  *    cluster tolerance relative to ||T||, default 1e-5); DG_RR_DROP

@@ -409,7 +409,6 @@ int chefsi(hipStream_t stream, const std::vector<int>& Js, const dg_chefsi_param
     c.en[a] = {a == 0 ? Nb : 1};
   }
   c.kmax = K;
-  c.autotune = false;
   c.gram_part = (double*)(A + L.off_part);
   c.gram_part_stride = (long long)L.part_stride;
   c.gram_part_ld = L.part_ld;

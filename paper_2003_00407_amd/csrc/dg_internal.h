@@ -245,14 +245,14 @@ struct Ctx {
   long long gram_part_stride = 0;
   int gram_part_ld = 0;
   int gram_max_split = 16;
-  std::map<long long, int> gram_split_table;   // autotuned row splits per Gram shape
-  bool autotune = true;
+  std::map<long long, int> gram_split_table;   // row splits per Gram shape (DG_TUNE=1)
+  bool autotune = false;                       // DG_TUNE=1: time the row splits of a Gram shape
   bool mixed_refine = false;                   // DG_MIXED_REFINE=1: refinement with FP32 search blocks after
                                                // the FP32 stage (default: FP64 LOBPCG refinement)
   bool bf16 = false;                           // DG_BF16=1: FP32 blocks' Grams and rotations as BF16x3
   bool fresh_hp_all = false;                   // DG_FRESH_HP=1: HP = H P for every element each LOBPCG step
   bool orth_w = false;                         // W <- W - X (X^T W) before the projected problem
-                                               // (DG_ORTH_W=1); by default the overlap S^T S carries it                        // DG_TUNE=0 keeps the default splits
+                                               // (DG_ORTH_W=1); by default the overlap S^T S carries it
   int nl_pending_np = 0, nl_pending_kk = 0;
   DgOp dg_op;                      // set: H*psi is the block-sparse H^DG product
   int kmax = 0;                    // max K over elements

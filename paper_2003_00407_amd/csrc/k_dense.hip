@@ -1745,8 +1745,8 @@ static int gram_impl(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T,
   const int groups = pl.ntiles;
   // row-range split: row ranges of about 8192 rows of the largest element, and at least
   // 2048 workgroups over the launch (long single ranges leave the launch to a tail of
-  // the largest elements), at least 256 rows each; the autotuner below may replace it
-  // by half or twice that for this Gram shape (the pair keeps two sets of partials)
+  // the largest elements), at least 256 rows each (the pair keeps two sets of partials);
+  // with DG_TUNE=1 half or twice that where it is timed faster
   const int split_cap = std::max(1, std::min(pair ? (int)(c.gram_part_stride / (2 * part_sq)) : c.gram_max_split,
                                              rows / 256));
   int nsplit = std::max((rows + 8191) / 8192, (2048 + groups * c.n_elem - 1) / (groups * c.n_elem));
@@ -1791,14 +1791,13 @@ static int gram_impl(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T,
     return DG_OK;
   };
   if (tuned == c.gram_split_table.end() && c.autotune && !c.capturing) {
-    // autotuner: time the candidate splits on this launch's data, in turn in three
-    // rounds, and keep the heuristic split unless another is at least 30 % faster in
-    // each of them.  The split decides how the row sums are grouped, so a choice made
-    // by noise changes the last bits from one context to the next: other element groups
-    // share the GPU meanwhile, and with the best of three launches against 3 %, or 10 %
-    // in each round, fresh contexts of twelve uneven elements on three streams now and
-    // then chose differently.  (Over 71 shapes of 24 batches the heuristic was never
-    // beaten by 3 % without that noise.)
+    // DG_TUNE=1: time the candidate splits on this launch's data, in turn in three rounds,
+    // and keep the heuristic split unless another is at least 30 % faster in each of them.
+    // Not by default: the split decides how the row sums are grouped, so a choice made by
+    // timing changes the last bits from one context to the next (other element groups share
+    // the GPU meanwhile; with 3 %, and with 10 % in each round, fresh contexts of twelve
+    // uneven elements on three streams now and then chose differently), and over 71 shapes
+    // of 24 batches no candidate beat the heuristic by 3 % without that noise.
     const int cand[3] = {nsplit, std::max(1, nsplit / 2), std::min(split_cap, nsplit * 2)};
     float best = 1e30f, worst_ratio[3] = {0.f, 0.f, 0.f}, ms_min[3] = {1e30f, 1e30f, 1e30f};
     int best_ns = nsplit;

@@ -231,3 +231,14 @@ def test_gram_split_tuning_keeps_results(monkeypatch, capfd):
         assert max(res0[k].max(), res1[k].max()) <= 1e-8
         assert np.max(np.abs(eig0[k] - eig1[k])) < 1e-10
         assert oalb.max_principal_angle(X0[k], X1[k]) < 1e-6
+
+
+def test_gram_split_is_not_timed_by_default(monkeypatch, capfd):
+    """Without DG_TUNE the Gram row split follows from the sizes alone: a choice made by
+    timing would change the last bits of the results from one context to the next."""
+    monkeypatch.delenv("DG_TUNE", raising=False)
+    monkeypatch.setenv("DG_LOG", "1")
+    _, eig, res, it, st = _solve(W.make_config("c2").elements[:2], tol=1e-3, n_streams=1)
+    log = capfd.readouterr().err
+    assert st == 0 and "[dg]" in log
+    assert "gram autotune" not in log
