@@ -396,3 +396,33 @@ def test_chefsi_block_product_at_tile_edges(Js, n_vec):
     assert np.max(np.abs(Xg.T @ Xg - np.eye(n_vec))) <= 4 * Nb * np.finfo(float).eps
     assert np.max(np.abs(np.sum(Xg * HX, axis=0) - th)) <= bound
     assert np.max(np.abs(np.linalg.norm(HX - Xg * th, axis=0) - res.cpu().numpy())) <= bound
+
+
+def _uneven_mesh(Js, elem_pts=7, nq=12, nz=12):
+    """A 3x3 mesh of elements with unequal numbers of ALBs, on faces of elem_pts x nz points
+    (84: five staged chunks of 16 and a quarter), E_k off the centre of Q_k, and projectors
+    on random points: four sites over all elements, six over one or two of them."""
+    rng = np.random.default_rng(21)
+    m, h = 3, W.H_SPACING
+    ng = (m * elem_pts, m * elem_pts, nz)
+    length = tuple(n * h for n in ng)
+    mesh = W.Mesh(m, elem_pts, ng, length, atoms=[])
+    cells = [mesh.elem_global_indices(k) for k in range(m * m)]
+    for members, n in [(range(9), 300), (range(9), 301)] * 2 + [((0, 8), 90), ((1,), 40), ((5, 8), 33), ((2, 3), 70),
+                                                                ((4,), 1), ((0, 1), 64)]:
+        pts = np.sort(rng.choice(np.concatenate([cells[k] for k in members]), size=n, replace=False))
+        mesh.atoms.append((pts, rng.standard_normal((4, n)) / np.sqrt(n)))
+    z = np.zeros(0)
+    els = [W.Element(n=(nq, nq, nz), length=(nq * h, nq * h, nz * h), elem_lo=(2, 3, 0),
+                     elem_n=(elem_pts, elem_pts, nz), n_states=J, v_eff=rng.standard_normal(nq * nq * nz),
+                     proj_ptr=np.zeros(1, np.int64), proj_idx=z.astype(np.int32), proj_val=z, gamma=z)
+           for J in Js]
+    return els, mesh
+
+
+def test_dg_hamiltonian_uneven_blocks_vs_oracle():
+    """Block tiles in every round a wave takes (up to 6 x 6 of them), rectangular blocks,
+    a partial last chunk of face points and of shared projectors."""
+    els, mesh = _uneven_mesh([84, 17, 65, 48, 33, 80, 16, 1, 84])
+    X0 = [W.initial_block(el.npts, el.n_states + W.guard_count(el.n_states), 800 + k).T for k, el in enumerate(els)]
+    _check_hamiltonian(_run(els, mesh, X0))
