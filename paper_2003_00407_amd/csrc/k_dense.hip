@@ -178,9 +178,8 @@ __device__ __forceinline__ void gram_run_block(const GramTile& g, int bprime, in
 }
 
 // PF: 16-byte pieces staged per thread and step (64 columns per pass of the workgroup)
-template <typename T, int MAXB, int PF>
-__global__ void __launch_bounds__(GP_THREADS, MAXB <= 6 ? 4 : 2) k_gram(GramArgs A) {
-  static_assert(sizeof(T) == 8, "FP64 Gram");
+template <int MAXB, int PF>
+__global__ void __launch_bounds__(GP_THREADS, 4) k_gram(GramArgs A) {
   const GramItem item = gram_item(A);
   if (!item.valid) return;
   const int e = item.e;
@@ -227,13 +226,13 @@ __global__ void __launch_bounds__(GP_THREADS, MAXB <= 6 ? 4 : 2) k_gram(GramArgs
   // tile's last; neither reaches an entry that is stored.
   constexpr int kCPP = GP_THREADS / (GP_R / 2);   // columns per pass of the workgroup
   const int srow = 2 * (threadIdx.x & (GP_R / 2 - 1)), scol = threadIdx.x / (GP_R / 2);
-  const T* cp[PF];
+  const double* cp[PF];
 #pragma unroll
   for (int u = 0; u < PF; ++u) {
     const int c = min(scol + kCPP * u, nc - 1);
     const bool inT = c >= g.ncA && c < g.ncA + g.ncB && !A.same;
     const int v = c < g.ncA ? 16 * g.P0 + c : 16 * g.Q0 + c - g.ncA - (c < g.ncA + g.ncB ? 0 : g.ncB);
-    cp[u] = (inT ? vcol<T>(E, A.T, v < nj ? v : 0, kT) : vcol<T>(E, A.S, v < ni ? v : 0, kS)) + srow;
+    cp[u] = (inT ? vcol<double>(E, A.T, v < nj ? v : 0, kT) : vcol<double>(E, A.S, v < ni ? v : 0, kS)) + srow;
   }
   double2 pre[PF];
   auto load = [&](int r) {
@@ -307,7 +306,7 @@ __global__ void __launch_bounds__(GP_THREADS, MAXB <= 6 ? 4 : 2) k_gram(GramArgs
       multiply();
     }
   };
-  switch (cs) {
+  switch (cs) {   // cs <= MAXB: the launch's plan covers every element shape (gram_blocks_per_wave)
     case 1: run(std::integral_constant<int, 1>()); break;
     case 2: if constexpr (MAXB >= 2) run(std::integral_constant<int, 2>()); break;
     case 3: if constexpr (MAXB >= 3) run(std::integral_constant<int, 3>()); break;
@@ -418,7 +417,6 @@ __global__ void __launch_bounds__(GP_THREADS, 4) k_gram32(GramArgs A) {
       *reinterpret_cast<f4v*>(st + (size_t)min(scol + kCPP * u, nc - 1) * G3_RP + srow) = pre[u];
     lds_barrier();
   };
-  const int full = r0 < r1 ? (r1 - r0) / G3_R : 0, rl = r0 + full * G3_R;
   auto run = [&](auto n) {
     constexpr int N = decltype(n)::value;
     auto multiply = [&] {
@@ -451,26 +449,13 @@ __global__ void __launch_bounds__(GP_THREADS, 4) k_gram32(GramArgs A) {
       }
       buf ^= 1;
     };
-    if (full > 0) {
+    if (r0 < r1) {   // a whole number of panels: every FP32 block has a multiple of G3_R rows
       load(r0);
-      for (int r = r0; r < rl; r += G3_R) {
+      for (int r = r0; r < r1; r += G3_R) {
         stage();
-        load(min(r + G3_R, rl - G3_R));
+        load(min(r + G3_R, r1 - G3_R));
         multiply();
       }
-    }
-    if (rl < r1) {
-      // the last rows: zero past the end
-#pragma unroll
-      for (int u = 0; u < PF; ++u)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool in = rl + srow + i < r1;
-          const float x = gload<float>(cp[u] + (in ? rl + i : -srow));
-          pre[u][i] = in ? x : 0.f;
-        }
-      stage();
-      multiply();
     }
   };
   switch (cs) {
@@ -722,9 +707,9 @@ constexpr int rt_rows(int nct) { return rt_threads(nct) / 64 * RT_RT * 16; }
 // 16 elements of 48x48x64, 144 to 2 x 48 columns: 998 us, 4.5 TB/s (1275 us with a copy of
 // the prefetched chunk and one workgroup of 512 threads per CU); twelve uneven elements up
 // to 264 to 2 x 88 columns: 1380 us, 1475 us; one of 16^3, 36 to 2 x 12: 8.4 us, 9.3 us.
-template <typename T, int NCT>
+template <int NCT>
 __global__ void __launch_bounds__(rt_threads(NCT), NCT <= 3 ? 3 : 2) k_rotate(RotArgs A) {
-  static_assert(sizeof(T) == 8 && RT_RT == 2, "FP64 rotation with two interleaved row tiles per lane");
+  static_assert(RT_RT == 2, "two interleaved row tiles per lane");
   constexpr int TH = rt_threads(NCT);
   const int e = blockIdx.y;
   const ElemDev& E = A.elems[e];
@@ -767,11 +752,11 @@ __global__ void __launch_bounds__(rt_threads(NCT), NCT <= 3 ? 3 : 2) k_rotate(Ro
     }
     // The (at most three) block bases of S are resolved once: a per-column lookup of
     // the block table would put a dependent pointer load before every column load.
-    const T* sb0 = reinterpret_cast<const T*>(E.blk[A.S.blk[0]]);
-    const long long d1 = A.S.nb > 1 ? reinterpret_cast<const T*>(E.blk[A.S.blk[1]]) - sb0 : 0;
-    const long long d2 = A.S.nb > 2 ? reinterpret_cast<const T*>(E.blk[A.S.blk[2]]) - sb0 : 0;
+    const double* sb0 = reinterpret_cast<const double*>(E.blk[A.S.blk[0]]);
+    const long long d1 = A.S.nb > 1 ? reinterpret_cast<const double*>(E.blk[A.S.blk[1]]) - sb0 : 0;
+    const long long d2 = A.S.nb > 2 ? reinterpret_cast<const double*>(E.blk[A.S.blk[2]]) - sb0 : 0;
     const long long ldS = E.ld;
-    auto scol = [&](int c) -> const T* {
+    auto scol = [&](int c) -> const double* {
       const bool in1 = c >= kS, in2 = c >= 2 * kS;
       const long long off = (in2 ? d2 : (in1 ? d1 : 0LL)) + (long long)(c - (in2 ? 2 * kS : (in1 ? kS : 0))) * ldS;
       return sb0 + off;
@@ -860,7 +845,7 @@ __global__ void __launch_bounds__(rt_threads(NCT), NCT <= 3 ? 3 : 2) k_rotate(Ro
     }
     // store the output this segment completes: lane holds out[rows rr0, rr0 + 1][col 16 t + kl + 4 q]
     const int o = (A.nout > 1 && sg == 0) ? 1 : 0;
-    T* out = reinterpret_cast<T*>(E.blk[A.out_blk[o]]);
+    double* out = reinterpret_cast<double*>(E.blk[A.out_blk[o]]);
     const double beta = A.beta[o];
 #pragma unroll
     for (int t = 0; t < NCT; ++t) {
@@ -869,7 +854,7 @@ __global__ void __launch_bounds__(rt_threads(NCT), NCT <= 3 ? 3 : 2) k_rotate(Ro
       for (int q = 0; q < 4; ++q) {
         const int j = t * 16 + kl + 4 * q;
         if (j >= ncol) continue;
-        T* p = out + (size_t)j * E.ld + rr0;
+        double* p = out + (size_t)j * E.ld + rr0;
         // the beta term: the output's own values, or those of an FP32 block
         const float* p32 = A.add32 ? reinterpret_cast<const float*>(E.blk[A.add32_blk[o]]) + (size_t)j * E.ld + rr0
                                    : nullptr;
@@ -889,7 +874,7 @@ __global__ void __launch_bounds__(rt_threads(NCT), NCT <= 3 ? 3 : 2) k_rotate(Ro
           gstore2(p, v.x, v.y);
         } else if (in0) {
           const double prev = beta != 0.0 ? beta * (p32 ? (double)*p32 : double(*p)) : 0.0;
-          *p = T(prev + A.alpha * acc[0][t][q]);
+          *p = prev + A.alpha * acc[0][t][q];
         }
       }
     }
@@ -1607,11 +1592,11 @@ static bool set_lds_limit(const void* fn, int bytes) {
 // pieces of 64 columns a pass, 1, 2, 3, 4 or 6; BF16x3: values of 16 columns, 8 or 18).
 template <int MB>
 static void gram_attrs() {
-  set_lds_limit((const void*)k_gram<double, MB, 1>, GP_LDS_LIMIT);
-  set_lds_limit((const void*)k_gram<double, MB, 2>, GP_LDS_LIMIT);
-  set_lds_limit((const void*)k_gram<double, MB, 3>, GP_LDS_LIMIT);
-  set_lds_limit((const void*)k_gram<double, MB, 4>, GP_LDS_LIMIT);
-  set_lds_limit((const void*)k_gram<double, MB, 6>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram<MB, 1>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram<MB, 2>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram<MB, 3>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram<MB, 4>, GP_LDS_LIMIT);
+  set_lds_limit((const void*)k_gram<MB, 6>, GP_LDS_LIMIT);
   set_lds_limit((const void*)k_gram_bf16<MB, 8>, 96000);
   set_lds_limit((const void*)k_gram_bf16<MB, 18>, 96000);
   set_lds_limit((const void*)k_gram32<MB, 1>, GP_LDS_LIMIT);
@@ -1635,11 +1620,11 @@ static void launch_gram_mb(int prec, int pf, dim3 g, size_t lds, hipStream_t s, 
   }
   if (prec == DG_FP64) {
     switch (pf) {
-      case 1: hipLaunchKernelGGL((k_gram<double, MB, 1>), g, dim3(GP_THREADS), lds, s, ga); break;
-      case 2: hipLaunchKernelGGL((k_gram<double, MB, 2>), g, dim3(GP_THREADS), lds, s, ga); break;
-      case 3: hipLaunchKernelGGL((k_gram<double, MB, 3>), g, dim3(GP_THREADS), lds, s, ga); break;
-      case 4: hipLaunchKernelGGL((k_gram<double, MB, 4>), g, dim3(GP_THREADS), lds, s, ga); break;
-      default: hipLaunchKernelGGL((k_gram<double, MB, 6>), g, dim3(GP_THREADS), lds, s, ga);
+      case 1: hipLaunchKernelGGL((k_gram<MB, 1>), g, dim3(GP_THREADS), lds, s, ga); break;
+      case 2: hipLaunchKernelGGL((k_gram<MB, 2>), g, dim3(GP_THREADS), lds, s, ga); break;
+      case 3: hipLaunchKernelGGL((k_gram<MB, 3>), g, dim3(GP_THREADS), lds, s, ga); break;
+      case 4: hipLaunchKernelGGL((k_gram<MB, 4>), g, dim3(GP_THREADS), lds, s, ga); break;
+      default: hipLaunchKernelGGL((k_gram<MB, 6>), g, dim3(GP_THREADS), lds, s, ga);
     }
   } else {
     if (pf <= 8) hipLaunchKernelGGL((k_gram_bf16<MB, 8>), g, dim3(GP_THREADS), lds, s, ga);
@@ -1669,6 +1654,19 @@ void init_kernel_attributes() {
 struct GramPlan {
   int tb = 1, maxblk = 0, maxnc = 0, ntiles = 0;
 };
+
+// blocks per wave of a plan's largest tile: the instantiation to launch.  No element of the
+// launch has more: the plan goes over every number of block rows there is, with the most
+// block columns (fewer make no tile larger).
+static int gram_blocks_per_wave(const GramPlan& pl) { return (pl.maxblk + 7) / 8; }
+
+// dynamic LDS of a Gram launch: two panels (FP64, FP32), or three BF16 planes and the
+// column pointers
+static size_t gram_lds_bytes(const GramPlan& pl, bool fp64, bool bf16) {
+  return fp64    ? (size_t)2 * GP_RP * pl.maxnc * sizeof(double)
+         : !bf16 ? (size_t)2 * G3_RP * pl.maxnc * sizeof(float)
+                 : (size_t)3 * pl.maxnc * GB_PITCH * 2 + (size_t)pl.maxnc * sizeof(void*);
+}
 
 static GramPlan plan_gram_tiles(const std::vector<int>& bis, int bj_max, int sym, int same, int pair,
                                 int max_blocks, int max_cols) {
@@ -1734,12 +1732,18 @@ static int gram_impl(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T,
   const bool bf16 = prec != DG_FP64 && c.bf16;
   const int cap_blocks = 6;
   const int cap_cols = prec == DG_FP64 ? GP_MAXCOL : (bf16 ? 128 : G3_MAXCOL);
+  if (prec != DG_FP64 && !bf16)   // k_gram32 takes whole panels: every supported grid has some
+    for (int e = 0; e < c.n_elem; ++e)
+      if (rows_e || c.N[e] % G3_R != 0) {
+        set_error("FP32 Gram of a number of rows that is no multiple of " + std::to_string(G3_R));
+        return DG_ERR_SHAPE;
+      }
   const GramPlan pl = plan_gram_tiles(bis, bj_max, sym, same ? 1 : 0, pair ? 1 : 0, cap_blocks, cap_cols);
   if (pl.maxblk == 0) {
     set_error("Gram: no tile fits the per-workgroup limits");
     return DG_ERR_SHAPE;
   }
-  const int maxb = (pl.maxblk + 7) / 8;   // blocks per wave, at most cap_blocks
+  const int maxb = gram_blocks_per_wave(pl);   // at most cap_blocks
   // staged per thread: FP64 and FP32 a 16-byte piece of 64 columns per pass; BF16 a value of 16
   const int pf = bf16 ? (pl.maxnc + 15) / 16 : (pl.maxnc + 63) / 64;
   const int groups = pl.ntiles;
@@ -1768,9 +1772,7 @@ static int gram_impl(Ctx& c, int prec, const ColSet& S, int kS, const ColSet& T,
     const double ni = S.nb * ke, nj = T.nb * kt;
     flops += (sym ? r * ni * (ni + 1.0) : 2.0 * r * ni * nj) * (pair ? 2.0 : 1.0);
   }
-  const size_t lds = prec == DG_FP64 ? (size_t)2 * GP_RP * pl.maxnc * sizeof(double)
-                     : !bf16       ? (size_t)2 * G3_RP * pl.maxnc * sizeof(float)
-                                   : (size_t)3 * pl.maxnc * GB_PITCH * 2 + (size_t)pl.maxnc * sizeof(void*);
+  const size_t lds = gram_lds_bytes(pl, prec == DG_FP64, bf16);
   auto launch = [&](int ns) -> int {
     ga.nsplit = ns;
     ga.part_pair = ns * part_sq;
@@ -1893,8 +1895,8 @@ int launch_rotate(Ctx& c, int prec, const RotArgs& a_in) {
   if (prec == DG_FP64) {
     const int rr = rt_rows(k3 ? 3 : 6);
     const dim3 g64((rows + rr - 1) / rr, c.n_elem);
-    if (k3) hipLaunchKernelGGL((k_rotate<double, 3>), g64, dim3(rt_threads(3)), 0, c.stream, a);
-    else hipLaunchKernelGGL((k_rotate<double, 6>), g64, dim3(rt_threads(6)), 0, c.stream, a);
+    if (k3) hipLaunchKernelGGL((k_rotate<3>), g64, dim3(rt_threads(3)), 0, c.stream, a);
+    else hipLaunchKernelGGL((k_rotate<6>), g64, dim3(rt_threads(6)), 0, c.stream, a);
   } else if (!c.bf16) {
     if (k3) hipLaunchKernelGGL((k_rotate32<3>), g, dim3(RT_THREADS), 0, c.stream, a);
     else hipLaunchKernelGGL((k_rotate32<6>), g, dim3(RT_THREADS), 0, c.stream, a);
