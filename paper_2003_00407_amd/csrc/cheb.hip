@@ -152,21 +152,6 @@ int run_chfsi(Ctx& c, int prec, double tol, int max_iter, int degree, int* iters
 // ---------------------------------------------------------------------------
 // band energy E = sum_i f_i psi_i^T H psi_i, Psi = p_m(H) Psi_0, and its adjoint
 // ---------------------------------------------------------------------------
-struct BELayout {
-  int nseg, s, m;
-  int ck_prev(int j) const { return s == 1 ? ck_cur(j - 1) : kMaxBlocks + 2 * j; }   // Y_{js-1}, j >= 1
-  int ck_cur(int j) const { return kMaxBlocks + 2 * j + 1; }                         // Y_{js}
-  int ym() const { return kMaxBlocks + 2 * nseg; }
-  int hym() const { return ym() + 1; }
-  int seg(int i) const { return hym() + 1 + i; }
-  // where the forward pass keeps Y_k: a checkpoint, the result, or nowhere (-1)
-  int kept(int k) const {
-    if (k == m) return ym();
-    if (k % s == 0) return ck_cur(k / s);
-    return (k + 1) % s == 0 && k + 1 < m ? ck_prev((k + 1) / s) : -1;
-  }
-};
-
 int band_energy(Ctx& c, int prec, int degree, const double* bounds_host, int n_vec, const void* psi0,
                 const double* f, double* E) {
   if (!bounds_host || !psi0 || !f || !E) {
@@ -194,7 +179,7 @@ int band_energy(Ctx& c, int prec, int degree, const double* bounds_host, int n_v
     }
   }
   int st;
-  BELayout L{(degree + c.ckpt_stride - 1) / c.ckpt_stride, c.ckpt_stride, degree};
+  const BELayout L(degree, c.ckpt_stride);
   c.be_bounds_host.assign(bounds_host, bounds_host + 3 * c.n_elem);
   DG_HIP(hipMemcpyAsync(c.dev_bounds, c.be_bounds_host.data(), sizeof(double) * 3 * c.n_elem,
                         hipMemcpyHostToDevice, c.stream));
@@ -234,7 +219,7 @@ int band_energy_backward(Ctx& c, const double* dE_host, void* dpsi0, void* dv) {
   }
   int st;
   const int prec = c.be_prec, n_vec = c.be_nvec, m = c.be_degree;
-  BELayout L{(m + c.ckpt_stride - 1) / c.ckpt_stride, c.ckpt_stride, m};
+  const BELayout L(m, c.ckpt_stride);
   const double* bd = c.dev_bounds;
   c.be_de_host.assign(dE_host, dE_host + c.n_elem);
   DG_HIP(hipMemcpyAsync(c.dev_de, c.be_de_host.data(), sizeof(double) * c.n_elem, hipMemcpyHostToDevice,

@@ -16,8 +16,28 @@ constexpr int kMaxBlocks = 8;     // solver blocks per element (roles permuted p
 // projectors per element: the nonlocal apply stages gamma C (17 doubles per projector)
 // in 64 KB of dynamic LDS
 constexpr int kMaxProjectors = 480;
-constexpr int kExtraBlocks = 40;  // band-energy checkpoint / segment blocks (allocated on demand)
+constexpr int kExtraBlocks = 40;  // most band-energy checkpoint / segment blocks
 constexpr int kTotalBlocks = kMaxBlocks + kExtraBlocks;
+
+// Blocks of a band energy of degree m with a checkpoint pair (Y_{js-1}, Y_{js}) every s
+// steps, after the solver's: the pairs (Y_{js-1} is the checkpoint before where s = 1, and
+// Y_{-1} is none), Y_m, H Y_m, and the iterates of a segment behind its checkpoint.
+struct BELayout {
+  int m, s, nseg;
+  BELayout(int degree, int stride) : m(degree), s(stride), nseg((degree + stride - 1) / stride) {}
+  int ck_cur(int j) const { return kMaxBlocks + (s == 1 ? j : 2 * j); }               // Y_{js}
+  int ck_prev(int j) const { return ck_cur(s == 1 ? j - 1 : j) - (s == 1 ? 0 : 1); }   // Y_{js-1}, j >= 1
+  int ym() const { return ck_cur(nseg - 1) + 1; }
+  int hym() const { return ym() + 1; }
+  int seg(int i) const { return hym() + i; }   // Y_{js+i}, 1 <= i < s
+  int n_blocks() const { return seg(s < m ? s : m) - kMaxBlocks; }
+  // where the forward pass keeps Y_k: a checkpoint, the result, or nowhere (-1)
+  int kept(int k) const {
+    if (k == m) return ym();
+    if (k % s == 0) return ck_cur(k / s);
+    return (k + 1) % s == 0 && k + 1 < m ? ck_prev((k + 1) / s) : -1;
+  }
+};
 enum BlockId { B_X = 0, B_W = 1, B_P = 2, B_HX = 3, B_HW = 4, B_HP = 5, B_T0 = 6, B_T1 = 7 };
 
 // Per-element data resident on the device (read-only in kernels).
@@ -197,15 +217,12 @@ struct Ctx {
   int dg_max_np = 0;               // DG build: most projectors on one E_k of this group
   int solved_K3 = 0;
   // band-energy state
-  int be_degree = 0, be_prec = 0, be_nvec = 0, be_stride = 1, be_nckpt = 0;
+  int be_degree = 0, be_prec = 0, be_nvec = 0;
   std::vector<double> be_bounds;
   std::vector<double> be_alpha, be_beta, be_c;   // per element coefficient arrays
   const void* be_psi0 = nullptr;
   const double* be_f = nullptr;
   bool be_valid = false;
-  void* ckpt_base = nullptr;       // checkpoint region
-  size_t ckpt_bytes_per_block = 0; // sum over elements of ld*K*8
-  std::vector<int64_t> ckpt_off;   // per element offset (bytes) inside one checkpoint block
   int max_cheb = 0, ckpt_stride = 1;
   // timing
   bool timing = false;
@@ -225,7 +242,6 @@ struct Ctx {
   double* dev_minpiv = nullptr;    // diagnostics: smallest scaled overlap pivot of the last RR
   int* dev_hpflag = nullptr;       // per element: the last RR's basis is ill-conditioned (H P afresh)
   std::vector<double> be_bounds_host, be_de_host;
-  int n_extra_blocks = 0;
   long long* dev_off_x0 = nullptr; // packed offsets (doubles), per element
   long long* dev_off_vec = nullptr;
   long long* dev_off_alb = nullptr;

@@ -141,9 +141,7 @@ struct Plan {
   int n_extra;
   size_t off_offx0, off_offvec, off_offalb, off_offgrid, off_offeig, off_offkall, off_offelem, off_offjj,
       off_nprojoff, off_lists;
-  size_t off_ckpt, off_part;
-  size_t ckpt_block_bytes;
-  int n_ckpt;
+  size_t off_part;
   int part_ld, nsplit_max;
   size_t part_stride;
   size_t total;
@@ -264,13 +262,15 @@ static int make_plan(int n_elem, const dg_element_desc* d, const dg_options* opt
     kmax = std::max(kmax, p.K);
     build_proj_plan(d[e], p.N, P.proj[e]);
   }
-  // band energy: checkpoint pairs every ckpt_stride steps, Y_m, H Y_m, one segment
-  P.n_extra = max_cheb > 0 ? 2 * ((max_cheb + stride - 1) / stride) + 2 + stride : 0;
-  if (P.n_extra > kExtraBlocks) {
-    set_error("max_cheb_degree / ckpt_stride need " + std::to_string(P.n_extra) +
+  // band energy: the blocks of the largest degree (a smaller one takes no more).  The limit
+  // counts a whole pair per checkpoint and a whole segment; fewer blocks than that exist.
+  const long long slots = max_cheb > 0 ? 2 * (((long long)max_cheb + stride - 1) / stride) + 2 + stride : 0;
+  if (slots > kExtraBlocks) {
+    set_error("max_cheb_degree / ckpt_stride need " + std::to_string(slots) +
               " checkpoint blocks (limit " + std::to_string(kExtraBlocks) + "); raise ckpt_stride");
     return DG_ERR_ARG;
   }
+  P.n_extra = max_cheb > 0 ? BELayout(max_cheb, stride).n_blocks() : 0;
   P.part_ld = 3 * kmax;
   P.nsplit_max = std::max(1, std::min(64, 4096 / n_elem));
   size_t off = 0;
@@ -301,7 +301,6 @@ static int make_plan(int n_elem, const dg_element_desc* d, const dg_options* opt
   P.off_offjj = take(sizeof(long long) * (n_elem + 1));
   P.off_nprojoff = take(sizeof(long long) * (n_elem + 1));
   P.off_lists = take(sizeof(int) * n_elem);
-  size_t ckpt_block = 0;
   for (int e = 0; e < n_elem; ++e) {
     ElemPlan& p = P.el[e];
     const ProjPlan& pp = P.proj[e];
@@ -326,11 +325,7 @@ static int make_plan(int n_elem, const dg_element_desc* d, const dg_options* opt
     for (int b = 0; b < p.n_blocks; ++b) p.off_blk[b] = take(sizeof(double) * (size_t)p.ld * p.Kpad);
     p.off_small = take(sizeof(double) * SmallLayout::total(p.KP));
     p.off_nlc = take(sizeof(double) * (size_t)std::max(1, d[e].n_proj) * p.kmax3);
-    ckpt_block += align256(sizeof(double) * (size_t)p.ld * p.Kpad);
   }
-  P.ckpt_block_bytes = ckpt_block;
-  P.n_ckpt = max_cheb > 0 ? (max_cheb / stride + 2) : 0;
-  P.off_ckpt = take(P.ckpt_block_bytes * P.n_ckpt + 256);
   // split-N Gram partials; the same region is the Rayleigh-Ritz inverse-iteration workspace
   P.part_stride = std::max((size_t)P.nsplit_max * P.part_ld * P.part_ld, (size_t)6 * (P.part_ld + 2) * 512);
   P.off_part = take(sizeof(double) * (size_t)n_elem * P.part_stride);
@@ -597,23 +592,12 @@ int create(Ctx** out, int n_elem, const dg_element_desc* d, const dg_options* op
   c->dev_de = (double*)(A + P.off_de);
   c->dev_minpiv = (double*)(A + P.off_minpiv);
   c->dev_hpflag = (int*)(A + P.off_hpflag);
-  c->n_extra_blocks = P.n_extra;
   c->dev_phase = (long long*)(A + P.off_phase);
   c->dev_maxres = (double*)(A + P.off_maxres);
   c->gram_part_ld = P.part_ld;
   c->gram_max_split = P.nsplit_max;
   c->gram_part = (double*)(A + P.off_part);
   c->gram_part_stride = (long long)P.part_stride;
-  c->ckpt_base = A + P.off_ckpt;
-  c->ckpt_bytes_per_block = P.ckpt_block_bytes;
-  c->ckpt_off.assign(n_elem, 0);
-  {
-    size_t o = 0;
-    for (int e = 0; e < n_elem; ++e) {
-      c->ckpt_off[e] = (int64_t)o;
-      o += align256(sizeof(double) * (size_t)P.el[e].ld * P.el[e].Kpad);
-    }
-  }
   c->elems_dev = (ElemDev*)(A + P.off_elems);
   if ((st = cpy(P.off_elems, c->elems_host.data(), sizeof(ElemDev) * n_elem))) return st;
   // zero the blocks so padded columns and unused tails are defined

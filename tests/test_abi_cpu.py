@@ -42,6 +42,34 @@ def test_query_workspace_sizes():
     assert b2 > b1
 
 
+@pytest.mark.parametrize("degree,stride", [(1, 1), (16, 1), (16, 2), (13, 4), (6, 3), (4, 9), (17, 2)])
+def test_query_workspace_counts_the_band_energy_blocks(degree, stride):
+    """Behind the solver's blocks there is one per iterate that a band energy keeps (Y_k
+    where a segment starts and the one before it), Y_m, H Y_m, and one segment's inside."""
+    d = _lib()
+    el = W.make_config("c1").elements[0]
+    kept = {k for k in range(degree) if k % stride == 0 or ((k + 1) % stride == 0 and k + 1 < degree)}
+    blocks = len(kept) + 2 + min(stride, degree) - 1
+    K = el.n_states + W.guard_count(el.n_states)
+    assert el.npts % 64 == 0 and K % 2 == 0
+    more = d.query_workspace([el], max_cheb_degree=degree, ckpt_stride=stride) - d.query_workspace([el])
+    assert more == blocks * el.npts * K * 8
+
+
+@pytest.mark.parametrize("degree,stride,ok", [(19, 1, False), (18, 1, True), (18, 2, True), (64, 8, True),
+                                              (30, 30, True), (4, 37, False), (2 ** 31 - 1, 1, False)])
+def test_query_workspace_band_energy_limit(degree, stride, ok):
+    """The limit on degree and stride: pairs, two results and a segment within 40."""
+    d = _lib()
+    el = W.make_config("c1").elements[0]
+    if ok:
+        assert d.query_workspace([el], max_cheb_degree=degree, ckpt_stride=stride) > 0
+        return
+    with pytest.raises(d.DGError) as e:
+        d.query_workspace([el], max_cheb_degree=degree, ckpt_stride=stride)
+    assert e.value.status == d.DG_ERR_ARG
+
+
 def test_query_workspace_rejects_bad_input():
     d = _lib()
     el = W.make_config("c1").elements[0]
