@@ -97,6 +97,18 @@ struct dg_ctx {
     }
     return DG_OK;
   }
+  // the join, also where a group failed: what the others have queued on the caller's
+  // buffers stays ordered before the caller's next work
+  int join_after(int st) {
+    if (st >= 0) {
+      const int s2 = join();
+      return s2 ? s2 : st;
+    }
+    const std::string why = dg::get_error();
+    (void)join();
+    dg::set_error(why);
+    return st;
+  }
   ~dg_ctx() {
     for (Ctx& c : g) {
       for (const dg::PendingTime& p : c.pending) {
@@ -176,6 +188,16 @@ int each_group(dg_ctx* b, F f) {
     worst = std::max(worst, st);
   }
   return worst;
+}
+
+// every group's part of a call is checked before any group queues work: a refused call
+// writes nothing and leaves the state of the calls before it
+int check_apply(dg_ctx* b, int elem, int n_vec, int prec, const void* x, int64_t ldx, const void* y, int64_t ldy) {
+  return each_group(b, [&](int i) {
+    const int a = b->lo[i], z = b->lo[i + 1];
+    if (elem >= 0 && (elem < a || elem >= z)) return (int)DG_OK;
+    return dg::check_apply_h(b->g[i], elem >= 0 ? elem - a : -1, n_vec, prec, x, ldx, y, ldy);
+  });
 }
 
 }  // namespace
@@ -322,6 +344,7 @@ int32_t dg_apply_H(dg_ctx* ctx, int32_t elem, int32_t n_vec, int32_t prec, const
       dg::set_error("ldx and ldy must be >= 0");
       return DG_ERR_ARG;
     }
+    if (int st = check_apply(ctx, elem, n_vec, prec, x_dev, ldx, y_dev, ldy)) return st;
     const size_t sz = prec == DG_FP32 ? sizeof(float) : sizeof(double);
     // values from a buffer's first to its last, over every group
     const int64_t pts = elem >= 0 ? ctx->off[DG_OFF_GRID][elem + 1] - ctx->off[DG_OFF_GRID][elem]
@@ -346,9 +369,7 @@ int32_t dg_apply_H(dg_ctx* ctx, int32_t elem, int32_t n_vec, int32_t prec, const
         const int64_t oy = ldy > 0 ? (int64_t)a * ldy * nv : ctx->off[DG_OFF_GRID][a] * nv;
         return dg::apply_h(ctx->g[i], -1, n_vec, prec, shift(x_dev, ox, sz), ldx, shift(y_dev, oy, sz), ldy, part);
       });
-      if (st < 0) return st;
-      if (int s2 = ctx->join()) return s2;
-      return st;
+      return ctx->join_after(st);
     };
     if (!overlap) return apply(dg::AP_IN_PLACE);
     // one group's y may lie in another's x: the join and fork between the parts have every
@@ -374,9 +395,7 @@ int32_t dg_solve_elements(dg_ctx* ctx, const dg_solve_params* params, double* ei
                        shift(resid_dev, ctx->off[DG_OFF_EIG][a], sizeof(double)),
                        iters_host ? iters_host + a : nullptr);
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    return ctx->join_after(st);
   })
 }
 
@@ -396,6 +415,7 @@ int32_t dg_apply_H_noalloc(dg_ctx* ctx, int32_t elem, int32_t n_vec, int32_t pre
       dg::set_error("ldx and ldy must be >= 0 and n_vec > 0");
       return DG_ERR_ARG;
     }
+    if (int st = check_apply(ctx, elem, n_vec, prec, x_dev, ldx, y_dev, ldy)) return st;
     // scratch: nproj x n_vec doubles per applied element, groups in disjoint parts
     std::vector<long long> base(ctx->groups() + 1, 0);
     for (int i = 0; i < ctx->groups(); ++i) {
@@ -427,9 +447,7 @@ int32_t dg_apply_H_noalloc(dg_ctx* ctx, int32_t elem, int32_t n_vec, int32_t pre
       return dg::apply_h_noalloc(ctx->g[i], -1, n_vec, prec, shift(x_dev, ox, sz), ldx, shift(y_dev, oy, sz),
                                  ldy, nlc);
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    return ctx->join_after(st);
   })
 }
 
@@ -549,8 +567,7 @@ int32_t dg_build_hamiltonian(dg_ctx* ctx, const dg_mesh_desc* mesh, double* hdg_
       for (int k = ctx->lo[i]; k < ctx->lo[i + 1]; ++k) c.dg_max_np = std::max(c.dg_max_np, mi.count[k]);
       return dg::dg_element_terms(c, work, del);
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
+    if (int s2 = ctx->join_after(st)) return s2;
     if (int s3 = dg::dg_assemble(ctx->user, P, work, hdg_dev, mi.alpha)) return s3;
     DG_HIP(hipStreamSynchronize(ctx->user));
     return DG_OK;
@@ -568,9 +585,7 @@ int32_t dg_get_ritz(dg_ctx* ctx, double* theta_dev, double* resid_dev) {
       const int64_t o = ctx->off[DG_OFF_KALL][ctx->lo[i]];
       return dg::get_ritz(ctx->g[i], shift(theta_dev, o, sizeof(double)), shift(resid_dev, o, sizeof(double)));
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    return ctx->join_after(st);
   })
 }
 
@@ -584,9 +599,7 @@ int32_t dg_get_vectors(dg_ctx* ctx, double* x_dev) {
     int st = each_group(ctx, [&](int i) {
       return dg::get_vectors(ctx->g[i], shift(x_dev, ctx->off[DG_OFF_VEC][ctx->lo[i]], sizeof(double)));
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    return ctx->join_after(st);
   })
 }
 
@@ -602,9 +615,7 @@ int32_t dg_make_alb(dg_ctx* ctx, double* alb_dev, double* sval_dev) {
       return dg::make_alb(ctx->g[i], shift(alb_dev, ctx->off[DG_OFF_ALB][a], sizeof(double)),
                           shift(sval_dev, ctx->off[DG_OFF_EIG][a], sizeof(double)));
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    return ctx->join_after(st);
   })
 }
 
@@ -675,9 +686,7 @@ int32_t dg_density(dg_ctx* ctx, const double* alb_dev, const double* c_dev, int6
                          shift(p_dev, ctx->off[DG_OFF_JJ][a], sizeof(double)),
                          shift(rho_dev, ctx->off[DG_OFF_ELEM][a], sizeof(double)));
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    return ctx->join_after(st);
   })
 }
 
@@ -688,6 +697,11 @@ int32_t dg_band_energy(dg_ctx* ctx, int32_t prec, int32_t degree, const double* 
     return DG_ERR_ARG;
   }
   DG_GUARD({
+    const int ok = each_group(ctx, [&](int i) {
+      return dg::check_band_energy(ctx->g[i], prec, degree, bounds_host ? bounds_host + 3 * ctx->lo[i] : nullptr, n_vec,
+                                   psi0_dev, f_dev, E_dev);
+    });
+    if (ok < 0) return ok;
     const size_t sz = prec == DG_FP32 ? sizeof(float) : sizeof(double);
     if (int st = ctx->fork()) return st;
     int st = each_group(ctx, [&](int i) {
@@ -696,11 +710,11 @@ int32_t dg_band_energy(dg_ctx* ctx, int32_t prec, int32_t degree, const double* 
       return dg::band_energy(ctx->g[i], prec, degree, bounds_host ? bounds_host + 3 * a : nullptr, n_vec,
                              shift(psi0_dev, o, sz), f_dev, E_dev ? E_dev + a : nullptr);
     });
-    if (st < 0) return st;
-    ctx->be_prec = prec;
-    ctx->be_nvec = n_vec;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    if (st >= 0) {
+      ctx->be_prec = prec;
+      ctx->be_nvec = n_vec;
+    }
+    return ctx->join_after(st);
   })
 }
 
@@ -719,9 +733,7 @@ int32_t dg_band_energy_backward(dg_ctx* ctx, const double* dE_host, void* dpsi0_
                                       shift(dpsi0_dev, og * (int64_t)ctx->be_nvec, sz),
                                       shift(dv_dev, og, sizeof(double)));
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    return ctx->join_after(st);
   })
 }
 
@@ -735,9 +747,7 @@ int32_t dg_set_potential(dg_ctx* ctx, const double* v_dev) {
     int st = each_group(ctx, [&](int i) {
       return dg::set_potential(ctx->g[i], shift(v_dev, ctx->off[DG_OFF_GRID][ctx->lo[i]], sizeof(double)));
     });
-    if (st < 0) return st;
-    if (int s2 = ctx->join()) return s2;
-    return st;
+    return ctx->join_after(st);
   })
 }
 

@@ -152,8 +152,8 @@ int run_chfsi(Ctx& c, int prec, double tol, int max_iter, int degree, int* iters
 // ---------------------------------------------------------------------------
 // band energy E = sum_i f_i psi_i^T H psi_i, Psi = p_m(H) Psi_0, and its adjoint
 // ---------------------------------------------------------------------------
-int band_energy(Ctx& c, int prec, int degree, const double* bounds_host, int n_vec, const void* psi0,
-                const double* f, double* E) {
+int check_band_energy(const Ctx& c, int prec, int degree, const double* bounds_host, int n_vec, const void* psi0,
+                      const double* f, const double* E) {
   if (!bounds_host || !psi0 || !f || !E) {
     set_error("bounds, psi0, f and E must be non-NULL");
     return DG_ERR_ARG;
@@ -178,6 +178,11 @@ int band_energy(Ctx& c, int prec, int degree, const double* bounds_host, int n_v
       return DG_ERR_ARG;
     }
   }
+  return DG_OK;
+}
+
+int band_energy(Ctx& c, int prec, int degree, const double* bounds_host, int n_vec, const void* psi0,
+                const double* f, double* E) {
   int st;
   const BELayout L(degree, c.ckpt_stride);
   c.be_bounds_host.assign(bounds_host, bounds_host + 3 * c.n_elem);

@@ -392,6 +392,8 @@ int create(Ctx** out, int n_elem, const dg_element_desc* d, const dg_options* op
 // y = H x on caller buffers: in place, or where x and y share memory in two parts, between
 // which the caller has every group's x copied before any group's y is written
 enum ApplyPart { AP_IN_PLACE, AP_COPY_X, AP_WRITE_Y };
+int check_apply_h(const Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx, const void* y,
+                  long long ldy);
 int apply_h(Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx, void* y, long long ldy,
             ApplyPart part);
 int solve(Ctx& c, const dg_solve_params* p, double* eig, double* resid, int* iters);
@@ -403,6 +405,8 @@ size_t chefsi_work_bytes(int M, int Nb, int K, int n_blocks);
 int chefsi(hipStream_t stream, const std::vector<int>& Js, const dg_chefsi_params& p, int n_blocks,
            const int64_t* row_ptr, const int32_t* col_idx, const int64_t* block_off, const double* hdg,
            double* x, double* eig, double* resid, void* work, size_t work_bytes, int* iters_out);
+int check_band_energy(const Ctx& c, int prec, int degree, const double* bounds_host, int n_vec, const void* psi0,
+                      const double* f, const double* E);
 int band_energy(Ctx& c, int prec, int degree, const double* bounds_host, int n_vec, const void* psi0,
                 const double* f, double* E);
 int band_energy_backward(Ctx& c, const double* dE_host, void* dpsi0, void* dv);

@@ -42,33 +42,6 @@ int noalloc_scratch(int device, double** ptr) {
 // scratch (nproj_off[n_elem] * n_vec doubles, checked by the caller)
 int apply_h_noalloc(Ctx& c, int elem, int n_vec, int prec, const void* x, long long ldx, void* y, long long ldy,
                     double* nlc) {
-  if (!x || !y || !nlc) {
-    set_error("x, y or the scratch is NULL");
-    return DG_ERR_ARG;
-  }
-  if (elem < -1 || elem >= c.n_elem) {
-    set_error("elem out of range");
-    return DG_ERR_ARG;
-  }
-  if (prec != DG_FP64 && prec != DG_FP32) {
-    set_error("prec must be DG_FP64 or DG_FP32");
-    return DG_ERR_ARG;
-  }
-  if (ldx < 0 || ldy < 0) {
-    set_error("ldx and ldy must be >= 0");
-    return DG_ERR_ARG;
-  }
-  for (int e = 0; e < c.n_elem; ++e) {
-    if (elem >= 0 && e != elem) continue;
-    if (n_vec <= 0 || n_vec > c.K[e] + (c.K[e] & 1)) {
-      set_error("n_vec must be in [1, J_k + guards] for every element applied");
-      return DG_ERR_ARG;
-    }
-    if ((ldx > 0 && ldx < c.N[e]) || (ldy > 0 && ldy < c.N[e])) {
-      set_error("ldx / ldy below the grid size N_k of element " + std::to_string(e + c.elem_base));
-      return DG_ERR_ARG;
-    }
-  }
   ExtBufs ext;
   ext.x = x;
   ext.y = y;

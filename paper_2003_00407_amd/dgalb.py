@@ -324,11 +324,11 @@ class Elements:
         if bnd.size != 3 * self.n_elem:
             raise ValueError("bounds needs 3 values per element")
         E = self._dev(self.n_elem, torch.float64)
-        self._be_f = f          # must outlive the backward
         self.generation += 1
         _check(_lib.dg_band_energy(self.ctx, prec, degree, _ptr(bnd, C.c_double), n_vec,
                                    C.c_void_p(psi0.data_ptr()), C.c_void_p(f.data_ptr()),
                                    C.c_void_p(E.data_ptr())), "dg_band_energy")
+        self._be_f = f          # must outlive the backward (a refused call leaves the one before)
         self._be_shape = (psi0.numel(), psi0.dtype)
         return E
 

@@ -302,3 +302,53 @@ def test_band_energy_state_is_invalidated():
         out1.sum().backward()
     out2.sum().backward()
     assert torch.isfinite(x.grad).all()
+
+
+def _two_groups(D, **kw):
+    """An element that takes 20 columns and one that takes 8, a group each."""
+    els = [dataclasses.replace(el, n_states=j) for el, j in zip(W.small_slab(n_states=8)[:2], (16, 4))]
+    return els, D.Elements(els, n_streams=2, **kw)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_refused_apply_writes_nothing(noalloc):
+    """n_vec fits the first group's element and not the second's: the call is refused before
+    any group has queued work."""
+    torch = need_torch_cuda()
+    D = _D()
+    els, E = _two_groups(D)
+    n_vec = 12
+    x = torch.randn(sum(e.npts for e in els) * n_vec, dtype=torch.float64, device="cuda")
+    y = torch.full_like(x, float("nan"))
+    with pytest.raises(D.DGError) as ex:
+        if noalloc:
+            E.apply_H_noalloc(x, y, n_vec)
+        else:
+            E.apply_H(x, n_vec, y=y)
+    assert ex.value.status == D.DG_ERR_ARG
+    torch.cuda.synchronize()
+    assert torch.isnan(y).all()
+
+
+def test_refused_band_energy_leaves_the_one_before():
+    """A band energy that one group refuses (too many columns) leaves every group's state:
+    the backward of the one before gives its gradients, in its shapes."""
+    torch = need_torch_cuda()
+    D = _D()
+    rng = np.random.default_rng(6)
+    got = []
+    for refused in (False, True):
+        els, E = _two_groups(D, max_cheb_degree=4, ckpt_stride=2)
+        n = sum(e.npts for e in els)
+        if not got:
+            psi = torch.tensor(rng.standard_normal(n * 12) * 0.01, dtype=torch.float64, device="cuda")
+        bounds = np.array([(0.4, 95.0, -1.0)] * len(els))
+        f = torch.ones(12, dtype=torch.float64, device="cuda")
+        E.band_energy(psi[:n * 3].contiguous(), f[:3].contiguous(), 4, bounds)
+        if refused:
+            with pytest.raises(D.DGError) as ex:
+                E.band_energy(psi, f, 4, bounds)
+            assert ex.value.status == D.DG_ERR_ARG
+        got.append(E.band_energy_backward(np.ones(len(els))))
+    for a, b in zip(*got):
+        assert a.numel() == b.numel() and torch.isfinite(a).all() and torch.equal(a, b)
