@@ -619,8 +619,9 @@ __global__ void __launch_bounds__(256) k_nl_apply(NlArgs A) {
     if (j < nc) gstore(Y + (size_t)(c0 + j) * ldy + r, T(y[j] + T(acc[j])));
 }
 
-// hy <- alpha (hy - c x) - beta prev on H x in FP32: H x is rounded to FP32, projector
-// term included, before the step, which the fused pass could not keep
+// hy <- alpha (hy - c x) - beta prev on H x in FP32: H x is rounded to FP32, projector term
+// included, before the step.  The fused pass would not keep that at the points that have
+// projector entries (their term comes after it)
 __global__ void __launch_bounds__(256) k_filter_step(const ElemDev* elems, const int* active, int x_blk, int hy_blk,
                                                      int cols, FilterStep f) {
   const int e = blockIdx.z;

@@ -32,13 +32,14 @@ struct RRArgs {
   int mode;
   int* status;         // per element: 0 ok, 2 breakdown of the X block
   long long* phase_clk;  // optional: 16 timestamps per element (diagnostics)
-  double* work;          // per element work region (the working matrix above kRRLdsOrder)
+  double* work;          // per element work region: the overlap factorisation's matrix, and the
+                         // tridiagonalisation's where an order is above kRRLdsOrder
   long long work_stride;
   double pivot_tol;      // X-column overlap pivots below this (after unit-diagonal scaling) = breakdown
   double drop_tol;       // W/P columns whose scaled pivot is below this are left out of the basis
   double* minpiv;        // optional: smallest scaled pivot, its column, dropped count (diagnostics)
   double ortol;          // eigenvalues closer than ortol * ||T|| are treated as one cluster
-  int lds_dyn;           // dynamic LDS bytes of the launch (LDS variant)
+  int mgs_lds;           // dynamic LDS bytes of the Gram-Schmidt launch
   int* hp_flag;          // optional, per element: 1 when the smallest scaled pivot is below hp_tol
                          // (the rotated H P' would carry cancellation error), 0 otherwise and
                          // for inactive elements
@@ -1060,7 +1061,7 @@ __global__ void __launch_bounds__(NT) k_rr_mgs(RRArgs A) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   double* zj = dyn;                 // the current vector
   double* zl = dyn + np;            // vectors 0 .. cap - 1
-  const int cap = min(nwant, A.lds_dyn / (np * (int)sizeof(double)) - 1);
+  const int cap = min(nwant, A.mgs_lds / (np * (int)sizeof(double)) - 1);
   for (int idx = tid; idx < cap * np; idx += NT) zl[idx] = Zv[idx];
   __syncthreads();
   for (int j = 1; j < nwant; ++j) {
@@ -1343,7 +1344,7 @@ int launch_rr(Ctx& c, int nb, int kfix, int nkeep, int mode, const int* active) 
   RRArgs a{c.elems_dev, active, nb, kfix, nkeep, mode, c.dev_status,
            c.log_level >= 2 ? c.dev_phase : nullptr, c.gram_part, c.gram_part_stride,
            c.rr_pivot_tol, c.rr_drop_tol, c.log_level >= 3 ? c.dev_minpiv : nullptr, c.rr_ortol,
-           in_lds ? (int)need : 0, mode == RR_GEN ? c.dev_hpflag : nullptr, c.hp_tol};
+           0, mode == RR_GEN ? c.dev_hpflag : nullptr, c.hp_tol};
   TimedScope ts(c, TC_RR, flops);
   auto over = [](int n, int per) { return (unsigned)((n + per - 1) / per); };
   const unsigned ne = (unsigned)c.n_elem;
@@ -1367,7 +1368,7 @@ int launch_rr(Ctx& c, int nb, int kfix, int nkeep, int mode, const int* active) 
     hipLaunchKernelGGL(k_rr_inv, dim3(over(nwmax, kInvPerWg), ne), dim3(64), inv_lds(npmax), c.stream, a);
     // as many vectors as fit, and the current one
     const size_t mgs = std::min((size_t)kMgsLds, (size_t)(nwmax + 1) * npmax * sizeof(double));
-    a.lds_dyn = (int)mgs;
+    a.mgs_lds = (int)mgs;
     if (in_lds) {
       hipLaunchKernelGGL(k_rr_mgs<512>, dim3(ne), dim3(512), mgs, c.stream, a);
       hipLaunchKernelGGL(k_rr_back<false>, dim3(over(nwmax, kBackVecs<false>), ne), dim3(kBackThreads),
