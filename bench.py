@@ -30,7 +30,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 FP64_PEAK_TFLOPS = 78.6        # MI355X FP64 (vector and matrix)
 BF16_PEAK_TFLOPS = 2500.0      # MI355X dense BF16 matrix
 CLASSES = ("plane", "zcol", "nonlocal", "teter", "gram", "rotate", "rayleigh_ritz", "other")
-# kernel symbol of each timing class's main kernel (rocprofv3 names)
+# kernel symbol of each timing class's main kernel (rocprofv3 names; the Rayleigh-Ritz
+# class is k_rr_chol .. k_rr_coef, its label the name of the one kernel they came from)
 CLASS_KERNEL = {"plane": "k_plane", "zcol": "k_zcol", "nonlocal": "k_nl_", "teter": "k_plane",
                 "gram": "k_gram", "rotate": "k_rotate", "rayleigh_ritz": "k_rr_lds", "other": "k_residual"}
 METRIC = "ALB element-solves/s + Hψ GB/s, mixed vs FP64 on one GPU at 1e-8 Ha eigen error"
@@ -46,8 +47,8 @@ PMC_TRAFFIC = {
     "gram": {"config": "c4/1",
              "source": ["paper_2003_00407_amd/csrc/k_dense.hip", "paper_2003_00407_amd/csrc/runtime.hip",
                         "workloads/__init__.py"],
-             "sha256": "79189e84464e9d8b358d53c4c53c961a316af2aaf671714964dd442ee5fd3c17",
-             "bytes_per_launch": 214595375967},
+             "sha256": "2f5df9f2ddb6bb9a94cf05cdf92f435d178ebc822ec53a24835dd3aa046287f7",
+             "bytes_per_launch": 210379159044},
 }
 
 
