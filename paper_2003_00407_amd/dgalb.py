@@ -233,7 +233,7 @@ class Elements:
         ctx = getattr(self, "ctx", None)
         if ctx is not None and ctx.value:
             self._destroy(ctx)
-            self.ctx = C.c_void_p(0)
+            ctx.value = None
 
     # ---- layout helpers
     def offsets(self, kind: int) -> np.ndarray:

@@ -203,3 +203,18 @@ def test_pack_initial_layout():
     g = W.guard_count(els[0].n_states)
     assert x0.size == sum(e.npts * (e.n_states + g) for e in els)
     assert np.array_equal(x0[: els[0].npts], W.initial_block(els[0].npts, els[0].n_states + g, 10)[0])
+
+
+def test_destructor_at_interpreter_exit(monkeypatch):
+    """A context still alive when the interpreter clears the module's globals is released
+    once, without an error."""
+    d = _lib()
+    E = object.__new__(d.Elements)
+    E.ctx = ctypes.c_void_p(16)
+    calls = []
+    E._destroy = lambda ctx: calls.append(ctx.value)
+    with monkeypatch.context() as m:
+        m.setattr(d, "C", None)
+        E.__del__()
+        E.__del__()
+    assert calls == [16] and E.ctx.value is None
